@@ -33,62 +33,44 @@ namespace vct {
 
 int nlist_check(const vct_nlist* nl, Grid& g);
 
-constexpr int kColCap = 7168;                // row entries of a chunk staged in LDS
+// Launch classes, chosen on the host by the mean row length (short_row in
+// tiles.h).  A row's entries are spread over `lanes` lanes that hold `slots` of
+// them each in registers, and both passes run over every slot, so the slots
+// that a set's rows do not fill are work for nothing: the long-row shape (112
+// entries, Wendland C2 with R = 3 d0 in 3-D: 103) costs a 2-D set with 26
+// neighbours four times the pair terms it needs and reserves five times its
+// LDS window, which leaves two work-groups on a CU where six fit.
+//   kShort2: 2-D rows up to about 28 entries, 4 lanes x 7 slots in 256-thread
+//     groups (8 lanes x 4 slots: 30-40% slower), windows up to 448 records
+//     (297 at R = 3 d0).  1,048,576 particles, R = 3 d0: FP64 0.385 -> 0.127
+//     ms, mixed 0.235 -> 0.086 ms (floor at the copy rate: 0.07 and 0.05 ms).
+//   kShort3: 3-D rows up to 64 entries (cubic spline, R = 2.4 d0: 57), 4 lanes
+//     x 16 slots, row entries read straight into the registers and a window
+//     that lets three groups share a CU (53,760 bytes each: LDS comes in
+//     pieces of 1,280 bytes).  2,097,152 particles: FP64 1.29 -> 0.91 ms,
+//     mixed 0.82 -> 0.63 ms; with 8 lanes x 8 slots and two groups 0.97 and
+//     0.70 ms.
+// A row longer than its class's slots finishes in a loop over the rest, a
+// window larger than the class's reads its records from memory: a set whose
+// rows are short on average but not everywhere stays correct.
+enum { kLongRows = 0, kShort3 = 1, kShort2 = 2 };
 
 // Lanes per particle, register slots per lane, occupancy target (waves per
-// SIMD) and LDS window capacity (records) of each arithmetic type
-// (overridable at build time for tuning).  Both forms run 512-thread groups
-// (8 lanes per particle) at 4 waves per SIMD, two groups per CU.  The FP64
-// form's FP64 records and sums take a smaller window (about 77 KB of LDS per
-// group) and fill the 128 VGPRs that 4 waves allow (a few prologue and
-// epilogue values go to scratch, none of the pair loops' values).
-#ifndef VCT_APPLY_F_LANES
-#define VCT_APPLY_F_LANES 8
-#endif
-#ifndef VCT_APPLY_F_SLOTS
-#define VCT_APPLY_F_SLOTS 14
-#endif
-#ifndef VCT_APPLY_F_WAVES
-#define VCT_APPLY_F_WAVES 4
-#endif
-#ifndef VCT_APPLY_F_WIN
-#define VCT_APPLY_F_WIN 1664
-#endif
-#ifndef VCT_APPLY_D_LANES
-#define VCT_APPLY_D_LANES 8
-#endif
-#ifndef VCT_APPLY_D_SLOTS
-#define VCT_APPLY_D_SLOTS 14
-#endif
-#ifndef VCT_APPLY_D_WAVES
-#define VCT_APPLY_D_WAVES 4
-#endif
-#ifndef VCT_APPLY_D_WIN
-#define VCT_APPLY_D_WIN 1400
-#endif
-#ifndef VCT_APPLY_F_COLS
-#define VCT_APPLY_F_COLS true
-#endif
-#ifndef VCT_APPLY_D_COLS
-#define VCT_APPLY_D_COLS true
-#endif
-template <class T> struct ApplyCfg;
-template <> struct ApplyCfg<float> {
-    static constexpr int lanes = VCT_APPLY_F_LANES;
-    static constexpr int slots = VCT_APPLY_F_SLOTS;
-    static constexpr int waves = VCT_APPLY_F_WAVES;
-    static constexpr int win = VCT_APPLY_F_WIN;
-    static constexpr bool col_lds = VCT_APPLY_F_COLS;   // stage the chunk's row entries in LDS
-    static constexpr int threads = kChunk * lanes;   // one chunk per work-group
+// SIMD), LDS window capacity (records) and row entries of a chunk staged in
+// LDS (0: read from memory into the slots) of each arithmetic type and class.
+// The long-row class runs 512-thread groups (8 lanes per particle) at 4 waves
+// per SIMD, two groups per CU; its FP64 form takes a smaller window (about 77
+// KB of LDS per group) and fills the 128 VGPRs that 4 waves allow.
+template <int LANES, int SLOTS, int WAVES, int WIN, int COLS> struct ApplyShape {
+    static constexpr int lanes = LANES, slots = SLOTS, waves = WAVES, win = WIN, cols = COLS;
 };
-template <> struct ApplyCfg<double> {
-    static constexpr int lanes = VCT_APPLY_D_LANES;
-    static constexpr int slots = VCT_APPLY_D_SLOTS;
-    static constexpr int waves = VCT_APPLY_D_WAVES;
-    static constexpr int win = VCT_APPLY_D_WIN;
-    static constexpr bool col_lds = VCT_APPLY_D_COLS;
-    static constexpr int threads = kChunk * lanes;
-};
+template <class T, int C> struct ApplyCfg;
+template <> struct ApplyCfg<float, kLongRows> : ApplyShape<8, 14, 4, 1664, 7168> {};
+template <> struct ApplyCfg<double, kLongRows> : ApplyShape<8, 14, 4, 1400, 7168> {};
+template <> struct ApplyCfg<float, kShort3> : ApplyShape<4, 16, 3, 1400, 0> {};
+template <> struct ApplyCfg<double, kShort3> : ApplyShape<4, 16, 3, 1184, 0> {};
+template <> struct ApplyCfg<float, kShort2> : ApplyShape<4, 7, 6, 448, 2304> {};
+template <> struct ApplyCfg<double, kShort2> : ApplyShape<4, 7, 5, 448, 2304> {};
 
 template <class S> struct ApplyArgs {
     int64_t n;
@@ -172,10 +154,10 @@ __device__ __forceinline__ void pair_sums(const T (&r)[D], T vq, T vc, T psi, co
 }
 
 // G~ = L~ a~ after the group reduction of a~ (dimensionless).
-template <int D, class T>
+template <int D, class T, int LANES>
 __device__ __forceinline__ void group_gradient(const T (&L2)[Dims<D>::nL], T (&a1)[D], T (&Gt)[D]) {
 #pragma unroll
-    for (int a = 0; a < D; ++a) a1[a] = group_sum(a1[a], ApplyCfg<T>::lanes);
+    for (int a = 0; a < D; ++a) a1[a] = group_sum(a1[a], LANES);
 #pragma unroll
     for (int a = 0; a < D; ++a) {
         T t = T(0);
@@ -221,10 +203,10 @@ enum { kGNone = 0, kGIn = 1, kGOut = 2 };
 
 // A chunk whose window exceeds the LDS capacity: the same two passes with
 // every record read from the memory hierarchy.
-template <int D, int KERNEL, class T, class S, bool GOUT>
+template <int D, int KERNEL, class T, class S, int C, bool GOUT>
 __device__ __forceinline__ void apply_chunk_global(const ApplyArgs<S>& A, const WindowT<D>& w, int64_t p0,
                                                 int64_t p1) {
-    constexpr int nk = Dims<D>::nk, kLanes = ApplyCfg<T>::lanes;
+    constexpr int nk = Dims<D>::nk, kLanes = ApplyCfg<T, C>::lanes;
     const int64_t n = A.n;
     const int lane = threadIdx.x % kLanes;
     const int64_t i = p0 + threadIdx.x / kLanes;
@@ -258,7 +240,7 @@ __device__ __forceinline__ void apply_chunk_global(const ApplyArgs<S>& A, const 
 #pragma unroll
             for (int a = 0; a < D; ++a) a1[a] += wgt * r[a];
         }
-        group_gradient<D, T>(L2, a1, Gt);
+        group_gradient<D, T, kLanes>(L2, a1, Gt);
         if (GOUT && lane == 0) {
 #pragma unroll
             for (int a = 0; a < D; ++a) A.g_out[((int64_t)f * D + a) * n + i] = (float)Gt[a];
@@ -289,17 +271,18 @@ __device__ __forceinline__ void apply_chunk_global(const ApplyArgs<S>& A, const 
 }
 
 // GM (kGNone, kGIn, kGOut): what the launch does with G~.
-template <int D, int KERNEL, class T, class S, int GM>
-__global__ __launch_bounds__(ApplyCfg<T>::threads, ApplyCfg<T>::waves) void k_apply(ApplyArgs<S> A) {
+template <int D, int KERNEL, class T, class S, int C, int GM>
+__global__ __launch_bounds__((kChunk * ApplyCfg<T, C>::lanes), (ApplyCfg<T, C>::waves)) void k_apply(ApplyArgs<S> A) {
     constexpr bool GIN = GM == kGIn, GOUT = GM == kGOut;
     static_assert(!GIN || !Scaled<T>::value, "only the FP64 form takes a given gradient");
     using Dm = Dims<D>;
-    constexpr int nk = Dm::nk, kS = ApplyCfg<T>::slots, kW = ApplyCfg<T>::win;
-    constexpr int kLanes = ApplyCfg<T>::lanes, kThreads = ApplyCfg<T>::threads;
-    constexpr int kColBlocks = (kColCap / 8 + kThreads - 1) / kThreads;   // 16-byte blocks per thread
+    using Cfg = ApplyCfg<T, C>;
+    constexpr int nk = Dm::nk, kS = Cfg::slots, kW = Cfg::win, kColCap = Cfg::cols;
+    constexpr int kLanes = Cfg::lanes, kThreads = kChunk * kLanes;   // one chunk per work-group
+    constexpr int kColBlocks = kColCap ? (kColCap / 8 + kThreads - 1) / kThreads : 1;   // 16-byte blocks per thread
     __shared__ double4 sd[kW];
     __shared__ T sv[kW];
-    __shared__ uint4 scol4[ApplyCfg<T>::col_lds ? kColCap / 8 : 1];
+    __shared__ uint4 scol4[kColCap ? kColCap / 8 : 1];
     __shared__ T sacc[kChunk][nk + D];
     __shared__ WindowT<D> w;
     const uint32_t b = xcd_tile(blockIdx.x, gridDim.x);
@@ -326,11 +309,11 @@ __global__ __launch_bounds__(ApplyCfg<T>::threads, ApplyCfg<T>::waves) void k_ap
     // the chunk's row entries [cb, ce), staged from the 16-byte aligned cb8
     const int64_t cb = A.row_ptr[p0], ce = A.row_ptr[p1], nnz = A.row_ptr[n];
     const int64_t cb8 = cb & ~int64_t(7);
-    const bool col_lds = ApplyCfg<T>::col_lds && ce - cb8 <= kColCap;
+    const bool col_lds = kColCap && ce - cb8 <= kColCap;
     __syncthreads();
     const int W = __builtin_amdgcn_readfirstlane(w.off[w.nr]);
     if (W > kW) {
-        apply_chunk_global<D, KERNEL, T, S, GOUT>(A, w, p0, p1);
+        apply_chunk_global<D, KERNEL, T, S, C, GOUT>(A, w, p0, p1);
         return;
     }
     // stage the window records and the chunk's row entries, in batches of
@@ -591,32 +574,40 @@ __global__ __launch_bounds__(ApplyCfg<T>::threads, ApplyCfg<T>::waves) void k_ap
     }
 }
 
-template <int D, int KERNEL, class T, class S>
+template <int D, int KERNEL, class T, class S, int C>
 static int launch_apply(const ApplyArgs<S>& a, int64_t cap, hipStream_t s) {
-    const dim3 grid((unsigned)cap), block(ApplyCfg<T>::threads);
+    const dim3 grid((unsigned)cap), block(kChunk * ApplyCfg<T, C>::lanes);
     const char* name = sizeof(T) == 4 ? "k_apply (mixed)" : "k_apply (fp64)";
     if constexpr (!Scaled<T>::value) {
         if (a.g_in) {
-            VCT_LAUNCH("k_apply (fp64, given G)", (k_apply<D, KERNEL, T, S, kGIn>), grid, block, 0, s, a);
+            VCT_LAUNCH("k_apply (fp64, given G)", (k_apply<D, KERNEL, T, S, C, kGIn>), grid, block, 0, s, a);
             VCT_LAUNCH_CHECK();
             return VCT_OK;
         }
     }
     if (a.g_out)
-        VCT_LAUNCH(name, (k_apply<D, KERNEL, T, S, kGOut>), grid, block, 0, s, a);
+        VCT_LAUNCH(name, (k_apply<D, KERNEL, T, S, C, kGOut>), grid, block, 0, s, a);
     else
-        VCT_LAUNCH(name, (k_apply<D, KERNEL, T, S, kGNone>), grid, block, 0, s, a);
+        VCT_LAUNCH(name, (k_apply<D, KERNEL, T, S, C, kGNone>), grid, block, 0, s, a);
     VCT_LAUNCH_CHECK();
     return VCT_OK;
 }
 
+template <int D, int KERNEL, class T, class S>
+static int launch_class(const ApplyArgs<S>& a, int64_t mean, int64_t cap, hipStream_t s) {
+    constexpr int kShort = D == 2 ? kShort2 : kShort3;
+    if (mean <= short_row<D>()) return launch_apply<D, KERNEL, T, S, kShort>(a, cap, s);
+    return launch_apply<D, KERNEL, T, S, kLongRows>(a, cap, s);
+}
+
 template <class T, class S>
-static int dispatch(int dim, int kernel, const ApplyArgs<S>& a, int64_t cap, hipStream_t s) {
-    if (dim == 2)
-        return kernel == VCT_KERNEL_WENDLAND_C2 ? launch_apply<2, VCT_KERNEL_WENDLAND_C2, T, S>(a, cap, s)
-                                                : launch_apply<2, VCT_KERNEL_CUBIC_SPLINE, T, S>(a, cap, s);
-    return kernel == VCT_KERNEL_WENDLAND_C2 ? launch_apply<3, VCT_KERNEL_WENDLAND_C2, T, S>(a, cap, s)
-                                            : launch_apply<3, VCT_KERNEL_CUBIC_SPLINE, T, S>(a, cap, s);
+static int dispatch(const vct_nlist* nl, int kernel, const ApplyArgs<S>& a, int64_t cap, hipStream_t s) {
+    const int64_t mean = mean_row(nl);
+    if (nl->dim == 2)
+        return kernel == VCT_KERNEL_WENDLAND_C2 ? launch_class<2, VCT_KERNEL_WENDLAND_C2, T, S>(a, mean, cap, s)
+                                                : launch_class<2, VCT_KERNEL_CUBIC_SPLINE, T, S>(a, mean, cap, s);
+    return kernel == VCT_KERNEL_WENDLAND_C2 ? launch_class<3, VCT_KERNEL_WENDLAND_C2, T, S>(a, mean, cap, s)
+                                            : launch_class<3, VCT_KERNEL_CUBIC_SPLINE, T, S>(a, mean, cap, s);
 }
 
 template <class S>
@@ -675,19 +666,19 @@ static int apply_ops(const vct_nlist* nl, int nf, const double* phi_sorted, cons
                            out);
         a.g_out = g_out;
         a.g_in = g_in;
-        return dispatch<double, double>(dim, kernel, a, cap, s);
+        return dispatch<double, double>(nl, kernel, a, cap, s);
     }
     case VCT_MIXED: {
         auto a = make_args(nl, g, nf, phi_sorted, pos_sorted, vol_sorted, static_cast<const float*>(state), out_mask,
                            out);
         a.g_out = g_out;
-        return dispatch<float, float>(dim, kernel, a, cap, s);
+        return dispatch<float, float>(nl, kernel, a, cap, s);
     }
     default: {
         auto a = make_args(nl, g, nf, phi_sorted, pos_sorted, vol_sorted, static_cast<const double*>(state), out_mask,
                            out);
         a.g_out = g_out;
-        return dispatch<float, double>(dim, kernel, a, cap, s);
+        return dispatch<float, double>(nl, kernel, a, cap, s);
     }
     }
 }

@@ -19,6 +19,17 @@ namespace vct {
 constexpr int kChunk = 64;        // particles per chunk
 constexpr int kMaxRanges = 9;     // 3 x 3 columns in 3-D, 3 in 2-D
 
+// Mean row length up to which a set takes the kernels' short-row shapes: 28 and
+// 64 register slots per row (2-D, 3-D), a little above the mean rows of the
+// supports in use that fit them (2-D: 26 at R = 3 d0, 20 at 2.4 d0; 3-D: 57 at
+// 2.4 d0); the next supports up (3-D: 103 at 3 d0) would run most of each row
+// outside the slots.
+template <int D> constexpr int64_t short_row() { return D == 2 ? 30 : 62; }
+// The mean row length the neighbour search left in the list (nnz unset: long).
+inline int64_t mean_row(const vct_nlist* nl) {
+    return nl->nnz > 0 && nl->n > 0 ? nl->nnz / nl->n : INT32_MAX;
+}
+
 // Chunk table: chunk b covers sorted particles [start[b], start[b+1]) of
 // column info[b].x, z cells [info[b].y, info[b].z].
 struct ChunkTable {
