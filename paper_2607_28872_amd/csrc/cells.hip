@@ -569,7 +569,8 @@ __global__ __launch_bounds__(kExT) void k_nb_expand(Grid g, const int64_t* __res
                                                     const int64_t* __restrict__ row_ptr,
                                                     const uint32_t* __restrict__ words,
                                                     const int32_t* __restrict__ win_tab,
-                                                    int32_t* __restrict__ col, uint16_t* __restrict__ col16) {
+                                                    int32_t* __restrict__ col, uint16_t* __restrict__ col16,
+                                                    uint16_t* __restrict__ range_pos) {
     constexpr int kWaves = kExT / kWave;
     constexpr int kPer = kBmWords / kWaves;   // words of one wave's share
     static_assert(kBmWords % kWaves == 0 && kChunk == kWave, "shares of whole words, lane = particle");
@@ -578,7 +579,7 @@ __global__ __launch_bounds__(kExT) void k_nb_expand(Grid g, const int64_t* __res
     __shared__ int32_t part[kWaves][kChunk];      // each wave's share of every row
     __shared__ uint32_t bucket[33];               // words per hit count (32 - count), then offsets
     __shared__ uint32_t list[kExList];            // particle | word << 6 | hits of the row before it << 12
-    __shared__ uint16_t sout[kExOut];
+    __shared__ __align__(16) uint16_t sout[kExOut];
     const uint32_t b = xcd_tile(blockIdx.x, gridDim.x);
     if (b >= *nchunks) return;   // uniform over the work-group
     const int64_t p0 = cstart[b];
@@ -620,10 +621,26 @@ __global__ __launch_bounds__(kExT) void k_nb_expand(Grid g, const int64_t* __res
     __syncthreads();
     int start = 0;   // hits of the row in the earlier waves' shares
     for (int x = 0; x < wv; ++x) start += part[x][pl];
+    if (range_pos) {
+        // where each range of the window begins in the row (read by the
+        // transposed-entry map), by the wave that holds the range's first word
+        for (int r = 1; r < w.nr; ++r) {
+            const int o = __builtin_amdgcn_readfirstlane(w.off[r]);
+            const int u0 = (o >> 5) - k0;
+            if (u0 < 0 || u0 > kPer || (u0 == kPer && wv < kWaves - 1)) continue;   // uniform over the wave
+            int at = start + before[kPer - 1] + __popc(v[kPer - 1]);   // past this share: its end
+#pragma unroll
+            for (int u = 0; u < kPer; ++u)
+                if (u == u0) at = start + before[u] + __popc(v[u] & ((1u << (o & 31)) - 1u));
+            sout[(kMaxRanges - 1) * pl + r - 1] = (uint16_t)at;
+        }
+    }
     uint32_t slot[kPer];
 #pragma unroll
     for (int u = 0; u < kPer; ++u) slot[u] = v[u] ? atomicAdd(&bucket[32 - __popc(v[u])], 1u) : 0u;
     __syncthreads();
+    if (range_pos && (int)threadIdx.x < np)
+        reinterpret_cast<uint4*>(range_pos)[p0 + threadIdx.x] = reinterpret_cast<const uint4*>(sout)[threadIdx.x];
     if (wv == 0) {   // exclusive prefix of the 32 bucket sizes; bucket[32] = the total
         const uint32_t t = pl < 32 ? bucket[pl] : 0u;
         uint32_t incl = t;
@@ -775,67 +792,169 @@ static size_t nb_ws_base(int64_t n, int64_t ncell) {
 
 extern "C" size_t vct_neighbors_workspace_size(int64_t n, int64_t ncell) {
     if (n < 0 || ncell < 1) return 0;
-    return aligned_sum({nb_ws_base(n, ncell), (size_t)(n > 0 ? n : 1) * kStage * sizeof(uint16_t)});
+    return aligned_sum({nb_ws_base(n, ncell), (size_t)(n > 0 ? n : 1) * kStage * sizeof(uint16_t),
+                        (size_t)(n > 0 ? n : 1) * (kMaxRanges - 1) * sizeof(uint16_t)});
 }
 
 namespace vct {
 // Transposed-entry map: for entry e = (i, j) of row i, the position of (j, i)
-// in row j, found by binary search of i in row j's ascending columns.  The
-// neighbour relation is symmetric (d2 is formed from x_j - x_i, whose
-// negation is exact), so every search succeeds; a miss raises the flag.
-// Each lane holds kTSlots entries and advances all their searches together,
-// so the dependent loads of one step are in flight at once.
-constexpr int kTLanes = 8;
-constexpr int kTSlots = 16;
-__global__ __launch_bounds__(256) void k_col_transpose(int64_t n, const int64_t* __restrict__ row_ptr,
-                                                       const int32_t* __restrict__ col, int32_t* __restrict__ col_t,
-                                                       int32_t* __restrict__ miss) {
-    // consecutive particles on one XCD: the rows a search reads are those of
-    // nearby particles, which then stay in that XCD's L2
-    const int64_t blk = xcd_tile(blockIdx.x, gridDim.x);
-    const int64_t i = (blk * blockDim.x + threadIdx.x) / kTLanes;
-    const int lane = threadIdx.x % kTLanes;
-    if (i >= n) return;
-    const int64_t rb = row_ptr[i], re = row_ptr[i + 1];
-    for (int64_t e0 = rb + lane; e0 < re; e0 += (int64_t)kTLanes * kTSlots) {
-        int64_t lo[kTSlots], hi[kTSlots];
-        bool act[kTSlots];
-#pragma unroll
-        for (int s = 0; s < kTSlots; ++s) {
-            const int64_t e = e0 + (int64_t)kTLanes * s;
-            act[s] = e < re;
-            const int64_t j = act[s] ? col[e] : i;
-            lo[s] = row_ptr[j];
-            hi[s] = row_ptr[j + 1] - 1;
-        }
-        bool more = true;
-        while (more) {
-            more = false;
-            int32_t v[kTSlots];
-#pragma unroll
-            for (int s = 0; s < kTSlots; ++s) {
-                const bool go = act[s] && lo[s] < hi[s];
-                v[s] = go ? col[(lo[s] + hi[s]) / 2] : 0;
+// in row j.  The neighbour relation is symmetric (d2 is formed from x_j - x_i,
+// whose negation is exact), and a chunk's particles are consecutive sorted
+// indices, so the entries of row j that lie in one chunk are consecutive too:
+// those of the chunk's particles that have j in their rows, in order.  One
+// work-group per chunk therefore marks, in LDS, which of its particles have
+// each window candidate (one bit per particle), finds where row j reaches the
+// chunk once per candidate, and an entry's transposed position is that plus
+// the number of marked particles before its own.  The expansion of the hit
+// words leaves where each column's part of every row begins (range_pos, 8
+// positions per row); the chunk's entries are then nearly always the first or
+// the last of the part in its column, which one read confirms, and a binary
+// search finds the others (and all of them where the rows came from the fill
+// pass, which leaves no range_pos).
+// Bound by the scattered reads of those confirmations and by the map's stores:
+// with a binary search per candidate, nine reads instead of one or two, 0.80
+// ms, and one search per entry, each lane searching 16 at a time, 2.66 ms, for
+// 1,049,800 particles in 3-D (104M entries); now 0.48 ms.  2-D, 1,048,576
+// particles: 0.43 -> 0.12 ms.  Windows beyond kTWin candidates are taken in
+// parts.
+constexpr int kTThreads = 512;
+constexpr int kTWin = 1536;   // candidates per part (18 KB of LDS)
+template <int D, bool OFFS>
+__global__ __launch_bounds__(kTThreads) void k_col_transpose(Grid g, const int64_t* __restrict__ cs,
+                                                             const int32_t* __restrict__ cstart,
+                                                             const int4* __restrict__ cinfo,
+                                                             const int64_t* __restrict__ nchunks,
+                                                             const int32_t* __restrict__ win_tab,
+                                                             const int64_t* __restrict__ row_ptr,
+                                                             const int32_t* __restrict__ col,
+                                                             const uint16_t* __restrict__ col16,
+                                                             const uint16_t* __restrict__ range_pos,
+                                                             int32_t* __restrict__ col_t, int32_t* __restrict__ miss) {
+    constexpr int kLanes = kTThreads / kChunk;   // lanes per row
+    // row entries per lane held in registers: the rows of R = 3 d0 (2-D: with
+    // 14 slots, mostly empty, 0.142 instead of 0.121 ms at 1,048,576 particles)
+    constexpr int kTSlots = D == 2 ? 4 : 14;
+    static_assert(kChunk == 64, "one mask bit per particle of the chunk");
+    __shared__ uint32_t mask[2][kTWin];   // particles 0..31 and 32..63 of the chunk
+    __shared__ int32_t base[kTWin];
+    __shared__ WindowT<D> w;
+    __shared__ int s_own[kMaxRanges], s_nr[kMaxRanges];   // per range: the chunk's column and the ranges, seen from it
+    const uint32_t b = xcd_tile(blockIdx.x, gridDim.x);
+    if (b >= *nchunks) return;   // uniform over the work-group
+    const int64_t p0 = cstart[b];
+    const int np = (int)(cstart[b + 1] - p0);
+    if (threadIdx.x < kWave) {
+        if (win_tab) window_load<D>(win_tab, b, w);
+        else chunk_window_wave<D>(g, cs, cinfo[b], w);
+    } else if (threadIdx.x < 2 * kWave && range_pos) {
+        // the columns around this one are the window's ranges; in the windows
+        // of such a column this one is range s_own of s_nr
+        const int ln = threadIdx.x - kWave;
+        const int64_t c = cinfo[b].x, ny = D == 3 ? g.nc[1] : 1;
+        const int64_t cx = c / ny, cy = c % ny;
+        auto inside = [&](int64_t x, int64_t y) { return x >= 0 && x < g.nc[0] && y >= 0 && y < ny; };
+        const int64_t x = cx + (D == 3 ? ln / 3 : ln) - 1, y = cy + (D == 3 ? ln % 3 - 1 : 0);
+        const bool in = ln < (D == 3 ? 9 : 3) && inside(x, y);
+        const uint64_t mb = (uint64_t)__ballot(in);
+        if (in) {
+            int own = 0, nr = 0;
+            for (int k = 0; k < (D == 3 ? 9 : 3); ++k) {
+                const int64_t x2 = x + (D == 3 ? k / 3 : k) - 1, y2 = y + (D == 3 ? k % 3 - 1 : 0);
+                if (!inside(x2, y2)) continue;
+                if (x2 == cx && y2 == cy) own = nr;
+                ++nr;
             }
+            const int r = __popcll(mb & ((1ull << ln) - 1ull));
+            s_own[r] = own;
+            s_nr[r] = nr;
+        }
+    }
+    const int pl = threadIdx.x / kLanes, lane = threadIdx.x % kLanes;
+    const int64_t rb = pl < np ? row_ptr[p0 + pl] : 0, re = pl < np ? row_ptr[p0 + pl + 1] : 0;
+    __syncthreads();
+    const int W = w.off[w.nr];
+    // window offset of entry e: stored, or from its sorted index j, whose
+    // range is the last one that starts at or before j (the ranges ascend; an
+    // empty range never holds j)
+    auto offset_of = [&](int64_t e) {
+        if constexpr (OFFS) return (int)col16[e];
+        const int32_t j = col[e];
+        int r = 0;
 #pragma unroll
-            for (int s = 0; s < kTSlots; ++s) {
-                if (act[s] && lo[s] < hi[s]) {
-                    const int64_t mid = (lo[s] + hi[s]) / 2;
-                    if (v[s] < i) lo[s] = mid + 1;
-                    else hi[s] = mid;
-                    more = more || lo[s] < hi[s];
+        for (int k = 1; k < kMaxRanges; ++k)
+            if (k < w.nr && (int64_t)j >= w.gstart[k] && w.off[k + 1] > w.off[k]) r = k;
+        return w.off[r] + (int)((int64_t)j - w.gstart[r]);
+    };
+    // the first kTSlots entries of a lane stay in registers for both uses
+    // (loaded together; longer rows re-read the rest)
+    int tt[kTSlots];
+#pragma unroll
+    for (int s = 0; s < kTSlots; ++s) {
+        const int64_t e = rb + lane + (int64_t)kLanes * s;
+        tt[s] = e < re ? offset_of(e) : -1;
+    }
+    const int64_t tail = rb + lane + (int64_t)kLanes * kTSlots;
+    for (int s0 = 0; s0 < W; s0 += kTWin) {
+        const int sW = W - s0 < kTWin ? W - s0 : kTWin;
+        for (int t = threadIdx.x; t < sW; t += kTThreads) mask[0][t] = mask[1][t] = 0u;
+        __syncthreads();
+        auto mark = [&](int t) {
+            if ((unsigned)t < (unsigned)sW) atomicOr(&mask[pl >> 5][t], 1u << (pl & 31));
+        };
+#pragma unroll
+        for (int s = 0; s < kTSlots; ++s) mark(tt[s] - s0);
+        for (int64_t e = tail; e < re; e += kLanes) mark(offset_of(e) - s0);
+        __syncthreads();
+        for (int t = threadIdx.x; t < sW; t += kTThreads) {
+            const unsigned long long m = mask[0][t] | (unsigned long long)mask[1][t] << 32;
+            if (!m) continue;
+            int r = 0;
+#pragma unroll
+            for (int q = 1; q < kMaxRanges; ++q)
+                if (q < w.nr && s0 + t >= w.off[q]) r = q;
+            const int64_t j = w.gstart[r] + (s0 + t - w.off[r]);
+            int64_t lo = row_ptr[j], hi = row_ptr[j + 1];
+            if (range_pos) {   // the part of row j in the chunk's column
+                const int own = s_own[r];
+                const uint16_t* rp = range_pos + j * (kMaxRanges - 1);
+                const int64_t jb = lo;
+                if (own + 1 < s_nr[r]) hi = jb + rp[own];
+                if (own > 0) lo = jb + rp[own - 1];
+            }
+            const int cnt = __popcll(m);
+            const int32_t first = (int32_t)p0 + __builtin_ctzll(m);
+            // nearly always the part begins or ends in this chunk
+            int64_t at = lo;
+            if (at >= hi || col[at] != first) {
+                at = hi - cnt;
+                if (at < lo || col[at] != first) {
+                    int64_t e = hi;
+                    at = lo;
+                    while (at < e) {
+                        const int64_t mid = (at + e) / 2;
+                        if (col[mid] < first) at = mid + 1;
+                        else e = mid;
+                    }
+                    if (at >= hi || col[at] != first) at = hi;   // not there
                 }
             }
+            const bool ok = at + cnt <= hi;
+            if (!ok) atomicOr(miss, 1);
+            base[t] = ok ? (int32_t)at : -1;
         }
-#pragma unroll
-        for (int s = 0; s < kTSlots; ++s) {
-            const int64_t e = e0 + (int64_t)kTLanes * s;
-            if (act[s]) {
-                const bool ok = lo[s] <= hi[s] && col[lo[s]] == (int32_t)i;
-                col_t[e] = ok ? (int32_t)lo[s] : -1;
-                if (!ok) atomicOr(miss, 1);
+        __syncthreads();
+        auto store = [&](int64_t e, int t) {
+            if ((unsigned)t < (unsigned)sW) {
+                const int32_t bt = base[t];
+                const uint32_t below = (1u << (pl & 31)) - 1u;
+                const int rank = pl < 32 ? __popc(mask[0][t] & below) : __popc(mask[0][t]) + __popc(mask[1][t] & below);
+                col_t[e] = bt < 0 ? -1 : bt + rank;
             }
-        }
+        };
+#pragma unroll
+        for (int s = 0; s < kTSlots; ++s) store(rb + lane + (int64_t)kLanes * s, tt[s] - s0);
+        for (int64_t e = tail; e < re; e += kLanes) store(e, offset_of(e) - s0);
+        __syncthreads();   // the part's masks are consumed
     }
 }
 
@@ -880,12 +999,14 @@ static int launch_nb(const vct_nlist* nl, const double* pos, const Grid& g, int3
 }
 
 template <int D>
-static int launch_expand(const vct_nlist* nl, const Grid& g, const uint16_t* staged, hipStream_t s) {
+static int launch_expand(const vct_nlist* nl, const Grid& g, const uint16_t* staged, uint16_t* range_pos,
+                         hipStream_t s) {
     const int64_t ncols = D == 3 ? g.nc[0] * g.nc[1] : g.nc[0];
     const int64_t cap = ncols + nl->n / kChunk + 1;
     VCT_LAUNCH("k_nb_expand", (k_nb_expand<D>), dim3((unsigned)cap), dim3(kExT), 0, s, g, nl->cell_start,
                nl->chunk_start, reinterpret_cast<const int4*>(nl->chunk_info), nl->chunk_off + ncols,
-               nl->row_ptr, reinterpret_cast<const uint32_t*>(staged), nl->chunk_win, nl->col, nl->col16);
+               nl->row_ptr, reinterpret_cast<const uint32_t*>(staged), nl->chunk_win, nl->col, nl->col16,
+               nl->col_t ? range_pos : nullptr);
     VCT_LAUNCH_CHECK();
     return VCT_OK;
 }
@@ -906,6 +1027,7 @@ extern "C" int vct_neighbors(vct_nlist* nl, const double* pos_sorted, int64_t co
     int64_t* tiles = cv.take<int64_t>(scan_ws_bytes(m) / 8);
     int32_t* flag = cv.take<int32_t>(16);
     uint16_t* staged = cv.take<uint16_t>((size_t)(n > 0 ? n : 1) * kStage);
+    uint16_t* range_pos = cv.take<uint16_t>((size_t)(n > 0 ? n : 1) * (kMaxRanges - 1));
     const int D = nl->dim;
     const bool want_cols = nl->col || nl->col16;
     // flag[0]: window wider than 16-bit offsets; flag[1]: transpose miss;
@@ -938,17 +1060,32 @@ extern "C" int vct_neighbors(vct_nlist* nl, const double* pos_sorted, int64_t co
     if (col_cap < nnz) return VCT_E_CAPACITY;
     if (nl->col_t && (!nl->col || nnz > INT32_MAX)) return VCT_E_ARG;
     if (hflag[0]) return VCT_E_WINDOW;
+    const bool rows_staged = staged_ok && !hflag[2];
     if (n > 0) {
-        if (staged_ok && !hflag[2])
-            st = (D == 2) ? launch_expand<2>(nl, g, staged, s) : launch_expand<3>(nl, g, staged, s);
+        if (rows_staged)
+            st = (D == 2) ? launch_expand<2>(nl, g, staged, range_pos, s)
+                          : launch_expand<3>(nl, g, staged, range_pos, s);
         else   // a window too wide for the staged hit words, or row_ptr given: the fill pass
             st = (D == 2) ? launch_nb<2, 1>(nl, pos_sorted, g, nullptr, flag, nullptr, s)
                           : launch_nb<3, 1>(nl, pos_sorted, g, nullptr, flag, nullptr, s);
         if (st) return st;
     }
     if (nl->col_t && n > 0) {
-        VCT_LAUNCH("k_col_transpose", k_col_transpose, dim3((unsigned)((n * kTLanes + 255) / 256)), dim3(256), 0, s, n,
-                   nl->row_ptr, nl->col, nl->col_t, flag + 1);
+        const int64_t ncols = D == 3 ? g.nc[0] * g.nc[1] : g.nc[0];
+        const dim3 grid((unsigned)(ncols + n / kChunk + 1));
+        const int4* cinfo = reinterpret_cast<const int4*>(nl->chunk_info);
+#define VCT_TRANSPOSE(D, O)                                                                                      \
+    VCT_LAUNCH("k_col_transpose", (k_col_transpose<D, O>), grid, dim3(kTThreads), 0, s, g, nl->cell_start,       \
+               nl->chunk_start, cinfo, nl->chunk_off + ncols, nl->chunk_win, nl->row_ptr, nl->col, nl->col16,     \
+               rows_staged ? range_pos : nullptr, nl->col_t, flag + 1)
+        if (D == 2) {
+            if (nl->col16) VCT_TRANSPOSE(2, true);
+            else VCT_TRANSPOSE(2, false);
+        } else {
+            if (nl->col16) VCT_TRANSPOSE(3, true);
+            else VCT_TRANSPOSE(3, false);
+        }
+#undef VCT_TRANSPOSE
         VCT_LAUNCH_CHECK();
     }
     VCT_HIP_CHECK(hipMemcpyAsync(hflag, flag, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, s));
