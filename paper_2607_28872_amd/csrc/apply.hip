@@ -40,15 +40,16 @@ int nlist_check(const vct_nlist* nl, Grid& g);
 // entries, Wendland C2 with R = 3 d0 in 3-D: 103) costs a 2-D set with 26
 // neighbours four times the pair terms it needs and reserves five times its
 // LDS window, which leaves two work-groups on a CU where six fit.
-//   kShort2: 2-D rows up to about 28 entries, 4 lanes x 7 slots in 256-thread
-//     groups (8 lanes x 4 slots: 30-40% slower), windows up to 448 records
-//     (297 at R = 3 d0).  1,048,576 particles, R = 3 d0: FP64 0.385 -> 0.127
-//     ms, mixed 0.235 -> 0.086 ms (floor at the copy rate: 0.07 and 0.05 ms).
+//   kShort2: 2-D rows up to about 30 entries, 4 lanes x 7 or 8 slots in
+//     256-thread groups (8 lanes x 4 slots: 20-40% slower), windows up to 448
+//     records (297 at R = 3 d0).  1,048,576 particles, R = 3 d0: FP64 0.385 ->
+//     0.127 ms, mixed 0.235 -> 0.096 ms (floor at the copy rate: 0.07 and 0.05
+//     ms).
 //   kShort3: 3-D rows up to 64 entries (cubic spline, R = 2.4 d0: 57), 4 lanes
 //     x 16 slots, row entries read straight into the registers and a window
 //     that lets three groups share a CU (53,760 bytes each: LDS comes in
 //     pieces of 1,280 bytes).  2,097,152 particles: FP64 1.29 -> 0.91 ms,
-//     mixed 0.82 -> 0.63 ms; with 8 lanes x 8 slots and two groups 0.97 and
+//     mixed 0.82 -> 0.64 ms; with 8 lanes x 8 slots and two groups 0.97 and
 //     0.70 ms.
 // A row longer than its class's slots finishes in a loop over the rest, a
 // window larger than the class's reads its records from memory: a set whose
@@ -69,8 +70,15 @@ template <> struct ApplyCfg<float, kLongRows> : ApplyShape<8, 14, 4, 1664, 7168>
 template <> struct ApplyCfg<double, kLongRows> : ApplyShape<8, 14, 4, 1400, 7168> {};
 template <> struct ApplyCfg<float, kShort3> : ApplyShape<4, 16, 3, 1400, 0> {};
 template <> struct ApplyCfg<double, kShort3> : ApplyShape<4, 16, 3, 1184, 0> {};
-template <> struct ApplyCfg<float, kShort2> : ApplyShape<4, 7, 6, 448, 2304> {};
+template <> struct ApplyCfg<float, kShort2> : ApplyShape<4, 8, 5, 448, 2304> {};
 template <> struct ApplyCfg<double, kShort2> : ApplyShape<4, 7, 5, 448, 2304> {};
+
+// The FP32 sums of the mixed form keep one order in every class, that of eight
+// lanes per row: with fewer lanes a lane holds as many partial sums as it
+// stands for (entry k of a row belongs to sum k mod 8), combined at the end as
+// the eight lanes combine theirs.  A set's class then leaves the bits of the
+// mixed form alone (in FP64 the order moves the last digits only).
+template <class T, int LANES> constexpr int kParts = sizeof(T) == 4 ? 8 / LANES : 1;
 
 template <class S> struct ApplyArgs {
     int64_t n;
@@ -136,9 +144,9 @@ __device__ __forceinline__ void pair_geom(const double4& q, T vj, const double (
 // Sums of one pair with residual psi: a~ += V c~ psi r~ and
 // s~ += V c~ psi (r~' L~ r~) / |r~|^4 r~ r~' (L2 holds L~ with doubled
 // off-diagonal entries), with vq = V c~ / |r~|^4 given.
-template <int D, class T>
+template <int D, class T, int H>
 __device__ __forceinline__ void pair_sums(const T (&r)[D], T vq, T vc, T psi, const T (&L2)[Dims<D>::nL],
-                                          T (&acc)[Dims<D>::nk]) {
+                                          T (&acc)[Dims<D>::nk][H], int h) {
     using Dm = Dims<D>;
     T qv[Dm::m];
 #pragma unroll
@@ -148,23 +156,33 @@ __device__ __forceinline__ void pair_sums(const T (&r)[D], T vq, T vc, T psi, co
     for (int p = 0; p < Dm::nL; ++p) rLr += L2[p] * qv[p];
     const T wa = vc * psi, ws = vq * psi * rLr;
 #pragma unroll
-    for (int a = 0; a < D; ++a) acc[a] += wa * r[a];
+    for (int a = 0; a < D; ++a) acc[a][h] += wa * r[a];
 #pragma unroll
-    for (int p = 0; p < Dm::m; ++p) acc[D + p] += ws * qv[p];
+    for (int p = 0; p < Dm::m; ++p) acc[D + p][h] += ws * qv[p];
+}
+
+// Total of a lane group's partial sums, H per lane.
+template <int LANES, int H, class T>
+__device__ __forceinline__ T group_total(const T (&v)[H]) {
+    static_assert(H == 1 || H == 2, "eight lanes' sums on eight or four lanes");
+    const T t = group_sum(v[0], LANES);
+    if constexpr (H == 1) return t;
+    else return t + group_sum(v[1], LANES);
 }
 
 // G~ = L~ a~ after the group reduction of a~ (dimensionless).
-template <int D, class T, int LANES>
-__device__ __forceinline__ void group_gradient(const T (&L2)[Dims<D>::nL], T (&a1)[D], T (&Gt)[D]) {
+template <int D, class T, int LANES, int H, class U>
+__device__ __forceinline__ void group_gradient(const T (&L2)[Dims<D>::nL], const U (&a1)[D][H], T (&Gt)[D]) {
+    T at[D];
 #pragma unroll
-    for (int a = 0; a < D; ++a) a1[a] = group_sum(a1[a], LANES);
+    for (int a = 0; a < D; ++a) at[a] = T(group_total<LANES>(a1[a]));
 #pragma unroll
     for (int a = 0; a < D; ++a) {
         T t = T(0);
 #pragma unroll
         for (int c = 0; c < D; ++c) {
             const int p = sym_index<D>(a, c);
-            t += (a == c ? L2[p] : T(0.5) * L2[p]) * a1[c];
+            t += (a == c ? L2[p] : T(0.5) * L2[p]) * at[c];
         }
         Gt[a] = t;
     }
@@ -206,7 +224,7 @@ enum { kGNone = 0, kGIn = 1, kGOut = 2 };
 template <int D, int KERNEL, class T, class S, int C, bool GOUT>
 __device__ __forceinline__ void apply_chunk_global(const ApplyArgs<S>& A, const WindowT<D>& w, int64_t p0,
                                                 int64_t p1) {
-    constexpr int nk = Dims<D>::nk, kLanes = ApplyCfg<T, C>::lanes;
+    constexpr int nk = Dims<D>::nk, kLanes = ApplyCfg<T, C>::lanes, kH = kParts<T, kLanes>;
     const int64_t n = A.n;
     const int lane = threadIdx.x % kLanes;
     const int64_t i = p0 + threadIdx.x / kLanes;
@@ -227,19 +245,28 @@ __device__ __forceinline__ void apply_chunk_global(const ApplyArgs<S>& A, const 
             q = make_double4(A.pos[j] * ps, A.pos[n + j] * ps, D == 3 ? A.pos[2 * n + j] * ps : 0.0, ph[j]);
             v = T(A.vol[j]);
         };
-        T a1[D], Gt[D];
+        T a1[D][kH], Gt[D];
 #pragma unroll
-        for (int a = 0; a < D; ++a) a1[a] = T(0);
-        for (int64_t e = rb + lane; e < re; e += kLanes) {
+        for (int a = 0; a < D; ++a)
+#pragma unroll
+            for (int h = 0; h < kH; ++h) a1[a][h] = T(0);
+        auto first = [&](int64_t e, int h) {
             double4 q;
-            T vj, r[D], q2, vc;
+            T vj, r[D], q2, vc, iq4;
             double dx[D];
             fetch(A.col16[e], q, vj);
-            pair_geom<D, KERNEL, T>(q, vj, xi, invR, dx, r, q2, vc);
+            // (the short classes weigh as with the window in LDS: where a
+            // chunk's records are read from does not show in its results)
+            if constexpr (C == kLongRows) pair_geom<D, KERNEL, T>(q, vj, xi, invR, dx, r, q2, vc);
+            else pair_geom<D, KERNEL, T, Scaled<T>::value>(q, vj, xi, invR, dx, r, q2, vc, &iq4);
             const T wgt = vc * T(q.w - phi_i);
 #pragma unroll
-            for (int a = 0; a < D; ++a) a1[a] += wgt * r[a];
-        }
+            for (int a = 0; a < D; ++a) a1[a][h] += wgt * r[a];
+        };
+        for (int64_t e = rb + lane; e < re; e += kH * kLanes)
+#pragma unroll
+            for (int h = 0; h < kH; ++h)
+                if (e + h * kLanes < re) first(e + h * kLanes, h);
         group_gradient<D, T, kLanes>(L2, a1, Gt);
         if (GOUT && lane == 0) {
 #pragma unroll
@@ -248,10 +275,12 @@ __device__ __forceinline__ void apply_chunk_global(const ApplyArgs<S>& A, const 
         double Gp[D];
 #pragma unroll
         for (int a = 0; a < D; ++a) Gp[a] = Scaled<T>::value ? (double)Gt[a] : (double)Gt[a] * A.invR;
-        T acc[nk];
+        T part[nk][kH], acc[nk];
 #pragma unroll
-        for (int c = 0; c < nk; ++c) acc[c] = T(0);
-        for (int64_t e = rb + lane; e < re; e += kLanes) {
+        for (int c = 0; c < nk; ++c)
+#pragma unroll
+            for (int h = 0; h < kH; ++h) part[c][h] = T(0);
+        auto second = [&](int64_t e, int h) {
             double4 q;
             T vj, r[D], q2, vc;
             double dx[D];
@@ -261,10 +290,14 @@ __device__ __forceinline__ void apply_chunk_global(const ApplyArgs<S>& A, const 
             double psi = q.w - phi_i;
 #pragma unroll
             for (int a = 0; a < D; ++a) psi -= dx[a] * Gp[a];
-            pair_sums<D, T>(r, vc * iq4, vc, T(psi), L2, acc);
-        }
+            pair_sums<D, T, kH>(r, vc * iq4, vc, T(psi), L2, part, h);
+        };
+        for (int64_t e = rb + lane; e < re; e += kH * kLanes)
 #pragma unroll
-        for (int c = 0; c < nk; ++c) acc[c] = group_sum(acc[c], kLanes);
+            for (int h = 0; h < kH; ++h)
+                if (e + h * kLanes < re) second(e + h * kLanes, h);
+#pragma unroll
+        for (int c = 0; c < nk; ++c) acc[c] = group_total<kLanes>(part[c]);
         for (int o = lane; o < A.nrows; o += kLanes)
             A.out[((int64_t)f * n + i) * A.nrows + o] = out_row<D, T, S>(A, i, o, acc, Gt);
     }
@@ -279,6 +312,8 @@ __global__ __launch_bounds__((kChunk * ApplyCfg<T, C>::lanes), (ApplyCfg<T, C>::
     using Cfg = ApplyCfg<T, C>;
     constexpr int nk = Dm::nk, kS = Cfg::slots, kW = Cfg::win, kColCap = Cfg::cols;
     constexpr int kLanes = Cfg::lanes, kThreads = kChunk * kLanes;   // one chunk per work-group
+    constexpr int kH = kParts<T, kLanes>;   // partial sums per lane
+    static_assert(kS % kH == 0, "the entries past the slots start at part 0");
     constexpr int kColBlocks = kColCap ? (kColCap / 8 + kThreads - 1) / kThreads : 1;   // 16-byte blocks per thread
     __shared__ double4 sd[kW];
     __shared__ T sv[kW];
@@ -411,16 +446,18 @@ __global__ __launch_bounds__((kChunk * ApplyCfg<T, C>::lanes), (ApplyCfg<T, C>::
         // holds for any G, so an FP32 G leaves the FP64 form's sums FP64 and
         // its result as accurate (psi keeps a linear part of relative size
         // 1e-7, which the operator reproduces exactly).
-        float a1[D];
+        float a1[D][kH];
         T Gt[D];
 #pragma unroll
-        for (int a = 0; a < D; ++a) a1[a] = 0.0f;
+        for (int a = 0; a < D; ++a)
+#pragma unroll
+            for (int h = 0; h < kH; ++h) a1[a][h] = 0.0f;
         const float invRf = (float)A.invR;
         // The mixed form keeps each register slot's V_j c~ and V_j c~ / q^4
         // from pass 1, so pass 2 forms neither (the FP64 form needs its own
         // FP64 values).
         float vcs[kS], vqs[kS];
-        auto term1 = [&](const double4& q, T vj, bool use, float& vq) -> float {
+        auto term1 = [&](const double4& q, T vj, bool use, int h, float& vq) -> float {
             if constexpr (Scaled<T>::value) {
                 double dx[D];
                 T r[D], q2, vc, iq4;
@@ -428,7 +465,7 @@ __global__ __launch_bounds__((kChunk * ApplyCfg<T, C>::lanes), (ApplyCfg<T, C>::
                 vq = vc * iq4;
                 const T wgt = vc * T(q.w - phi_i);
 #pragma unroll
-                for (int a = 0; a < D; ++a) a1[a] += wgt * r[a];
+                for (int a = 0; a < D; ++a) a1[a][h] += wgt * r[a];
                 return vc;
             } else {
                 float r[D], q2 = 0.0f;
@@ -441,7 +478,7 @@ __global__ __launch_bounds__((kChunk * ApplyCfg<T, C>::lanes), (ApplyCfg<T, C>::
                 const float vc = (float)vj * kernel_shape<KERNEL>(vsqrt(q2));
                 const float wgt = vc * (float)(q.w - phi_i);
 #pragma unroll
-                for (int a = 0; a < D; ++a) a1[a] += wgt * r[a];
+                for (int a = 0; a < D; ++a) a1[a][h] += wgt * r[a];
                 vq = 0.0f;
                 return 0.0f;
             }
@@ -467,26 +504,21 @@ __global__ __launch_bounds__((kChunk * ApplyCfg<T, C>::lanes), (ApplyCfg<T, C>::
                     vn = sv[cols(s + 1)];
                 }
                 __builtin_amdgcn_sched_barrier(0);
-                vcs[s] = term1(q, vj, s < nslot, vqs[s]);
+                vcs[s] = term1(q, vj, s < nslot, s % kH, vqs[s]);
                 __builtin_amdgcn_sched_barrier(0);
             }
-            for (int64_t e = tail + lane; e < re; e += kLanes) {
-                const int t = col_at(e);
-                float vq_;
-                term1(sd[t], sv[t], true, vq_);
-            }
+            for (int64_t e0 = tail + lane; e0 < re; e0 += kH * kLanes) {
 #pragma unroll
-            for (int a = 0; a < D; ++a) a1[a] = group_sum(a1[a], kLanes);
-#pragma unroll
-            for (int a = 0; a < D; ++a) {
-                T t = T(0);
-#pragma unroll
-                for (int c = 0; c < D; ++c) {
-                    const int p = sym_index<D>(a, c);
-                    t += (a == c ? L2[p] : T(0.5) * L2[p]) * T(a1[c]);
+                for (int h = 0; h < kH; ++h) {
+                    const int64_t e = e0 + h * kLanes;
+                    if (e < re) {
+                        const int t = col_at(e);
+                        float vq_;
+                        term1(sd[t], sv[t], true, h, vq_);
+                    }
                 }
-                Gt[a] = t;
             }
+            group_gradient<D, T, kLanes>(L2, a1, Gt);
         }
         double Gp[D];
 #pragma unroll
@@ -501,10 +533,12 @@ __global__ __launch_bounds__((kChunk * ApplyCfg<T, C>::lanes), (ApplyCfg<T, C>::
         // addresses are recomputed here instead of being kept live from pass 1.
 #pragma unroll
         for (int k = 0; k < (kS + 1) / 2; ++k) asm volatile("" : "+v"(cpk[k]));
-        T acc[nk];
+        T part[nk][kH];
 #pragma unroll
-        for (int c = 0; c < nk; ++c) acc[c] = T(0);
-        auto term2 = [&](const double4& q, T vj, bool use, int s) {
+        for (int c = 0; c < nk; ++c)
+#pragma unroll
+            for (int h = 0; h < kH; ++h) part[c][h] = T(0);
+        auto term2 = [&](const double4& q, T vj, bool use, int s, int h) {
             double dx[D];
             T r[D], q2, vc;
             T iq4;
@@ -518,7 +552,7 @@ __global__ __launch_bounds__((kChunk * ApplyCfg<T, C>::lanes), (ApplyCfg<T, C>::
                 double psi = q.w - phi_i;
 #pragma unroll
                 for (int a = 0; a < D; ++a) psi -= dx[a] * Gp[a];
-                pair_sums<D, T>(r, T(vqs[s]), vc, T(psi), L2, acc);
+                pair_sums<D, T, kH>(r, T(vqs[s]), vc, T(psi), L2, part, h);
                 return;
             } else {
                 pair_geom<D, KERNEL, T, true>(q, vj, xi, invR, dx, r, q2, vc, &iq4, use);
@@ -526,7 +560,7 @@ __global__ __launch_bounds__((kChunk * ApplyCfg<T, C>::lanes), (ApplyCfg<T, C>::
             double psi = q.w - phi_i;
 #pragma unroll
             for (int a = 0; a < D; ++a) psi -= dx[a] * Gp[a];
-            pair_sums<D, T>(r, vc * iq4, vc, T(psi), L2, acc);
+            pair_sums<D, T, kH>(r, vc * iq4, vc, T(psi), L2, part, h);
         };
         double4 qn = sd[cols(0)];
         T vn = sv[cols(0)];
@@ -539,16 +573,23 @@ __global__ __launch_bounds__((kChunk * ApplyCfg<T, C>::lanes), (ApplyCfg<T, C>::
                 vn = sv[cols(s + 1)];
             }
             __builtin_amdgcn_sched_barrier(0);
-            term2(q, vj, s < nslot, s);
+            term2(q, vj, s < nslot, s, s % kH);
             __builtin_amdgcn_sched_barrier(0);
         }
-        for (int64_t e = tail + lane; e < re; e += kLanes) {
-            const int t = col_at(e);
-            term2(sd[t], sv[t], true, -1);
+        for (int64_t e0 = tail + lane; e0 < re; e0 += kH * kLanes) {
+#pragma unroll
+            for (int h = 0; h < kH; ++h) {
+                const int64_t e = e0 + h * kLanes;
+                if (e < re) {
+                    const int t = col_at(e);
+                    term2(sd[t], sv[t], true, -1, h);
+                }
+            }
         }
         // epilogue: the group's sums to LDS, then one thread per (row, particle)
+        T acc[nk];
 #pragma unroll
-        for (int c = 0; c < nk; ++c) acc[c] = group_sum(acc[c], kLanes);
+        for (int c = 0; c < nk; ++c) acc[c] = group_total<kLanes>(part[c]);
         if (lane == 0) {
 #pragma unroll
             for (int c = 0; c < nk; ++c) sacc[pl][c] = acc[c];

@@ -68,6 +68,7 @@ def test_row_classes(name):
     scale = np.abs(ref).max(axis=1, keepdims=True)
     kap = OX.moment_condition(w.pos, w.vol, w.kernel, w.R, rows=np.arange(w.n))
     ng = w.dim
+    mixed = []
     for nnz in (g.nnz, 0):
         g.nl.nnz = nnz
         got = {p: g.unsort(g.apply(phi, p)[:, : g.n]).cpu().numpy()
@@ -80,4 +81,7 @@ def test_row_classes(name):
             for rows, bar in ((slice(0, ng), 1e-5), (slice(ng, None), 1e-4)):
                 e = per_particle(got[p][..., rows], ref[..., rows], scale[..., rows])
                 assert np.all(e <= np.maximum(bar, 20 * 2.0 ** -24 * kap)), (name, nnz, p, e.max())
+        mixed.append((got[vct.VCT_MIXED], got[vct.VCT_MIXED_S64]))
     g.nl.nnz = g.nnz
+    # the mixed form sums in the same order in both classes
+    assert np.array_equal(mixed[0][0], mixed[1][0]) and np.array_equal(mixed[0][1], mixed[1][1])
