@@ -13,21 +13,9 @@ namespace vct {
 
 // ------------------------------------------------------------------ small kernels
 
-__global__ void k_fill_i32(int32_t* p, int64_t n, int32_t v) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = v;
-}
-
 __global__ void k_fill_i64(int64_t* p, int64_t n, int64_t v) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = v;
-}
-
-static int fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t s) {
-    if (n <= 0) return VCT_OK;
-    VCT_LAUNCH("k_fill_i32", k_fill_i32, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p, n, v);
-    VCT_LAUNCH_CHECK();
-    return VCT_OK;
 }
 
 static int fill_i64(int64_t* p, int64_t n, int64_t v, hipStream_t s) {
@@ -37,14 +25,37 @@ static int fill_i64(int64_t* p, int64_t n, int64_t v, hipStream_t s) {
     return VCT_OK;
 }
 
+// p[0..n) = 0 and q[0..m) = 0, m <= 256
+__global__ void k_fill_i32(int32_t* p, int64_t n, int32_t* q, int m) {
+    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) p[i] = 0;
+    if (i < m) q[i] = 0;
+}
+
+static int zero_i32(int32_t* p, int64_t n, int32_t* q, int m, hipStream_t s) {
+    VCT_LAUNCH("k_fill_i32", k_fill_i32, dim3((unsigned)((n > m ? n : m) + 255) / 256), dim3(256), 0, s, p, n, q, m);
+    VCT_LAUNCH_CHECK();
+    return VCT_OK;
+}
+
 // ------------------------------------------------------------------ exclusive scan
 
-// out[i] = sum_{k<i} in[k] for i in [0, n], int32 -> int64, in three passes:
-// per-tile sums, a single-block scan of the tile sums, per-tile scans.
+// out[i] = sum_{k<i} in[k] for i in [0, n], int32 -> int64.  Up to kScanOne
+// values one work-group does it in one launch.  Beyond, per-tile sums and
+// per-tile scans, each tile adding up the sums of the tiles before it by
+// itself (up to kScanSelf tiles: at most 32 values per thread, from the L2; 8.4M
+// values are 4,096 tiles); beyond that a single-block scan of the tile sums
+// stands between the two.  A launch costs about as much as scanning 100,000
+// values, and a small geometry is five scans: with three launches each they
+// took 97 of the 280 us of its kernels (4,096 particles in 2-D).
 constexpr int kScanThreads = 256;
 constexpr int kScanItems = 8;
 constexpr int kScanTile = kScanThreads * kScanItems;
+constexpr int kScanOneThreads = 1024;
+constexpr int kScanOne = kScanOneThreads * 16;
+constexpr int kScanSelf = 8192;
 
+template <int THREADS>
 __device__ int64_t block_exclusive_scan(int64_t v, int64_t* lds_waves, int64_t* total) {
     const int lane = threadIdx.x % kWave, wv = threadIdx.x / kWave;
     int64_t inc = v;
@@ -55,7 +66,7 @@ __device__ int64_t block_exclusive_scan(int64_t v, int64_t* lds_waves, int64_t* 
     if (lane == kWave - 1) lds_waves[wv] = inc;
     __syncthreads();
     int64_t wbase = 0, tot = 0;
-    for (int k = 0; k < kScanThreads / kWave; ++k) {
+    for (int k = 0; k < THREADS / kWave; ++k) {
         if (k < wv) wbase += lds_waves[k];
         tot += lds_waves[k];
     }
@@ -64,46 +75,87 @@ __device__ int64_t block_exclusive_scan(int64_t v, int64_t* lds_waves, int64_t* 
     return wbase + inc - v;
 }
 
-__global__ void k_scan_tiles(const int32_t* in, int64_t n, int64_t* tile_sums) {
-    __shared__ int64_t lw[kScanThreads / kWave];
-    int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
+// ITEMS consecutive values of a thread, as 16-byte loads where whole (in is
+// 16-byte aligned, base a multiple of ITEMS)
+template <int ITEMS>
+__device__ __forceinline__ int64_t scan_load(const int32_t* __restrict__ in, int64_t n, int64_t base, int (&v)[ITEMS]) {
     int64_t s = 0;
-    for (int k = 0; k < kScanItems; ++k)
-        if (base + k < n) s += in[base + k];
+#pragma unroll
+    for (int k = 0; k < ITEMS; k += 4) {
+        if (base + k + 4 <= n) {
+            const int4 q = *reinterpret_cast<const int4*>(in + base + k);
+            v[k] = q.x; v[k + 1] = q.y; v[k + 2] = q.z; v[k + 3] = q.w;
+        } else {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[k + u] = base + k + u < n ? in[base + k + u] : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) s += v[k + u];
+    }
+    return s;
+}
+
+__global__ __launch_bounds__(kScanOneThreads) void k_scan_one(const int32_t* in, int64_t n, int64_t* out) {
+    constexpr int kItems = kScanOne / kScanOneThreads;
+    __shared__ int64_t lw[kScanOneThreads / kWave];
+    const int64_t base = (int64_t)threadIdx.x * kItems;
+    int v[kItems];
+    const int64_t s = scan_load(in, n, base, v);
     int64_t tot;
-    block_exclusive_scan(s, lw, &tot);
+    int64_t run = block_exclusive_scan<kScanOneThreads>(s, lw, &tot);
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) {
+        if (base + k < n) out[base + k] = run;
+        run += v[k];
+    }
+    if (threadIdx.x == 0) out[n] = tot;
+}
+
+__global__ __launch_bounds__(kScanThreads) void k_scan_tiles(const int32_t* in, int64_t n, int64_t* tile_sums) {
+    __shared__ int64_t lw[kScanThreads / kWave];
+    int v[kScanItems];
+    const int64_t s = scan_load(in, n, (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems, v);
+    int64_t tot;
+    block_exclusive_scan<kScanThreads>(s, lw, &tot);
     if (threadIdx.x == 0) tile_sums[blockIdx.x] = tot;
 }
 
-__global__ void k_scan_sums(int64_t* sums, int64_t ntiles, int64_t* out_total) {
+__global__ void k_scan_sums(int64_t* sums, int64_t ntiles) {
     __shared__ int64_t lw[kScanThreads / kWave];
     int64_t carry = 0;
     for (int64_t b = 0; b < ntiles; b += kScanThreads) {
         int64_t i = b + threadIdx.x;
         int64_t v = i < ntiles ? sums[i] : 0;
         int64_t tot;
-        int64_t ex = block_exclusive_scan(v, lw, &tot);
+        int64_t ex = block_exclusive_scan<kScanThreads>(v, lw, &tot);
         if (i < ntiles) sums[i] = carry + ex;
         carry += tot;
     }
-    if (threadIdx.x == 0) *out_total = carry;
 }
 
-__global__ void k_scan_apply(const int32_t* in, int64_t n, const int64_t* tile_off, int64_t* out) {
+// scanned: tile_sums already holds each tile's offset
+__global__ __launch_bounds__(kScanThreads) void k_scan_apply(const int32_t* in, int64_t n,
+                                                            const int64_t* __restrict__ tile_sums, bool scanned,
+                                                            int64_t* out) {
     __shared__ int64_t lw[kScanThreads / kWave];
-    int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
-    int64_t v[kScanItems];
-    int64_t s = 0;
-    for (int k = 0; k < kScanItems; ++k) {
-        v[k] = (base + k < n) ? in[base + k] : 0;
-        s += v[k];
+    const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
+    int v[kScanItems];
+    const int64_t s = scan_load(in, n, base, v);
+    int64_t off = 0, tot;
+    if (scanned) {
+        off = tile_sums[blockIdx.x];
+    } else {
+        int64_t before = 0;
+        for (int64_t k = threadIdx.x; k < (int64_t)blockIdx.x; k += kScanThreads) before += tile_sums[k];
+        block_exclusive_scan<kScanThreads>(before, lw, &off);
     }
-    int64_t tot;
-    int64_t run = tile_off[blockIdx.x] + block_exclusive_scan(s, lw, &tot);
+    int64_t run = off + block_exclusive_scan<kScanThreads>(s, lw, &tot);
+#pragma unroll
     for (int k = 0; k < kScanItems; ++k) {
         if (base + k < n) out[base + k] = run;
         run += v[k];
     }
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) out[n] = off + tot;
 }
 
 static size_t scan_ws_bytes(int64_t n) {
@@ -113,13 +165,22 @@ static size_t scan_ws_bytes(int64_t n) {
 
 // out has n + 1 entries; out[n] is the total
 static int exclusive_scan(const int32_t* in, int64_t n, int64_t* out, int64_t* tile_ws, hipStream_t s) {
-    int64_t ntiles = (n + kScanTile - 1) / kScanTile;
-    if (ntiles == 0) return fill_i64(out, 1, 0, s);
+    if (n == 0) return fill_i64(out, 1, 0, s);
+    if (n <= kScanOne) {
+        VCT_LAUNCH("k_scan_one", k_scan_one, dim3(1), dim3(kScanOneThreads), 0, s, in, n, out);
+        VCT_LAUNCH_CHECK();
+        return VCT_OK;
+    }
+    const int64_t ntiles = (n + kScanTile - 1) / kScanTile;
+    const bool scanned = ntiles > kScanSelf;
     VCT_LAUNCH("k_scan_tiles", k_scan_tiles, dim3((unsigned)ntiles), dim3(kScanThreads), 0, s, in, n, tile_ws);
     VCT_LAUNCH_CHECK();
-    VCT_LAUNCH("k_scan_sums", k_scan_sums, dim3(1), dim3(kScanThreads), 0, s, tile_ws, ntiles, out + n);
-    VCT_LAUNCH_CHECK();
-    VCT_LAUNCH("k_scan_apply", k_scan_apply, dim3((unsigned)ntiles), dim3(kScanThreads), 0, s, in, n, tile_ws, out);
+    if (scanned) {
+        VCT_LAUNCH("k_scan_sums", k_scan_sums, dim3(1), dim3(kScanThreads), 0, s, tile_ws, ntiles);
+        VCT_LAUNCH_CHECK();
+    }
+    VCT_LAUNCH("k_scan_apply", k_scan_apply, dim3((unsigned)ntiles), dim3(kScanThreads), 0, s, in, n, tile_ws,
+               scanned, out);
     VCT_LAUNCH_CHECK();
     return VCT_OK;
 }
@@ -259,19 +320,27 @@ __device__ int64_t z_of(const Grid& g, const int64_t* __restrict__ cs, int64_t c
     return lo;
 }
 
+// One column per kFillLanes lanes, each lane every kFillLanes-th chunk of it: a
+// 2-D set has few columns of many chunks (1,048,576 particles: 683 columns of
+// 25 chunks, each chunk two bisections over the column's cells: 86 us with one
+// thread per column, 9 us now; 3-D columns of 5 chunks fill a third of the lanes
+// and take what they took, 10 us).
+constexpr int kFillLanes = 16;
 template <int D>
 __global__ void k_chunk_fill(Grid g, int64_t n, const int64_t* __restrict__ cs, const int64_t* __restrict__ off,
                              int32_t* __restrict__ cstart, int4* __restrict__ cinfo) {
-    const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t c = t / kFillLanes;
+    const int lane = (int)(t % kFillLanes);
     const int64_t ncols = grid_ncols<D>(g);
     if (c >= ncols) {
-        if (c == ncols) cstart[off[ncols]] = (int32_t)n;
+        if (c == ncols && lane == 0) cstart[off[ncols]] = (int32_t)n;
         return;
     }
     const int64_t nz = grid_nz<D>(g);
     const int64_t a = cs[col_key<D>(g, c, 0)], e = cs[col_key<D>(g, c, nz - 1) + 1];
-    int64_t b = off[c];
-    for (int64_t p = a; p < e; p += kChunk, ++b) {
+    int64_t b = off[c] + lane;
+    for (int64_t p = a + (int64_t)lane * kChunk; p < e; p += (int64_t)kFillLanes * kChunk, b += kFillLanes) {
         const int64_t q = (p + kChunk < e ? p + kChunk : e) - 1;
         cstart[b] = (int32_t)p;
         cinfo[b] = make_int4((int)c, (int)z_of<D>(g, cs, c, p), (int)z_of<D>(g, cs, c, q), 0);
@@ -730,8 +799,7 @@ extern "C" int vct_build_cells(int dim, int64_t n, const double* pos, const doub
     int64_t* tiles = cv.take<int64_t>(scan_ws_bytes(ncell) / 8);
     int32_t* bad = cv.take<int32_t>(16);
     int st;
-    if ((st = fill_i32(counts, ncell, 0, s))) return st;
-    if ((st = fill_i32(bad, 1, 0, s))) return st;
+    if ((st = zero_i32(counts, ncell, bad, 1, s))) return st;
     if (n > 0) {
         VCT_LAUNCH("k_cell_keys", k_cell_keys, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, dim, n, pos, g,
                    keys, slots, counts, bad);
@@ -973,13 +1041,13 @@ int nlist_check(const vct_nlist* nl, Grid& g) {
 template <int D>
 static int build_chunks(const vct_nlist* nl, const Grid& g, int32_t* tmp, int64_t* tiles, hipStream_t s) {
     const int64_t ncols = D == 3 ? g.nc[0] * g.nc[1] : g.nc[0];
-    const unsigned nb = (unsigned)((ncols + 1 + 255) / 256);
-    VCT_LAUNCH("k_chunk_count", (k_chunk_count<D>), dim3(nb), dim3(256), 0, s, g, nl->cell_start, tmp);
+    VCT_LAUNCH("k_chunk_count", (k_chunk_count<D>), dim3((unsigned)((ncols + 255) / 256)), dim3(256), 0, s, g,
+               nl->cell_start, tmp);
     VCT_LAUNCH_CHECK();
     int st = exclusive_scan(tmp, ncols, nl->chunk_off, tiles, s);
     if (st) return st;
-    VCT_LAUNCH("k_chunk_fill", (k_chunk_fill<D>), dim3(nb), dim3(256), 0, s, g, nl->n, nl->cell_start, nl->chunk_off,
-               nl->chunk_start, reinterpret_cast<int4*>(nl->chunk_info));
+    VCT_LAUNCH("k_chunk_fill", (k_chunk_fill<D>), dim3((unsigned)(((ncols + 1) * kFillLanes + 255) / 256)), dim3(256),
+               0, s, g, nl->n, nl->cell_start, nl->chunk_off, nl->chunk_start, reinterpret_cast<int4*>(nl->chunk_info));
     VCT_LAUNCH_CHECK();
     return VCT_OK;
 }
@@ -1032,7 +1100,7 @@ extern "C" int vct_neighbors(vct_nlist* nl, const double* pos_sorted, int64_t co
     const bool want_cols = nl->col || nl->col16;
     // flag[0]: window wider than 16-bit offsets; flag[1]: transpose miss;
     // flag[2]: a window whose hit words exceed the staging capacity
-    if ((st = fill_i32(flag, 3, 0, s))) return st;
+    if ((st = zero_i32(flag, 3, flag, 0, s))) return st;
     bool staged_ok = false;
     if (!reuse_row_ptr) {
         st = (D == 2) ? build_chunks<2>(nl, g, counts, tiles, s) : build_chunks<3>(nl, g, counts, tiles, s);
