@@ -293,7 +293,7 @@ typedef struct {
 int64_t vct_chunk_capacity(int dim, int64_t n, int64_t ncell);
 
 /* Workspace of vct_neighbors: counts, scan tiles, flags and a staging area of
- * 128 16-bit entries per particle (256 n bytes). */
+ * 136 16-bit entries per particle (272 n bytes), and a list of chunks. */
 size_t vct_neighbors_workspace_size(int64_t n, int64_t ncell);
 
 /* Neighbour lists S_i = { j != i : d2(i,j) < R*R } (Eq. SPH_neighbor_set) of
@@ -319,6 +319,20 @@ size_t vct_neighbors_workspace_size(int64_t n, int64_t ncell);
  * cannot address it).  SYNC (reads nnz).                                       */
 int vct_neighbors(vct_nlist* nl, const double* pos_sorted, int64_t col_cap, int64_t* nnz_out, int reuse_row_ptr,
                   void* ws, size_t ws_bytes, void* stream);
+
+/* The same search in two calls, for callers that size the columns by the
+ * result: vct_neighbors_search writes the chunk table, row_ptr, *nnz_out and
+ * nl->nnz (nl->col and nl->col16 are not touched) and leaves the hits in the
+ * workspace (*staged says in which form); vct_neighbors_rows, given the same
+ * list with the columns set, the same workspace, unchanged in between, and
+ * that value, writes the columns (and col_t) as vct_neighbors does, without
+ * searching again.  One search instead of the two of a vct_neighbors call
+ * without columns followed by one with them.  Errors as vct_neighbors.  The
+ * first call is SYNC; the second is only with col_t.                          */
+int vct_neighbors_search(vct_nlist* nl, const double* pos_sorted, int64_t* nnz_out, int* staged, void* ws,
+                         size_t ws_bytes, void* stream);
+int vct_neighbors_rows(const vct_nlist* nl, const double* pos_sorted, int64_t col_cap, int staged, void* ws,
+                       size_t ws_bytes, void* stream);
 
 /* ---------------------------------------------------------------- moments */
 

@@ -95,7 +95,8 @@ __device__ __forceinline__ int64_t scan_load(const int32_t* __restrict__ in, int
     return s;
 }
 
-__global__ __launch_bounds__(kScanOneThreads) void k_scan_one(const int32_t* in, int64_t n, int64_t* out) {
+__global__ __launch_bounds__(kScanOneThreads) void k_scan_one(const int32_t* in, int64_t n, int64_t* out,
+                                                             int64_t* total) {
     constexpr int kItems = kScanOne / kScanOneThreads;
     __shared__ int64_t lw[kScanOneThreads / kWave];
     const int64_t base = (int64_t)threadIdx.x * kItems;
@@ -108,7 +109,10 @@ __global__ __launch_bounds__(kScanOneThreads) void k_scan_one(const int32_t* in,
         if (base + k < n) out[base + k] = run;
         run += v[k];
     }
-    if (threadIdx.x == 0) out[n] = tot;
+    if (threadIdx.x == 0) {
+        out[n] = tot;
+        if (total) *total = tot;
+    }
 }
 
 __global__ __launch_bounds__(kScanThreads) void k_scan_tiles(const int32_t* in, int64_t n, int64_t* tile_sums) {
@@ -136,7 +140,7 @@ __global__ void k_scan_sums(int64_t* sums, int64_t ntiles) {
 // scanned: tile_sums already holds each tile's offset
 __global__ __launch_bounds__(kScanThreads) void k_scan_apply(const int32_t* in, int64_t n,
                                                             const int64_t* __restrict__ tile_sums, bool scanned,
-                                                            int64_t* out) {
+                                                            int64_t* out, int64_t* total) {
     __shared__ int64_t lw[kScanThreads / kWave];
     const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
     int v[kScanItems];
@@ -155,7 +159,10 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_apply(const int32_t* in, 
         if (base + k < n) out[base + k] = run;
         run += v[k];
     }
-    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) out[n] = off + tot;
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+        out[n] = off + tot;
+        if (total) *total = off + tot;
+    }
 }
 
 static size_t scan_ws_bytes(int64_t n) {
@@ -163,11 +170,12 @@ static size_t scan_ws_bytes(int64_t n) {
     return (size_t)(ntiles > 0 ? ntiles : 1) * sizeof(int64_t);
 }
 
-// out has n + 1 entries; out[n] is the total
-static int exclusive_scan(const int32_t* in, int64_t n, int64_t* out, int64_t* tile_ws, hipStream_t s) {
+// out has n + 1 entries; out[n] is the total (n > 0: also written to *total when given)
+static int exclusive_scan(const int32_t* in, int64_t n, int64_t* out, int64_t* tile_ws, hipStream_t s,
+                          int64_t* total = nullptr) {
     if (n == 0) return fill_i64(out, 1, 0, s);
     if (n <= kScanOne) {
-        VCT_LAUNCH("k_scan_one", k_scan_one, dim3(1), dim3(kScanOneThreads), 0, s, in, n, out);
+        VCT_LAUNCH("k_scan_one", k_scan_one, dim3(1), dim3(kScanOneThreads), 0, s, in, n, out, total);
         VCT_LAUNCH_CHECK();
         return VCT_OK;
     }
@@ -180,7 +188,7 @@ static int exclusive_scan(const int32_t* in, int64_t n, int64_t* out, int64_t* t
         VCT_LAUNCH_CHECK();
     }
     VCT_LAUNCH("k_scan_apply", k_scan_apply, dim3((unsigned)ntiles), dim3(kScanThreads), 0, s, in, n, tile_ws,
-               scanned, out);
+               scanned, out, total);
     VCT_LAUNCH_CHECK();
     return VCT_OK;
 }
@@ -298,10 +306,20 @@ __global__ void k_scatter(int64_t n, int ncomp, const int32_t* __restrict__ perm
 
 // ------------------------------------------------------------------ chunk table
 
+// What a search hands to the host: the entries found, whether some window is
+// beyond 16-bit offsets, whether an entry had no transpose, and how many
+// windows are wider than the staged hit words describe.
+struct SearchHead {
+    int64_t nnz;
+    int32_t overflow, miss, wide, pad;
+};
+
 // Chunks of one column: ceil(count / kChunk) pieces of consecutive particles.
 template <int D>
-__global__ void k_chunk_count(Grid g, const int64_t* __restrict__ cs, int32_t* __restrict__ nch) {
+__global__ void k_chunk_count(Grid g, const int64_t* __restrict__ cs, int32_t* __restrict__ nch,
+                              SearchHead* __restrict__ head) {
     const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (c == 0) *head = SearchHead{0, 0, 0, 0, 0};   // for the search that follows
     if (c >= grid_ncols<D>(g)) return;
     const int64_t nz = grid_nz<D>(g);
     const int64_t cnt = cs[col_key<D>(g, c, nz - 1) + 1] - cs[col_key<D>(g, c, 0)];
@@ -392,19 +410,15 @@ constexpr int kBmWords = kStage / 2;           // hit words per particle slot: w
 // counts and the chunk's hit words, [word][particle] with the chunk's np
 // particles per word, at word p0 * kBmWords of `col16` (the staging buffer),
 // for k_nb_expand to turn into rows; a window wider than kBmWords * 32
-// candidates does not fit there and is flagged (overflow[2]).  overflow[0]
-// flags windows beyond 65535.
+// candidates does not fit there: its chunk goes to the list `wide`, whose
+// counts k_nb_wide adds.  head->overflow flags windows beyond 65535.
 template <int D, int MODE>
-__global__ __launch_bounds__(kNbThreads) void k_nb_chunk(int64_t n, const double* __restrict__ pos, Grid g,
-                                                         double R2, const int64_t* __restrict__ cs,
-                                                         const int32_t* __restrict__ cstart,
-                                                         const int4* __restrict__ cinfo,
-                                                         const int64_t* __restrict__ nchunks,
-                                                         int32_t* __restrict__ counts,
-                                                         const int64_t* __restrict__ row_ptr,
-                                                         int32_t* __restrict__ col, uint16_t* __restrict__ col16,
-                                                         int32_t* __restrict__ overflow,
-                                                         int32_t* __restrict__ win_tab) {
+__device__ __forceinline__ void nb_chunk(uint32_t b, int64_t n, const double* __restrict__ pos, const Grid& g, double R2,
+                                         const int64_t* __restrict__ cs, const int32_t* __restrict__ cstart,
+                                         const int4* __restrict__ cinfo, int32_t* __restrict__ counts,
+                                         const int64_t* __restrict__ row_ptr, int32_t* __restrict__ col,
+                                         uint16_t* __restrict__ col16, SearchHead* __restrict__ head,
+                                         int32_t* __restrict__ wide, int32_t* __restrict__ win_tab) {
     constexpr bool FILL = MODE == 1, STAGE = MODE == 2;
     static_assert(kChunk == kWave, "lane = particle");
     static_assert(kNbSeg % 32 == 0, "segments hold whole words");
@@ -413,8 +427,6 @@ __global__ __launch_bounds__(kNbThreads) void k_nb_chunk(int64_t n, const double
     __shared__ int32_t wcnt[kNbWaves][kChunk];
     __shared__ float wmax[kNbWaves];
     __shared__ WindowT<D> w;
-    const uint32_t b = xcd_tile(blockIdx.x, gridDim.x);
-    if (b >= *nchunks) return;   // uniform over the work-group
     const int64_t p0 = cstart[b], p1 = cstart[b + 1];
     const int np = (int)(p1 - p0);
     const int wv = threadIdx.x / kWave, pl = threadIdx.x % kWave;
@@ -435,7 +447,7 @@ __global__ __launch_bounds__(kNbThreads) void k_nb_chunk(int64_t n, const double
     const int64_t rlo = FILL ? row_ptr[ii] : 0, rlen = FILL ? row_ptr[ii + 1] - rlo : 0;
     __syncthreads();
     const int W = w.off[w.nr];
-    if ((FILL || STAGE) && threadIdx.x == 0 && W > 65535) atomicOr(overflow, 1);
+    if ((FILL || STAGE) && threadIdx.x == 0 && W > 65535) atomicOr(&head->overflow, 1);
     if (win_tab && wv == 0) window_store<D>(w, win_tab, b);   // for the later calls
     // the particle's own window offset (it is never its own neighbour)
     int self_t = -1;
@@ -445,9 +457,11 @@ __global__ __launch_bounds__(kNbThreads) void k_nb_chunk(int64_t n, const double
     }
     // the chunk's hit words (MODE 2), np per word; only when they fit its
     // share of the staging buffer (np * kBmWords words)
-    const bool bm_fit = W <= kBmWords * 32;
-    if (STAGE && threadIdx.x == 0 && !bm_fit) atomicOr(overflow + 2, 1);
-    uint32_t* bmg = STAGE && bm_fit ? reinterpret_cast<uint32_t*>(col16) + p0 * kBmWords : nullptr;
+    if (STAGE && W > kBmWords * 32) {   // uniform
+        if (threadIdx.x == 0) wide[atomicAdd(&head->wide, 1)] = (int32_t)b;
+        return;
+    }
+    uint32_t* bmg = STAGE ? reinterpret_cast<uint32_t*>(col16) + p0 * kBmWords : nullptr;
     int rowpos = 0;                     // entries of the row found so far (MODE 1)
     int mycnt = 0;                      // hits of this wave's candidates (MODES 0, 2)
     for (int s0 = 0; s0 < W; s0 += kNbSeg) {
@@ -564,7 +578,7 @@ __global__ __launch_bounds__(kNbThreads) void k_nb_chunk(int64_t n, const double
                 bm[k][pl] = bits;
                 cnt += __popc(bits);
             } else {
-                if (STAGE && bmg && valid)
+                if (STAGE && valid)
                     bmg[dcheck((s0 / 32 + k) * np + pl, np * kBmWords, kChkCapacity)] = bits;
                 mycnt += __popc(bits);
             }
@@ -608,6 +622,41 @@ __global__ __launch_bounds__(kNbThreads) void k_nb_chunk(int64_t n, const double
             for (int v = 0; v < kNbWaves; ++v) c += wcnt[v][pl];
             counts[i] = c;
         }
+    }
+}
+
+// One chunk per work-group.
+template <int D, int MODE>
+__global__ __launch_bounds__(kNbThreads) void k_nb_chunk(int64_t n, const double* __restrict__ pos, Grid g,
+                                                         double R2, const int64_t* __restrict__ cs,
+                                                         const int32_t* __restrict__ cstart,
+                                                         const int4* __restrict__ cinfo,
+                                                         const int64_t* __restrict__ nchunks,
+                                                         int32_t* __restrict__ counts,
+                                                         const int64_t* __restrict__ row_ptr,
+                                                         int32_t* __restrict__ col, uint16_t* __restrict__ col16,
+                                                         SearchHead* __restrict__ head, int32_t* __restrict__ wide,
+                                                         int32_t* __restrict__ win_tab) {
+    const uint32_t b = xcd_tile(blockIdx.x, gridDim.x);
+    if (b >= *nchunks) return;   // uniform over the work-group
+    nb_chunk<D, MODE>(b, n, pos, g, R2, cs, cstart, cinfo, counts, row_ptr, col, col16, head, wide, win_tab);
+}
+
+// The counts of the listed wide chunks, taken in turn by a fixed grid (none at
+// the supports in use: the launch then ends at once).
+constexpr int kWideBlocks = 512;
+template <int D>
+__global__ __launch_bounds__(kNbThreads) void k_nb_wide(int64_t n, const double* __restrict__ pos, Grid g, double R2,
+                                                        const int64_t* __restrict__ cs,
+                                                        const int32_t* __restrict__ cstart,
+                                                        const int4* __restrict__ cinfo, int32_t* __restrict__ counts,
+                                                        SearchHead* __restrict__ head,
+                                                        const int32_t* __restrict__ wide) {
+    const int cnt = head->wide;
+    for (int k = blockIdx.x; k < cnt; k += gridDim.x) {
+        nb_chunk<D, 0>((uint32_t)wide[k], n, pos, g, R2, cs, cstart, cinfo, counts, nullptr, nullptr, nullptr, head,
+                       nullptr, nullptr);
+        __syncthreads();   // the chunk's LDS is consumed
     }
 }
 
@@ -855,7 +904,7 @@ extern "C" int64_t vct_chunk_capacity(int dim, int64_t n, int64_t ncell) {
 // Workspace without the staging buffer (enough for the two-pass search).
 static size_t nb_ws_base(int64_t n, int64_t ncell) {
     const int64_t m = n > ncell ? n : ncell;
-    return aligned_sum({(size_t)m * 4, scan_ws_bytes(m), 64});
+    return aligned_sum({(size_t)m * 4, scan_ws_bytes(m), sizeof(SearchHead), (size_t)(n / kChunk + ncell + 1) * 4});
 }
 
 extern "C" size_t vct_neighbors_workspace_size(int64_t n, int64_t ncell) {
@@ -1038,11 +1087,32 @@ int nlist_check(const vct_nlist* nl, Grid& g) {
 }
 }  // namespace vct
 
+// The workspace of a search and its rows.
+struct NbWork {
+    int32_t* counts;
+    int64_t* tiles;
+    SearchHead* head;
+    int32_t* wide;         // chunks whose windows are wider than the hit words
+    uint16_t* staged;      // hit words
+    uint16_t* range_pos;   // per row: where each column's part begins
+    NbWork(const vct_nlist* nl, void* p, size_t bytes) {
+        const int64_t n = nl->n, m = n > nl->ncell ? n : nl->ncell;
+        Carver cv(p, bytes);
+        counts = cv.take<int32_t>((size_t)m);
+        tiles = cv.take<int64_t>(scan_ws_bytes(m) / 8);
+        head = cv.take<SearchHead>(1);
+        wide = cv.take<int32_t>((size_t)(n / kChunk + nl->ncell + 1));
+        staged = cv.take<uint16_t>((size_t)(n > 0 ? n : 1) * kStage);
+        range_pos = cv.take<uint16_t>((size_t)(n > 0 ? n : 1) * (kMaxRanges - 1));
+    }
+};
+
 template <int D>
-static int build_chunks(const vct_nlist* nl, const Grid& g, int32_t* tmp, int64_t* tiles, hipStream_t s) {
+static int build_chunks(const vct_nlist* nl, const Grid& g, int32_t* tmp, int64_t* tiles, SearchHead* head,
+                        hipStream_t s) {
     const int64_t ncols = D == 3 ? g.nc[0] * g.nc[1] : g.nc[0];
     VCT_LAUNCH("k_chunk_count", (k_chunk_count<D>), dim3((unsigned)((ncols + 255) / 256)), dim3(256), 0, s, g,
-               nl->cell_start, tmp);
+               nl->cell_start, tmp, head);
     VCT_LAUNCH_CHECK();
     int st = exclusive_scan(tmp, ncols, nl->chunk_off, tiles, s);
     if (st) return st;
@@ -1053,111 +1123,164 @@ static int build_chunks(const vct_nlist* nl, const Grid& g, int32_t* tmp, int64_
 }
 
 template <int D, int MODE>
-static int launch_nb(const vct_nlist* nl, const double* pos, const Grid& g, int32_t* counts, int32_t* overflow,
-                     uint16_t* staged, hipStream_t s) {
+static int launch_nb(const vct_nlist* nl, const double* pos, const Grid& g, const NbWork& ws, hipStream_t s) {
     const int64_t ncols = D == 3 ? g.nc[0] * g.nc[1] : g.nc[0];
     const int64_t cap = ncols + nl->n / kChunk + 1;   // upper bound of the chunk count
     const char* name = MODE == 0 ? "k_nb_chunk (count)" : MODE == 1 ? "k_nb_chunk (fill)" : "k_nb_chunk (stage)";
+    const int4* cinfo = reinterpret_cast<const int4*>(nl->chunk_info);
     VCT_LAUNCH(name, (k_nb_chunk<D, MODE>), dim3((unsigned)cap), dim3(kNbThreads), 0, s, nl->n, pos, g,
-               nl->R * nl->R, nl->cell_start, nl->chunk_start,
-               reinterpret_cast<const int4*>(nl->chunk_info), nl->chunk_off + ncols, counts, nl->row_ptr,
-               MODE == 1 ? nl->col : nullptr, MODE == 1 ? nl->col16 : staged, overflow, nl->chunk_win);
+               nl->R * nl->R, nl->cell_start, nl->chunk_start, cinfo, nl->chunk_off + ncols,
+               MODE == 1 ? nullptr : ws.counts, nl->row_ptr, MODE == 1 ? nl->col : nullptr,
+               MODE == 1 ? nl->col16 : ws.staged, ws.head, ws.wide, nl->chunk_win);
     VCT_LAUNCH_CHECK();
+    if (MODE == 2) {
+        VCT_LAUNCH("k_nb_chunk (count)", (k_nb_wide<D>), dim3((unsigned)(cap < kWideBlocks ? cap : kWideBlocks)),
+                   dim3(kNbThreads), 0, s, nl->n, pos, g, nl->R * nl->R, nl->cell_start, nl->chunk_start, cinfo,
+                   ws.counts, ws.head, ws.wide);
+        VCT_LAUNCH_CHECK();
+    }
     return VCT_OK;
 }
 
 template <int D>
-static int launch_expand(const vct_nlist* nl, const Grid& g, const uint16_t* staged, uint16_t* range_pos,
-                         hipStream_t s) {
+static int launch_expand(const vct_nlist* nl, const Grid& g, const NbWork& ws, hipStream_t s) {
     const int64_t ncols = D == 3 ? g.nc[0] * g.nc[1] : g.nc[0];
     const int64_t cap = ncols + nl->n / kChunk + 1;
     VCT_LAUNCH("k_nb_expand", (k_nb_expand<D>), dim3((unsigned)cap), dim3(kExT), 0, s, g, nl->cell_start,
                nl->chunk_start, reinterpret_cast<const int4*>(nl->chunk_info), nl->chunk_off + ncols,
-               nl->row_ptr, reinterpret_cast<const uint32_t*>(staged), nl->chunk_win, nl->col, nl->col16,
-               nl->col_t ? range_pos : nullptr);
+               nl->row_ptr, reinterpret_cast<const uint32_t*>(ws.staged), nl->chunk_win, nl->col, nl->col16,
+               nl->col_t ? ws.range_pos : nullptr);
     VCT_LAUNCH_CHECK();
     return VCT_OK;
 }
 
+static int nb_check(const vct_nlist* nl, const double* pos, const void* ws, size_t ws_bytes, Grid& g) {
+    const int st = nlist_check(nl, g);
+    if (st) return st;
+    if (nl->n > 0 && !pos) return VCT_E_ARG;
+    return !ws || ws_bytes < vct_neighbors_workspace_size(nl->n, nl->ncell) ? VCT_E_WORKSPACE : VCT_OK;
+}
+
+// Chunk table, counts and row pointers; with `stage` also the hit words.
+template <int D>
+static int nb_search(const vct_nlist* nl, const double* pos, const Grid& g, const NbWork& ws, bool stage,
+                     hipStream_t s) {
+    int st = build_chunks<D>(nl, g, ws.counts, ws.tiles, ws.head, s);
+    if (st) return st;
+    if (nl->n > 0) {
+        st = stage ? launch_nb<D, 2>(nl, pos, g, ws, s) : launch_nb<D, 0>(nl, pos, g, ws, s);
+        if (st) return st;
+    }
+    return exclusive_scan(ws.counts, nl->n, nl->row_ptr, ws.tiles, s, &ws.head->nnz);
+}
+
+// The columns behind row_ptr (from the hit words, or by the fill pass) and the
+// transposed-entry map.
+template <int D>
+static int nb_rows(const vct_nlist* nl, const double* pos, const Grid& g, const NbWork& ws, bool words, hipStream_t s) {
+    const int64_t n = nl->n;
+    if (n == 0) return VCT_OK;
+    const int st = words ? launch_expand<D>(nl, g, ws, s) : launch_nb<D, 1>(nl, pos, g, ws, s);
+    if (st || !nl->col_t) return st;
+    const int64_t ncols = D == 3 ? g.nc[0] * g.nc[1] : g.nc[0];
+    const dim3 grid((unsigned)(ncols + n / kChunk + 1));
+    const int4* cinfo = reinterpret_cast<const int4*>(nl->chunk_info);
+    const uint16_t* range_pos = words ? ws.range_pos : nullptr;
+    if (nl->col16)
+        VCT_LAUNCH("k_col_transpose", (k_col_transpose<D, true>), grid, dim3(kTThreads), 0, s, g, nl->cell_start,
+                   nl->chunk_start, cinfo, nl->chunk_off + ncols, nl->chunk_win, nl->row_ptr, nl->col, nl->col16,
+                   range_pos, nl->col_t, &ws.head->miss);
+    else
+        VCT_LAUNCH("k_col_transpose", (k_col_transpose<D, false>), grid, dim3(kTThreads), 0, s, g, nl->cell_start,
+                   nl->chunk_start, cinfo, nl->chunk_off + ncols, nl->chunk_win, nl->row_ptr, nl->col, nl->col16,
+                   range_pos, nl->col_t, &ws.head->miss);
+    VCT_LAUNCH_CHECK();
+    return VCT_OK;
+}
+
+static int read_head(const NbWork& ws, SearchHead& h, hipStream_t s) {
+    VCT_HIP_CHECK(hipMemcpyAsync(&h, ws.head, sizeof(h), hipMemcpyDeviceToHost, s));
+    VCT_HIP_CHECK(hipStreamSynchronize(s));
+    return VCT_OK;
+}
+
+__global__ void k_head_given(SearchHead* head, const int64_t* nnz) { *head = SearchHead{*nnz, 0, 0, 0, 0}; }
+
 extern "C" int vct_neighbors(vct_nlist* nl, const double* pos_sorted, int64_t col_cap, int64_t* nnz_out,
-                             int reuse_row_ptr, void* ws, size_t ws_bytes, void* stream) {
+                             int reuse_row_ptr, void* ws_p, size_t ws_bytes, void* stream) {
     VCT_API_RANGE("vct_neighbors");
     Grid g;
-    int st = nlist_check(nl, g);
+    if (!nnz_out) {
+        const int st = nlist_check(nl, g);
+        return st ? st : VCT_E_ARG;
+    }
+    int st = nb_check(nl, pos_sorted, ws_p, ws_bytes, g);
     if (st) return st;
-    if (!nnz_out || (nl->n > 0 && !pos_sorted)) return VCT_E_ARG;
-    const int64_t n = nl->n;
-    if (!ws || ws_bytes < vct_neighbors_workspace_size(n, nl->ncell)) return VCT_E_WORKSPACE;
     hipStream_t s = as_stream(stream);
-    Carver cv(ws, ws_bytes);
-    const int64_t m = n > nl->ncell ? n : nl->ncell;
-    int32_t* counts = cv.take<int32_t>((size_t)m);
-    int64_t* tiles = cv.take<int64_t>(scan_ws_bytes(m) / 8);
-    int32_t* flag = cv.take<int32_t>(16);
-    uint16_t* staged = cv.take<uint16_t>((size_t)(n > 0 ? n : 1) * kStage);
-    uint16_t* range_pos = cv.take<uint16_t>((size_t)(n > 0 ? n : 1) * (kMaxRanges - 1));
-    const int D = nl->dim;
+    const NbWork ws(nl, ws_p, ws_bytes);
     const bool want_cols = nl->col || nl->col16;
-    // flag[0]: window wider than 16-bit offsets; flag[1]: transpose miss;
-    // flag[2]: a window whose hit words exceed the staging capacity
-    if ((st = zero_i32(flag, 3, flag, 0, s))) return st;
-    bool staged_ok = false;
-    if (!reuse_row_ptr) {
-        st = (D == 2) ? build_chunks<2>(nl, g, counts, tiles, s) : build_chunks<3>(nl, g, counts, tiles, s);
-        if (st) return st;
-        if (n > 0) {
-            if (want_cols)
-                st = (D == 2) ? launch_nb<2, 2>(nl, pos_sorted, g, counts, flag, staged, s)
-                              : launch_nb<3, 2>(nl, pos_sorted, g, counts, flag, staged, s);
-            else
-                st = (D == 2) ? launch_nb<2, 0>(nl, pos_sorted, g, counts, flag, nullptr, s)
-                              : launch_nb<3, 0>(nl, pos_sorted, g, counts, flag, nullptr, s);
-            if (st) return st;
-        }
-        if ((st = exclusive_scan(counts, n, nl->row_ptr, tiles, s))) return st;
-        staged_ok = want_cols;
-    }
-    int64_t nnz = 0;
-    int32_t hflag[3] = {0, 0, 0};
-    VCT_HIP_CHECK(hipMemcpyAsync(&nnz, nl->row_ptr + n, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    VCT_HIP_CHECK(hipMemcpyAsync(hflag, flag, 3 * sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    VCT_HIP_CHECK(hipStreamSynchronize(s));
-    *nnz_out = nnz;
-    nl->nnz = nnz;
-    if (!want_cols) return VCT_OK;
-    if (col_cap < nnz) return VCT_E_CAPACITY;
-    if (nl->col_t && (!nl->col || nnz > INT32_MAX)) return VCT_E_ARG;
-    if (hflag[0]) return VCT_E_WINDOW;
-    const bool rows_staged = staged_ok && !hflag[2];
-    if (n > 0) {
-        if (rows_staged)
-            st = (D == 2) ? launch_expand<2>(nl, g, staged, range_pos, s)
-                          : launch_expand<3>(nl, g, staged, range_pos, s);
-        else   // a window too wide for the staged hit words, or row_ptr given: the fill pass
-            st = (D == 2) ? launch_nb<2, 1>(nl, pos_sorted, g, nullptr, flag, nullptr, s)
-                          : launch_nb<3, 1>(nl, pos_sorted, g, nullptr, flag, nullptr, s);
-        if (st) return st;
-    }
-    if (nl->col_t && n > 0) {
-        const int64_t ncols = D == 3 ? g.nc[0] * g.nc[1] : g.nc[0];
-        const dim3 grid((unsigned)(ncols + n / kChunk + 1));
-        const int4* cinfo = reinterpret_cast<const int4*>(nl->chunk_info);
-#define VCT_TRANSPOSE(D, O)                                                                                      \
-    VCT_LAUNCH("k_col_transpose", (k_col_transpose<D, O>), grid, dim3(kTThreads), 0, s, g, nl->cell_start,       \
-               nl->chunk_start, cinfo, nl->chunk_off + ncols, nl->chunk_win, nl->row_ptr, nl->col, nl->col16,     \
-               rows_staged ? range_pos : nullptr, nl->col_t, flag + 1)
-        if (D == 2) {
-            if (nl->col16) VCT_TRANSPOSE(2, true);
-            else VCT_TRANSPOSE(2, false);
-        } else {
-            if (nl->col16) VCT_TRANSPOSE(3, true);
-            else VCT_TRANSPOSE(3, false);
-        }
-#undef VCT_TRANSPOSE
+    if (reuse_row_ptr) {
+        VCT_LAUNCH("k_head_given", k_head_given, dim3(1), dim3(1), 0, s, ws.head, nl->row_ptr + nl->n);
         VCT_LAUNCH_CHECK();
+    } else {
+        st = nl->dim == 2 ? nb_search<2>(nl, pos_sorted, g, ws, want_cols, s)
+                          : nb_search<3>(nl, pos_sorted, g, ws, want_cols, s);
+        if (st) return st;
     }
-    VCT_HIP_CHECK(hipMemcpyAsync(hflag, flag, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    VCT_HIP_CHECK(hipStreamSynchronize(s));
-    if (hflag[0]) return VCT_E_WINDOW;
-    return hflag[1] ? VCT_E_HIP : VCT_OK;
+    SearchHead h;
+    if ((st = read_head(ws, h, s))) return st;
+    *nnz_out = h.nnz;
+    nl->nnz = h.nnz;
+    if (!want_cols) return VCT_OK;
+    if (col_cap < h.nnz) return VCT_E_CAPACITY;
+    if (nl->col_t && (!nl->col || h.nnz > INT32_MAX)) return VCT_E_ARG;
+    if (h.overflow) return VCT_E_WINDOW;
+    const bool words = !reuse_row_ptr && h.wide == 0;
+    st = nl->dim == 2 ? nb_rows<2>(nl, pos_sorted, g, ws, words, s) : nb_rows<3>(nl, pos_sorted, g, ws, words, s);
+    if (st) return st;
+    if ((st = read_head(ws, h, s))) return st;
+    if (h.overflow) return VCT_E_WINDOW;
+    return h.miss ? VCT_E_HIP : VCT_OK;
+}
+
+// what vct_neighbors_search left in the workspace
+enum { kStagedFill = 0, kStagedWords = 1, kStagedOverflow = 2 };
+
+extern "C" int vct_neighbors_search(vct_nlist* nl, const double* pos_sorted, int64_t* nnz_out, int* staged, void* ws_p,
+                                    size_t ws_bytes, void* stream) {
+    VCT_API_RANGE("vct_neighbors_search");
+    Grid g;
+    if (!nnz_out || !staged) return VCT_E_ARG;
+    int st = nb_check(nl, pos_sorted, ws_p, ws_bytes, g);
+    if (st) return st;
+    hipStream_t s = as_stream(stream);
+    const NbWork ws(nl, ws_p, ws_bytes);
+    st = nl->dim == 2 ? nb_search<2>(nl, pos_sorted, g, ws, true, s) : nb_search<3>(nl, pos_sorted, g, ws, true, s);
+    if (st) return st;
+    SearchHead h;
+    if ((st = read_head(ws, h, s))) return st;
+    *nnz_out = h.nnz;
+    nl->nnz = h.nnz;
+    *staged = h.overflow ? kStagedOverflow : h.wide ? kStagedFill : kStagedWords;
+    return VCT_OK;
+}
+
+extern "C" int vct_neighbors_rows(const vct_nlist* nl, const double* pos_sorted, int64_t col_cap, int staged,
+                                  void* ws_p, size_t ws_bytes, void* stream) {
+    VCT_API_RANGE("vct_neighbors_rows");
+    Grid g;
+    int st = nb_check(nl, pos_sorted, ws_p, ws_bytes, g);
+    if (st) return st;
+    if (staged < kStagedFill || staged > kStagedOverflow || (!nl->col && !nl->col16) || nl->nnz < 0) return VCT_E_ARG;
+    if (col_cap < nl->nnz) return VCT_E_CAPACITY;
+    if (nl->col_t && (!nl->col || nl->nnz > INT32_MAX)) return VCT_E_ARG;
+    if (staged == kStagedOverflow) return VCT_E_WINDOW;
+    hipStream_t s = as_stream(stream);
+    const NbWork ws(nl, ws_p, ws_bytes);
+    const bool words = staged == kStagedWords;
+    st = nl->dim == 2 ? nb_rows<2>(nl, pos_sorted, g, ws, words, s) : nb_rows<3>(nl, pos_sorted, g, ws, words, s);
+    if (st || !nl->col_t) return st;
+    SearchHead h;   // the transposed-entry map reports entries without a transpose
+    if ((st = read_head(ws, h, s))) return st;
+    return h.miss ? VCT_E_HIP : VCT_OK;
 }

@@ -105,6 +105,10 @@ def lib():
         L.vct_neighbors_workspace_size.argtypes = [_i64, _i64]
         L.vct_neighbors.restype = C.c_int
         L.vct_neighbors.argtypes = [_nlp, _vp, _i64, C.POINTER(_i64), C.c_int, _vp, _sz, _vp]
+        L.vct_neighbors_search.restype = C.c_int
+        L.vct_neighbors_search.argtypes = [_nlp, _vp, C.POINTER(_i64), C.POINTER(C.c_int), _vp, _sz, _vp]
+        L.vct_neighbors_rows.restype = C.c_int
+        L.vct_neighbors_rows.argtypes = [_nlp, _vp, _i64, C.c_int, _vp, _sz, _vp]
         L.vct_moments_workspace_size.restype = _sz
         L.vct_moments_workspace_size.argtypes = [C.c_int, _i64]
         L.vct_moments.restype = C.c_int
@@ -312,6 +316,19 @@ def vct_neighbors(nl, pos_sorted, col_cap, reuse, ws, stream=None):
     return st, nnz.value
 
 
+def vct_neighbors_search(nl, pos_sorted, ws, stream=None):
+    """(nnz, staged): the search alone; vct_neighbors_rows writes the columns."""
+    nnz, staged = _i64(0), C.c_int(0)
+    _check("vct_neighbors_search", lib().vct_neighbors_search(
+        C.byref(nl), _p(pos_sorted), C.byref(nnz), C.byref(staged), _p(ws), _nbytes(ws), _stream(stream)))
+    return nnz.value, staged.value
+
+
+def vct_neighbors_rows(nl, pos_sorted, col_cap, staged, ws, stream=None):
+    return _check("vct_neighbors_rows", lib().vct_neighbors_rows(
+        C.byref(nl), _p(pos_sorted), int(col_cap), int(staged), _p(ws), _nbytes(ws), _stream(stream)))
+
+
 def vct_moments(nl, pos_sorted, vol_sorted, kernel, cmap, mask, state64, state32, flags, count_flagged, ws,
                 stream=None):
     cnt = _i64(0)
@@ -465,23 +482,21 @@ class Geometry:
         self.chunk_info = torch.empty((cap, 4), dtype=torch.int32, device=device)
         self.chunk_win = torch.empty((cap, 32), dtype=torch.int32, device=device)
         self._nws = _bytes(lib().vct_neighbors_workspace_size(n, self.ncell), device)
-        nl = make_nlist(self.dim, n, self.ncell, lo, hi, R, self.cell_start, self.chunk_off, self.chunk_start,
-                        self.chunk_info, self.row_ptr, chunk_cap=cap, chunk_win=self.chunk_win)
-        _, nnz = vct_neighbors(nl, self.pos, 0, 0, self._nws)
-        self.nnz = nnz
-        self.col = torch.empty(max(nnz, 1), dtype=torch.int32, device=device) if keep_col else None
-        self.col16 = torch.empty(max(nnz, 1), dtype=torch.uint16, device=device)
+        self.nl = nl = make_nlist(self.dim, n, self.ncell, lo, hi, R, self.cell_start, self.chunk_off,
+                                  self.chunk_start, self.chunk_info, self.row_ptr, chunk_cap=cap,
+                                  chunk_win=self.chunk_win)
+        # one search, which leaves the hits in the workspace; the columns are
+        # allocated by its count and written from there
+        self.nnz, staged = vct_neighbors_search(nl, self.pos, self._nws)
+        nnz = max(self.nnz, 1)
+        self.col = torch.empty(nnz, dtype=torch.int32, device=device) if keep_col else None
+        self.col16 = torch.empty(nnz, dtype=torch.uint16, device=device)
         # transposed-entry map, for the adjoint (needs the int32 columns)
-        self.col_t = torch.empty(max(nnz, 1), dtype=torch.int32, device=device) if keep_col else None
-        self.nl = make_nlist(self.dim, n, self.ncell, lo, hi, R, self.cell_start, self.chunk_off, self.chunk_start,
-                             self.chunk_info, self.row_ptr, self.col, self.col16, chunk_cap=cap, col_t=self.col_t,
-                             chunk_win=self.chunk_win)
-        # one search that stages the hit words and expands them into rows
-        # (falling back to the fill pass by itself when a window is wider than
-        # the staged words can describe)
-        _, nnz2 = vct_neighbors(self.nl, self.pos, max(nnz, 1), 0, self._nws)
-        if nnz2 != nnz:
-            raise VctError("vct_neighbors", VCT_E_HIP)
+        self.col_t = torch.empty(nnz, dtype=torch.int32, device=device) if keep_col else None
+        nl.col16 = self.col16.data_ptr()
+        if keep_col:
+            nl.col, nl.col_t = self.col.data_ptr(), self.col_t.data_ptr()
+        vct_neighbors_rows(nl, self.pos, nnz, staged, self._nws)
         self.state64 = self.state32 = self.flags = None
         self.mask = None
 
