@@ -89,8 +89,8 @@ __global__ __launch_bounds__(kAThreads, 2) void k_adjoint_weights(AdjArgs A) {
     constexpr int nL = Dm::nL, nk = Dm::nk;
     __shared__ double4 sd[kAWin];   // x, y, z, V
     __shared__ WindowT<D> w;
-    const uint32_t b = xcd_tile(blockIdx.x, gridDim.x);
-    if (b >= *A.nchunks) return;   // uniform over the work-group
+    uint32_t b;
+    if (!chunk_of_block(A.nchunks, b)) return;   // uniform over the work-group
     const int64_t n = A.n;
     const int64_t p0 = A.cstart[b], p1 = A.cstart[b + 1];
     if (threadIdx.x < kWave) {
@@ -369,8 +369,8 @@ __global__ __launch_bounds__(kAThreads, 2) void k_r2_prep(AdjArgs A, double* __r
     __shared__ double4 sd[kAWin];   // x, y, z, V
     __shared__ double sf[kAWin];    // phi
     __shared__ WindowT<D> w;
-    const uint32_t b = xcd_tile(blockIdx.x, gridDim.x);
-    if (b >= *A.nchunks) return;   // uniform over the work-group
+    uint32_t b;
+    if (!chunk_of_block(A.nchunks, b)) return;   // uniform over the work-group
     const int64_t n = A.n;
     const int64_t p0 = A.cstart[b], p1 = A.cstart[b + 1];
     if (threadIdx.x < kWave) {

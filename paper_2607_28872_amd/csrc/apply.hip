@@ -320,8 +320,8 @@ __global__ __launch_bounds__((kChunk * ApplyCfg<T, C>::lanes), (ApplyCfg<T, C>::
     __shared__ uint4 scol4[kColCap ? kColCap / 8 : 1];
     __shared__ T sacc[kChunk][nk + D];
     __shared__ WindowT<D> w;
-    const uint32_t b = xcd_tile(blockIdx.x, gridDim.x);
-    if (b >= *A.nchunks) return;   // uniform over the work-group
+    uint32_t b;
+    if (!chunk_of_block(A.nchunks, b)) return;   // uniform over the work-group
     const int64_t n = A.n;
     const int64_t p0 = A.cstart[b], p1 = A.cstart[b + 1];
     if (threadIdx.x < kWave) {

@@ -637,8 +637,8 @@ __global__ __launch_bounds__(kNbThreads) void k_nb_chunk(int64_t n, const double
                                                          int32_t* __restrict__ col, uint16_t* __restrict__ col16,
                                                          SearchHead* __restrict__ head, int32_t* __restrict__ wide,
                                                          int32_t* __restrict__ win_tab) {
-    const uint32_t b = xcd_tile(blockIdx.x, gridDim.x);
-    if (b >= *nchunks) return;   // uniform over the work-group
+    uint32_t b;
+    if (!chunk_of_block(nchunks, b)) return;   // uniform over the work-group
     nb_chunk<D, MODE>(b, n, pos, g, R2, cs, cstart, cinfo, counts, row_ptr, col, col16, head, wide, win_tab);
 }
 
@@ -698,8 +698,8 @@ __global__ __launch_bounds__(kExT) void k_nb_expand(Grid g, const int64_t* __res
     __shared__ uint32_t bucket[33];               // words per hit count (32 - count), then offsets
     __shared__ uint32_t list[kExList];            // particle | word << 6 | hits of the row before it << 12
     __shared__ __align__(16) uint16_t sout[kExOut];
-    const uint32_t b = xcd_tile(blockIdx.x, gridDim.x);
-    if (b >= *nchunks) return;   // uniform over the work-group
+    uint32_t b;
+    if (!chunk_of_block(nchunks, b)) return;   // uniform over the work-group
     const int64_t p0 = cstart[b];
     const int np = (int)(cstart[b + 1] - p0);
     const int wv = threadIdx.x / kWave, pl = threadIdx.x % kWave;
@@ -956,8 +956,8 @@ __global__ __launch_bounds__(kTThreads) void k_col_transpose(Grid g, const int64
     __shared__ int32_t base[kTWin];
     __shared__ WindowT<D> w;
     __shared__ int s_own[kMaxRanges], s_nr[kMaxRanges];   // per range: the chunk's column and the ranges, seen from it
-    const uint32_t b = xcd_tile(blockIdx.x, gridDim.x);
-    if (b >= *nchunks) return;   // uniform over the work-group
+    uint32_t b;
+    if (!chunk_of_block(nchunks, b)) return;   // uniform over the work-group
     const int64_t p0 = cstart[b];
     const int np = (int)(cstart[b + 1] - p0);
     if (threadIdx.x < kWave) {

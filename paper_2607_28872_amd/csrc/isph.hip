@@ -85,8 +85,8 @@ __global__ __launch_bounds__(kZThreads, 4) void k_ops0(ZeroArgs A, MapParams mp)
     __shared__ double4 sd[kZWin];
     __shared__ double sf[kZWin];
     __shared__ WindowT<D> w;
-    const uint32_t b = xcd_tile(blockIdx.x, gridDim.x);
-    if (b >= *A.nchunks) return;   // uniform over the work-group
+    uint32_t b;
+    if (!chunk_of_block(A.nchunks, b)) return;   // uniform over the work-group
     const int64_t n = A.n;
     const int64_t p0 = A.cstart[b], p1 = A.cstart[b + 1];
     if (threadIdx.x < kWave) {
@@ -178,8 +178,8 @@ __global__ __launch_bounds__(kZThreads, 4) void k_grad_sum(ZeroArgs A, MapParams
     __shared__ double4 sd[kZWin];
     __shared__ double2 sp[kZWin];   // rho_j, p_j / rho_j^2
     __shared__ WindowT<D> w;
-    const uint32_t b = xcd_tile(blockIdx.x, gridDim.x);
-    if (b >= *A.nchunks) return;
+    uint32_t b;
+    if (!chunk_of_block(A.nchunks, b)) return;   // uniform over the work-group
     const int64_t n = A.n;
     const int64_t p0 = A.cstart[b], p1 = A.cstart[b + 1];
     if (threadIdx.x < kWave) {

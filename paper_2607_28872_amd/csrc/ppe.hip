@@ -88,8 +88,8 @@ __global__ __launch_bounds__(kQThreads, 4) void k_ppe_first(PpeArgs A, MapParams
     __shared__ double4 sd[kQWinF];
     __shared__ double sf[NC][kQWinF];
     __shared__ WindowT<D> w;
-    const uint32_t b = xcd_tile(blockIdx.x, gridDim.x);
-    if (b >= *A.nchunks) return;   // uniform over the work-group
+    uint32_t b;
+    if (!chunk_of_block(A.nchunks, b)) return;   // uniform over the work-group
     const int64_t n = A.n;
     const int64_t p0 = A.cstart[b], p1 = A.cstart[b + 1];
     if (threadIdx.x < kWave) {
@@ -227,8 +227,8 @@ __global__ __launch_bounds__(kQThreads, 2) void k_ppe_diag(PpeArgs A) {
     constexpr int nL = Dm::nL, nk = Dm::nk;
     __shared__ double4 sd[kQWin];
     __shared__ WindowT<D> w;
-    const uint32_t b = xcd_tile(blockIdx.x, gridDim.x);
-    if (b >= *A.nchunks) return;
+    uint32_t b;
+    if (!chunk_of_block(A.nchunks, b)) return;   // uniform over the work-group
     const int64_t n = A.n;
     const int64_t p0 = A.cstart[b], p1 = A.cstart[b + 1];
     if (threadIdx.x < kWave) {

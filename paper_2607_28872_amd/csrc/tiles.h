@@ -38,6 +38,23 @@ struct ChunkTable {
     const int64_t* count;   // device scalar: number of chunks
 };
 
+// The chunk of this work-group, one per block; false for the blocks past the
+// last chunk.  The launches size their grid by an upper bound (columns + n /
+// 64 + 1): the count stays on the device.  The chunks themselves, not the
+// blocks, are shared out over the XCDs: dealt out by the grid, the last XCDs
+// hold the blocks that return at once, and the others take 11% more chunks
+// than their share in 3-D at R = 3 d0 (four and a half chunks a column), 30%
+// more for the cubic spline (two and a half).  Sharing out the chunks, one
+// MI355X: FP64 apply 1.18 -> 1.09 ms (2,097,152 particles) and 0.56 -> 0.49 ms
+// (1,048,352), with the cubic spline 0.90 -> 0.77 ms; moment sweeps 5.51 ->
+// 5.16 ms (8,388,608).
+__device__ __forceinline__ bool chunk_of_block(const int64_t* __restrict__ nchunks, uint32_t& b) {
+    const uint32_t n = (uint32_t)*nchunks;
+    if (blockIdx.x >= n) return false;
+    b = xcd_tile(blockIdx.x, n);
+    return true;
+}
+
 template <int D> struct WindowT {
     int nr;
     int64_t gstart[kMaxRanges];
