@@ -443,18 +443,18 @@ size_t vct_adjoint_workspace_size(int dim, int64_t n, int64_t nnz, int nterms);
  *              fixed).
  * dphi, two forms; each evaluates every weight W_ij once and gives the same
  * bits on every run (no floating-point atomics):
- *   with nl->col_t: every particle i writes u_i W_ij for its row into the
- *     workspace at the transposed position col_t[e], then every particle k sums
- *     its row of that buffer in row order (the map costs a binary search per
- *     entry to build, so this pays when one geometry serves many adjoints);
- *   without (push form; needs nl->chunk_win, VCT_E_ARG otherwise): per
- *     background-cell column, every particle i adds
- *     u_i W_ij (and -u_i sum_j W_ij to itself) to accumulators of the
- *     column's window held in LDS as exact integers: each term is scaled by
- *     2^k from a per-column bound M on the terms (k = 61 - ilogb(M)), rounded
- *     and summed in two 64-bit integer parts, so the order of arrival does not
- *     matter; the column's totals go to one of 3^(d-1) slots per particle,
- *     summed in slot order.  The rounding of each term is at most 2^-62 M.
+ *   transposed form (nl->col_t given, and either nl->chunk_win is not or the
+ *     mean window of a cell column is beyond 3264 particles): every particle i
+ *     writes u_i W_ij for its row into the workspace at the transposed position
+ *     col_t[e], then every particle k sums its row of that buffer in row order;
+ *   push form (otherwise; needs nl->chunk_win, VCT_E_ARG without it and
+ *     without nl->col_t): per background-cell column, every particle i adds
+ *     u_i W_ij to accumulators of the column's window held in LDS as exact
+ *     integers: each term is scaled by 2^k from a per-column bound M on the
+ *     terms (k = 62 - ilogb(M) - bitlen(longest row)), rounded and summed in
+ *     64-bit integers, so the order of arrival does not matter; the column's
+ *     totals go to one of 3^(d-1) slots per particle, summed in slot order,
+ *     and the row sum u_i sum_j W_ij is subtracted.
  * dtheta: per particle from D^ phi_i, reduced in a fixed order.
  * `state64` must come from vct_moments (or vct_moments_resolve) with out_mask
  * containing VCT_OUT_LAP and either VCT_OUT_PZ or both VCT_OUT_PGRAD and
@@ -467,11 +467,11 @@ size_t vct_adjoint_workspace_size(int dim, int64_t n, int64_t nnz, int nterms);
  * is not finite makes the outputs it reaches NaN.  The workspace holds
  * nnz + (1 + 3^(d-1)) n doubles and the reduction partials
  * (vct_adjoint_workspace_size, with nnz = nl->nnz).  When both dphi and
- * dtheta are wanted, dtheta is computed on a second stream of the calling
- * host thread (created on its first such call on the device, default
- * priority, kept until the process ends), forked from `stream` and joined
- * back into it by events: the outputs are complete in `stream` order as for
- * one stream.                                                                  */
+ * dtheta of at least 3,000,000 particles are wanted, dtheta is computed on a
+ * second stream of the calling host thread (created on its first such call on
+ * the device, default priority, kept until the process ends), forked from
+ * `stream` and joined back into it by events: the outputs are complete in
+ * `stream` order as for one stream.                                            */
 int vct_apply_ops_adjoint(const vct_nlist* nl, const double* pos_sorted, const double* vol_sorted, int kernel,
                           const double* state64, uint32_t out_mask, const vct_map* map /* host */,
                           const double* proj, const double* u, double* dphi, double* dtheta, void* ws,
