@@ -19,6 +19,8 @@
 namespace vct {
 
 int nlist_check(const vct_nlist* nl, Grid& g);
+int apply_lap(const vct_nlist* nl, const Grid& g, const double* x, const double* pos, const double* vol, int kernel,
+              const double* state, uint32_t mask, const uint8_t* dirichlet, double* out, hipStream_t s);
 
 constexpr int kQLanes = 8;                    // lanes per particle
 constexpr int kQThreads = kChunk * kQLanes;   // one chunk per work-group
@@ -294,10 +296,8 @@ enum { ST_RUNNING = 0, ST_CONVERGED = 1, ST_BREAKDOWN = 2, ST_MAXIT = 3 };
 
 struct BicgVec {
     int64_t n;
-    int nout, lap_row;
-    const uint8_t* dirichlet;
     const double* b;
-    double *x, *r, *rh, *p, *v, *s, *t, *ph, *sh, *dinv, *tmp, *part, *sc;
+    double *x, *r, *rh, *p, *v, *s, *t, *ph, *sh, *dinv, *part, *sc;
 };
 
 __device__ __forceinline__ void block_partials(double (&v)[kVSlots], int ns, double* part) {
@@ -315,16 +315,11 @@ __device__ __forceinline__ void block_partials(double (&v)[kVSlots], int ns, dou
     }
 }
 
-// A x on the pressure system from the operator's output tmp (the Laplacian row)
-__device__ __forceinline__ double sys_row(const BicgVec& V, int64_t i, const double* xin) {
-    return (V.dirichlet && V.dirichlet[i]) ? xin[i] : V.tmp[i * V.nout + V.lap_row];
-}
-
-// stage 0: r = b - A x0, r^ = r, p = v = 0; partials (r^, r), (r, r), (b, b)
+// stage 0 (t = A x0): r = b - t, r^ = r, p = v = 0; partials (r^, r), (r, r), (b, b)
 __global__ __launch_bounds__(kVThreads) void k_bicg_init(BicgVec V) {
     double acc[kVSlots] = {0.0, 0.0, 0.0};
     for (int64_t i = (int64_t)blockIdx.x * kVThreads + threadIdx.x; i < V.n; i += (int64_t)kVBlocks * kVThreads) {
-        const double ri = V.b[i] - sys_row(V, i, V.x);
+        const double ri = V.b[i] - V.t[i];
         V.r[i] = ri;
         V.rh[i] = ri;
         V.p[i] = 0.0;
@@ -400,14 +395,12 @@ __global__ __launch_bounds__(kVThreads) void k_bicg_p(BicgVec V) {
     }
 }
 
-// v = A p^; partial (r^, v)
+// v = A p^ (from the operator); partial (r^, v)
 __global__ __launch_bounds__(kVThreads) void k_bicg_v(BicgVec V) {
     if (V.sc[S_DONE] != 0.0) return;
     double acc[kVSlots] = {0.0, 0.0, 0.0};
     for (int64_t i = (int64_t)blockIdx.x * kVThreads + threadIdx.x; i < V.n; i += (int64_t)kVBlocks * kVThreads) {
-        const double vi = sys_row(V, i, V.ph);
-        V.v[i] = vi;
-        acc[0] += V.rh[i] * vi;
+        acc[0] += V.rh[i] * V.v[i];
     }
     block_partials(acc, 1, V.part);
 }
@@ -423,13 +416,12 @@ __global__ __launch_bounds__(kVThreads) void k_bicg_s(BicgVec V) {
     }
 }
 
-// t = A s^; partials (t, s), (t, t)
+// t = A s^ (from the operator); partials (t, s), (t, t)
 __global__ __launch_bounds__(kVThreads) void k_bicg_t(BicgVec V) {
     if (V.sc[S_DONE] != 0.0) return;
     double acc[kVSlots] = {0.0, 0.0, 0.0};
     for (int64_t i = (int64_t)blockIdx.x * kVThreads + threadIdx.x; i < V.n; i += (int64_t)kVBlocks * kVThreads) {
-        const double ti = sys_row(V, i, V.sh);
-        V.t[i] = ti;
+        const double ti = V.t[i];
         acc[0] += ti * V.s[i];
         acc[1] += ti * ti;
     }
@@ -451,11 +443,11 @@ __global__ __launch_bounds__(kVThreads) void k_bicg_x(BicgVec V) {
     block_partials(acc, 2, V.part);
 }
 
-// true residual b - A x; partial (res, res)
+// true residual b - A x (t = A x); partial (res, res)
 __global__ __launch_bounds__(kVThreads) void k_bicg_res(BicgVec V) {
     double acc[kVSlots] = {0.0, 0.0, 0.0};
     for (int64_t i = (int64_t)blockIdx.x * kVThreads + threadIdx.x; i < V.n; i += (int64_t)kVBlocks * kVThreads) {
-        const double ri = V.b[i] - sys_row(V, i, V.x);
+        const double ri = V.b[i] - V.t[i];
         acc[0] += ri * ri;
     }
     block_partials(acc, 1, V.part);
@@ -548,7 +540,7 @@ extern "C" int vct_ppe_correct(const vct_nlist* nl, const double* pos_sorted, co
 extern "C" size_t vct_ppe_workspace_size(int dim, int64_t n, uint32_t out_mask) {
     if ((dim != 2 && dim != 3) || n < 0 || !mask_valid(out_mask)) return 0;
     const size_t nn = (size_t)(n > 0 ? n : 1);
-    return aligned_sum({nn * 10 * sizeof(double), nn * (size_t)n_out_rows(dim, out_mask) * sizeof(double),
+    return aligned_sum({nn * 9 * sizeof(double),
                         (size_t)kVSlots * kVBlocks * sizeof(double), (size_t)kNScalars * sizeof(double)});
 }
 
@@ -570,14 +562,12 @@ extern "C" int vct_ppe_solve(const vct_nlist* nl, const double* pos_sorted, cons
     if (!rhs || !p) return VCT_E_ARG;
     if (!ws || ws_bytes < vct_ppe_workspace_size(dim, n, out_mask)) return VCT_E_WORKSPACE;
     hipStream_t s = as_stream(stream);
-    const int nout = n_out_rows(dim, out_mask);
     Carver cv(ws, ws_bytes);
     BicgVec V;
-    V.n = n; V.nout = nout; V.lap_row = a.lap_row; V.dirichlet = dirichlet; V.b = rhs; V.x = p;
-    double* vecs = cv.take<double>((size_t)n * 10);
+    V.n = n; V.b = rhs; V.x = p;
+    double* vecs = cv.take<double>((size_t)n * 9);
     V.r = vecs; V.rh = vecs + n; V.p = vecs + 2 * n; V.v = vecs + 3 * n; V.s = vecs + 4 * n; V.t = vecs + 5 * n;
     V.ph = vecs + 6 * n; V.sh = vecs + 7 * n; V.dinv = vecs + 8 * n;
-    V.tmp = cv.take<double>((size_t)n * nout);
     V.part = cv.take<double>((size_t)kVSlots * kVBlocks);
     V.sc = cv.take<double>(kNScalars);
     const int64_t cap = chunk_cap(nl, g);
@@ -591,11 +581,11 @@ extern "C" int vct_ppe_solve(const vct_nlist* nl, const double* pos_sorted, cons
     }
     VCT_LAUNCH_CHECK();
     const double tol2 = tol * tol;
-    auto matvec = [&](const double* xin) {
-        return vct_apply_ops(nl, 1, xin, pos_sorted, vol_sorted, kernel, state64, out_mask, VCT_FP64, V.tmp, stream);
+    auto matvec = [&](const double* xin, double* out) {
+        return apply_lap(nl, g, xin, pos_sorted, vol_sorted, kernel, state64, out_mask, dirichlet, out, s);
     };
     const dim3 vg(kVBlocks), vb(kVThreads);
-    if ((st = matvec(V.x)) < 0) return st;
+    if ((st = matvec(V.x, V.t)) < 0) return st;
     VCT_LAUNCH("k_bicg_init", k_bicg_init, vg, vb, 0, s, V);
     VCT_LAUNCH_CHECK();
     VCT_LAUNCH("k_bicg_reduce", k_bicg_reduce, dim3(1), dim3(kVBlocks), 0, s, V.part, V.sc, (int)R_INIT, tol2, max_iter);
@@ -611,14 +601,14 @@ extern "C" int vct_ppe_solve(const vct_nlist* nl, const double* pos_sorted, cons
         for (int k = 0; k < kBatch && done_iters < max_iter; ++k, ++done_iters) {
             VCT_LAUNCH("k_bicg_p", k_bicg_p, vg, vb, 0, s, V);
             VCT_LAUNCH_CHECK();
-            if ((st = matvec(V.ph)) < 0) return st;
+            if ((st = matvec(V.ph, V.v)) < 0) return st;
             VCT_LAUNCH("k_bicg_v", k_bicg_v, vg, vb, 0, s, V);
             VCT_LAUNCH_CHECK();
             VCT_LAUNCH("k_bicg_reduce", k_bicg_reduce, dim3(1), dim3(kVBlocks), 0, s, V.part, V.sc, (int)R_ALPHA, tol2, max_iter);
             VCT_LAUNCH_CHECK();
             VCT_LAUNCH("k_bicg_s", k_bicg_s, vg, vb, 0, s, V);
             VCT_LAUNCH_CHECK();
-            if ((st = matvec(V.sh)) < 0) return st;
+            if ((st = matvec(V.sh, V.t)) < 0) return st;
             VCT_LAUNCH("k_bicg_t", k_bicg_t, vg, vb, 0, s, V);
             VCT_LAUNCH_CHECK();
             VCT_LAUNCH("k_bicg_reduce", k_bicg_reduce, dim3(1), dim3(kVBlocks), 0, s, V.part, V.sc, (int)R_OMEGA, tol2, max_iter);
@@ -630,7 +620,7 @@ extern "C" int vct_ppe_solve(const vct_nlist* nl, const double* pos_sorted, cons
         }
     }
     // the true residual of the result
-    if ((st = matvec(V.x)) < 0) return st;
+    if ((st = matvec(V.x, V.t)) < 0) return st;
     VCT_LAUNCH("k_bicg_res", k_bicg_res, vg, vb, 0, s, V);
     VCT_LAUNCH_CHECK();
     VCT_LAUNCH("k_bicg_reduce", k_bicg_reduce, dim3(1), dim3(kVBlocks), 0, s, V.part, V.sc, (int)R_RES, tol2, max_iter);
