@@ -24,10 +24,6 @@ namespace vct {
 
 int nlist_check(const vct_nlist* nl, Grid& g);
 
-constexpr int kZLanes = 8;                    // lanes per particle
-constexpr int kZThreads = kChunk * kZLanes;   // one chunk per work-group
-constexpr int kZWin = 1400;                   // LDS window capacity (records)
-
 struct ZeroArgs {
     int64_t n;
     double invR, KG;
@@ -41,7 +37,6 @@ struct ZeroArgs {
     const int4* cinfo;
     const int32_t* cwin;
     const int64_t* nchunks;
-    int nf;
     const double* f;      // [nf][n] fields, or the pressure
     const double* rho;    // [n] or NULL (gradient summation)
     double rho0;
@@ -62,28 +57,35 @@ inline double gfac_norm(int dim, int kernel, double R) {
     return ad / (l * l);
 }
 
-// window record of neighbour slot t: position, volume (LDS or global)
-template <int D>
-__device__ __forceinline__ double4 window_record(const ZeroArgs& A, const WindowT<D>& w, const double4* sd, bool in_lds,
-                                                 int t, int64_t& j) {
-    if (in_lds) return sd[t];
-    j = window_global<D>(w, t);
-    const int64_t n = A.n;
-    return make_double4(A.pos[j], A.pos[n + j], D == 3 ? A.pos[2 * n + j] : 0.0, A.vol[j]);
-}
+// One record of a sweep: position and two values (volume and field, or the two
+// weights of the pressure sum).
+struct ZeroRec {
+    double4 q;   // x, y, z, first value
+    double f;
+};
 
-// Per chunk of particles (one work-group, kZLanes lanes per particle), for
-// each field: a = sum V c~ phi_ij r~, S_IJ = sum V c~ phi_ij r~_I r~_J / |r~|^2
-// and t = sum V c~ phi_ij; then
+// Per chunk of particles and field (one work-group, RowShape<C>::lanes lanes per
+// particle): a = sum V c~ phi_ij r~, S_IJ = sum V c~ phi_ij
+// r~_I r~_J / |r~|^2 and t = sum V c~ phi_ij; then
 //   grad^ = KG R a,   H^_IJ = KG (c S_IJ - delta_IJ t)
-// and the output rows of the mask at the particle's mapping.
-template <int D, int KERNEL>
-__global__ __launch_bounds__(kZThreads, 4) void k_ops0(ZeroArgs A, MapParams mp) {
+// and the output rows of the mask at the particle's mapping.  The sums go
+// through LDS to the first wave, one particle per lane: every lane of every
+// wave evaluating its particle's mapping (sines, cosines, divisions) was a
+// third of the kernel.  (The fields are a dimension of the grid: in a loop over
+// them the compiler keeps the mapping's uniform products in registers across
+// the sweeps and spills them, 2 ms.)  1,065,547 particles in 3-D, one field: 0.75 -> 0.46
+// ms, 1,048,576 in 2-D 0.32 -> 0.096 ms; bound by latency (staging, then one
+// wave's mapping) with two work-groups on a CU.
+template <int D, int KERNEL, int C>
+__global__ __launch_bounds__((kChunk * RowShape<C>::lanes), RowShape<C>::waves) void k_ops0(ZeroArgs A, MapParams mp) {
     using Dm = Dims<D>;
-    constexpr int m = Dm::m;
+    using Sh = RowShape<C>;
+    constexpr int m = Dm::m, kLanes = Sh::lanes, kThreads = kChunk * kLanes, kWin = Sh::win;
+    constexpr int kSums = D + m + 2;   // a, S, t, neighbours at zero distance
     constexpr double cc = D == 2 ? 4.0 : 5.0;
-    __shared__ double4 sd[kZWin];
-    __shared__ double sf[kZWin];
+    __shared__ double4 sd[kWin];
+    __shared__ double sf[kWin];
+    __shared__ double ssum[kSums][kChunk];
     __shared__ WindowT<D> w;
     uint32_t b;
     if (!chunk_of_block(A.nchunks, b)) return;   // uniform over the work-group
@@ -93,44 +95,42 @@ __global__ __launch_bounds__(kZThreads, 4) void k_ops0(ZeroArgs A, MapParams mp)
         if (A.cwin) window_load<D>(A.cwin, b, w);
         else chunk_window_wave<D>(A.g, A.cs, A.cinfo[b], w);
     }
-    const int lane = threadIdx.x % kZLanes;
-    const int64_t i = p0 + threadIdx.x / kZLanes;
+    const int lane = threadIdx.x % kLanes, pl = threadIdx.x / kLanes;
+    const int64_t i = p0 + pl;
     const bool valid = i < p1;
     const int64_t ii = valid ? i : p0;
     double xi[3];
 #pragma unroll
     for (int a = 0; a < 3; ++a) xi[a] = a < D ? A.pos[a * n + ii] : 0.0;
+    const RowSlots<kLanes, Sh::slots> rs(A.col16, valid ? A.row_ptr[ii] : 0, valid ? A.row_ptr[ii + 1] : 0, lane);
     __syncthreads();
-    const int W = w.off[w.nr];
-    const bool in_lds = W <= kZWin;
-    if (in_lds) {
-        for (int t = threadIdx.x; t < W; t += kZThreads) {
-            const int64_t j = window_global<D>(w, t);
-            sd[t] = make_double4(A.pos[j], A.pos[n + j], D == 3 ? A.pos[2 * n + j] : 0.0, A.vol[j]);
-        }
-    }
-    const int64_t rb = valid ? A.row_ptr[ii] : 0, re = valid ? A.row_ptr[ii + 1] : 0;
-    // the mapping at the particle (lane 0 writes)
-    const MapCoef<double> mc = map_coef_at(mp, ii, xi[0], D == 3 ? xi[1] : 0.0, xi[D - 1]);
-    const bool map_ok = mc.alpha > 0.0 && isfinite(mc.alpha + mc.gx + mc.gy + mc.c0 + mc.zxy);
-    const double nanv = __builtin_nan("");
-    for (int f = 0; f < A.nf; ++f) {
-        const double* F = A.f + (int64_t)f * n;
-        if (f > 0) __syncthreads();   // the previous field's reads of sf are done
-        if (in_lds)
-            for (int t = threadIdx.x; t < W; t += kZThreads) sf[t] = F[window_global<D>(w, t)];
-        __syncthreads();
-        const double fi = F[ii];
-        double acc[D], S[m], ts = 0.0, bad = 0.0;
+    const int W = __builtin_amdgcn_readfirstlane(w.off[w.nr]);
+    const bool in_lds = W <= kWin;
+    const int f = blockIdx.y;
+    const double* F = A.f + (int64_t)f * n;
+    auto record = [&](int t) -> ZeroRec {
+        const int64_t j = window_global<D>(w, t);
+        return {make_double4(A.pos[j], A.pos[n + j], D == 3 ? A.pos[2 * n + j] : 0.0, A.vol[j]), F[j]};
+    };
+    if (in_lds)
+        stage_window<kWin, kThreads>(W, record, [&](int t, const ZeroRec& z) {
+            sd[t] = z.q;
+            sf[t] = z.f;
+        });
+    __syncthreads();
+    const double fi = F[ii];
+    double acc[D], S[m], ts = 0.0, bad = 0.0;
 #pragma unroll
-        for (int a = 0; a < D; ++a) acc[a] = 0.0;
+    for (int a = 0; a < D; ++a) acc[a] = 0.0;
 #pragma unroll
-        for (int p = 0; p < m; ++p) S[p] = 0.0;
-        for (int64_t e = rb + lane; e < re; e += kZLanes) {
-            const int t = dcheck((int)A.col16[e], W, kChkWindow);
-            int64_t j = 0;
-            const double4 q = window_record<D>(A, w, sd, in_lds, t, j);
-            const double fj = in_lds ? sf[t] : F[j];
+    for (int p = 0; p < m; ++p) S[p] = 0.0;
+    sweep_row(rs, A.col16, W, in_lds,
+        [&](int t) -> ZeroRec {
+            if (in_lds) return {sd[t], sf[t]};
+            return record(t);
+        },
+        [&](const ZeroRec& z) {
+            const double4& q = z.q;
             double r[D];
             r[0] = (q.x - xi[0]) * A.invR;
             r[1] = (q.y - xi[1]) * A.invR;
@@ -142,41 +142,61 @@ __global__ __launch_bounds__(kZThreads, 4) void k_ops0(ZeroArgs A, MapParams mp)
             // non-finite) distance makes the particle's outputs NaN
             bad = q2 > 0.0 ? bad : 1.0;
             const double y = vrsq(q2);
-            const double fij = q.w * kernel_shape<KERNEL>(q2 * y) * (fj - fi);
+            const double fij = q.w * kernel_shape<KERNEL>(q2 * y) * (z.f - fi);
             const double u = fij * (y * y);
 #pragma unroll
             for (int a = 0; a < D; ++a) acc[a] = fma(fij, r[a], acc[a]);
             ts += fij;
 #pragma unroll
             for (int p = 0; p < m; ++p) S[p] = fma(u * r[pair_a<D>(p)], r[pair_b<D>(p)], S[p]);
-        }
+        });
 #pragma unroll
-        for (int a = 0; a < D; ++a) acc[a] = group_sum(acc[a], kZLanes);
+    for (int a = 0; a < D; ++a) acc[a] = group_sum(acc[a], kLanes);
 #pragma unroll
-        for (int p = 0; p < m; ++p) S[p] = group_sum(S[p], kZLanes);
-        ts = group_sum(ts, kZLanes);
-        bad = group_sum(bad, kZLanes);
-        if (valid && lane == 0) {
-            double pg[D], ph[m];
-            const double kr = A.KG / A.invR;
+    for (int p = 0; p < m; ++p) S[p] = group_sum(S[p], kLanes);
+    ts = group_sum(ts, kLanes);
+    bad = group_sum(bad, kLanes);
+    if (lane == 0) {
 #pragma unroll
-            for (int a = 0; a < D; ++a) pg[a] = kr * acc[a];
+        for (int a = 0; a < D; ++a) ssum[a][pl] = acc[a];
 #pragma unroll
-            for (int p = 0; p < m; ++p) ph[p] = A.KG * (p < D ? fma(cc, S[p], -ts) : cc * S[p]);
-            double* o = A.out + ((int64_t)f * n + ii) * A.nrows;
-            const bool ok = map_ok && bad == 0.0;
-            emit_rows<D>(A.mask, mc, pg, ph, [&](int k, double v) { o[k] = ok ? v : nanv; });
-        }
+        for (int p = 0; p < m; ++p) ssum[D + p][pl] = S[p];
+        ssum[D + m][pl] = ts;
+        ssum[D + m + 1][pl] = bad;
     }
+    __syncthreads();
+    if (threadIdx.x >= kChunk || p0 + threadIdx.x >= p1) return;
+    const int q = threadIdx.x;
+    const int64_t iq = p0 + q;
+    const MapCoef<double> mc =
+        map_coef_at(mp, iq, A.pos[iq], D == 3 ? A.pos[n + iq] : 0.0, A.pos[(int64_t)(D - 1) * n + iq]);
+    const bool ok = mc.alpha > 0.0 && isfinite(mc.alpha + mc.gx + mc.gy + mc.c0 + mc.zxy) &&
+                    ssum[D + m + 1][q] == 0.0;
+    double pg[D], ph[m];
+    const double kr = A.KG / A.invR;
+#pragma unroll
+    for (int a = 0; a < D; ++a) pg[a] = kr * ssum[a][q];
+#pragma unroll
+    for (int p = 0; p < m; ++p)
+        ph[p] = A.KG * (p < D ? fma(cc, ssum[D + p][q], -ssum[D + m][q]) : cc * ssum[D + p][q]);
+    double* o = A.out + ((int64_t)f * n + iq) * A.nrows;
+    const double nanv = __builtin_nan("");
+    emit_rows<D>(A.mask, mc, pg, ph, [&](int k, double v) { o[k] = ok ? v : nanv; });
 }
 
 // Summation gradient of the pressure field f[0]: per particle
 // grad^ = rho_i KG R sum_j V_j rho_j (p_j / rho_j^2 + p_i / rho_i^2) c~ r~_ij,
-// then J grad^ (GRAD rows) and grad^ (PGRAD rows).
-template <int D, int KERNEL>
-__global__ __launch_bounds__(kZThreads, 4) void k_grad_sum(ZeroArgs A, MapParams mp) {
-    __shared__ double4 sd[kZWin];
-    __shared__ double2 sp[kZWin];   // rho_j, p_j / rho_j^2
+// then J grad^ (GRAD rows) and grad^ (PGRAD rows).  The records hold V_j p_j /
+// rho_j and V_j rho_j.  1,065,547 particles in 3-D: 0.78 -> 0.44 ms, 1,048,576
+// in 2-D 0.33 -> 0.091 ms.
+template <int D, int KERNEL, int C>
+__global__ __launch_bounds__((kChunk * RowShape<C>::lanes), RowShape<C>::waves) void k_grad_sum(ZeroArgs A,
+                                                                                               MapParams mp) {
+    using Sh = RowShape<C>;
+    constexpr int kLanes = Sh::lanes, kThreads = kChunk * kLanes, kWin = Sh::win;
+    __shared__ double4 sd[kWin];    // x, y, z, V_j p_j / rho_j
+    __shared__ double sf[kWin];     // V_j rho_j
+    __shared__ double ssum[D + 1][kChunk];
     __shared__ WindowT<D> w;
     uint32_t b;
     if (!chunk_of_block(A.nchunks, b)) return;   // uniform over the work-group
@@ -186,8 +206,8 @@ __global__ __launch_bounds__(kZThreads, 4) void k_grad_sum(ZeroArgs A, MapParams
         if (A.cwin) window_load<D>(A.cwin, b, w);
         else chunk_window_wave<D>(A.g, A.cs, A.cinfo[b], w);
     }
-    const int lane = threadIdx.x % kZLanes;
-    const int64_t i = p0 + threadIdx.x / kZLanes;
+    const int lane = threadIdx.x % kLanes, pl = threadIdx.x / kLanes;
+    const int64_t i = p0 + pl;
     const bool valid = i < p1;
     const int64_t ii = valid ? i : p0;
     double xi[3];
@@ -195,61 +215,68 @@ __global__ __launch_bounds__(kZThreads, 4) void k_grad_sum(ZeroArgs A, MapParams
     for (int a = 0; a < 3; ++a) xi[a] = a < D ? A.pos[a * n + ii] : 0.0;
     const double rhoi = A.rho ? A.rho[ii] : A.rho0;
     const double pi_r = A.f[ii] / (rhoi * rhoi);
+    const RowSlots<kLanes, Sh::slots> rs(A.col16, valid ? A.row_ptr[ii] : 0, valid ? A.row_ptr[ii + 1] : 0, lane);
+    auto record = [&](int t) -> ZeroRec {
+        const int64_t j = window_global<D>(w, t);
+        const double rj = A.rho ? A.rho[j] : A.rho0, V = A.vol[j];
+        return {make_double4(A.pos[j], A.pos[n + j], D == 3 ? A.pos[2 * n + j] : 0.0, V * (A.f[j] / rj)), V * rj};
+    };
     __syncthreads();
-    const int W = w.off[w.nr];
-    const bool in_lds = W <= kZWin;
-    if (in_lds) {
-        for (int t = threadIdx.x; t < W; t += kZThreads) {
-            const int64_t j = window_global<D>(w, t);
-            sd[t] = make_double4(A.pos[j], A.pos[n + j], D == 3 ? A.pos[2 * n + j] : 0.0, A.vol[j]);
-            const double rj = A.rho ? A.rho[j] : A.rho0;
-            sp[t] = make_double2(rj, A.f[j] / (rj * rj));
-        }
-    }
+    const int W = __builtin_amdgcn_readfirstlane(w.off[w.nr]);
+    const bool in_lds = W <= kWin;
+    if (in_lds)
+        stage_window<kWin, kThreads>(W, record, [&](int t, const ZeroRec& z) {
+            sd[t] = z.q;
+            sf[t] = z.f;
+        });
     __syncthreads();
     double acc[D], bad = 0.0;
 #pragma unroll
     for (int a = 0; a < D; ++a) acc[a] = 0.0;
-    const int64_t rb = valid ? A.row_ptr[ii] : 0, re = valid ? A.row_ptr[ii + 1] : 0;
-    for (int64_t e = rb + lane; e < re; e += kZLanes) {
-        const int t = dcheck((int)A.col16[e], W, kChkWindow);
-        int64_t j = 0;
-        const double4 q = window_record<D>(A, w, sd, in_lds, t, j);
-        double2 pr;
-        if (in_lds) {
-            pr = sp[t];
-        } else {
-            const double rj = A.rho ? A.rho[j] : A.rho0;
-            pr = make_double2(rj, A.f[j] / (rj * rj));
-        }
-        double r[D];
-        r[0] = (q.x - xi[0]) * A.invR;
-        r[1] = (q.y - xi[1]) * A.invR;
-        if (D == 3) r[D - 1] = (q.z - xi[2]) * A.invR;
-        double q2 = r[0] * r[0];
+    sweep_row(rs, A.col16, W, in_lds,
+        [&](int t) -> ZeroRec {
+            if (in_lds) return {sd[t], sf[t]};
+            return record(t);
+        },
+        [&](const ZeroRec& z) {
+            const double4& q = z.q;
+            double r[D];
+            r[0] = (q.x - xi[0]) * A.invR;
+            r[1] = (q.y - xi[1]) * A.invR;
+            if (D == 3) r[D - 1] = (q.z - xi[2]) * A.invR;
+            double q2 = r[0] * r[0];
 #pragma unroll
-        for (int a = 1; a < D; ++a) q2 = fma(r[a], r[a], q2);
-        bad = q2 > 0.0 ? bad : 1.0;
-        const double y = vrsq(q2);
-        const double s = q.w * pr.x * (pr.y + pi_r) * kernel_shape<KERNEL>(q2 * y);
+            for (int a = 1; a < D; ++a) q2 = fma(r[a], r[a], q2);
+            bad = q2 > 0.0 ? bad : 1.0;
+            const double y = vrsq(q2);
+            const double s = fma(z.f, pi_r, q.w) * kernel_shape<KERNEL>(q2 * y);
 #pragma unroll
-        for (int a = 0; a < D; ++a) acc[a] = fma(s, r[a], acc[a]);
+            for (int a = 0; a < D; ++a) acc[a] = fma(s, r[a], acc[a]);
+        });
+#pragma unroll
+    for (int a = 0; a < D; ++a) acc[a] = group_sum(acc[a], kLanes);
+    bad = group_sum(bad, kLanes);
+    if (lane == 0) {
+#pragma unroll
+        for (int a = 0; a < D; ++a) ssum[a][pl] = rhoi * acc[a];
+        ssum[D][pl] = bad;
     }
-#pragma unroll
-    for (int a = 0; a < D; ++a) acc[a] = group_sum(acc[a], kZLanes);
-    bad = group_sum(bad, kZLanes);
-    if (!valid || lane != 0) return;
-    const MapCoef<double> mc = map_coef_at(mp, ii, xi[0], D == 3 ? xi[1] : 0.0, xi[D - 1]);
-    const bool map_ok = mc.alpha > 0.0 && isfinite(mc.alpha + mc.gx + mc.gy) && bad == 0.0;
+    __syncthreads();
+    if (threadIdx.x >= kChunk || p0 + threadIdx.x >= p1) return;
+    const int q = threadIdx.x;
+    const int64_t iq = p0 + q;
+    const MapCoef<double> mc =
+        map_coef_at(mp, iq, A.pos[iq], D == 3 ? A.pos[n + iq] : 0.0, A.pos[(int64_t)(D - 1) * n + iq]);
+    const bool ok = mc.alpha > 0.0 && isfinite(mc.alpha + mc.gx + mc.gy) && ssum[D][q] == 0.0;
     const double nanv = __builtin_nan("");
     double pg[D], ph[Dims<D>::m];
-    const double kr = rhoi * A.KG / A.invR;
+    const double kr = A.KG / A.invR;
 #pragma unroll
-    for (int a = 0; a < D; ++a) pg[a] = kr * acc[a];
+    for (int a = 0; a < D; ++a) pg[a] = kr * ssum[a][q];
 #pragma unroll
     for (int p = 0; p < Dims<D>::m; ++p) ph[p] = 0.0;
-    double* o = A.out + ii * A.nrows;
-    emit_rows<D>(A.mask, mc, pg, ph, [&](int k, double v) { o[k] = map_ok ? v : nanv; });
+    double* o = A.out + iq * A.nrows;
+    emit_rows<D>(A.mask, mc, pg, ph, [&](int k, double v) { o[k] = ok ? v : nanv; });
 }
 
 static int zero_common(const vct_nlist* nl, Grid& g, const double* pos_sorted, const double* vol_sorted, int kernel,
@@ -298,19 +325,33 @@ extern "C" int vct_apply_ops0(const vct_nlist* nl, int nf, const double* phi_sor
     if (nf < 0) return VCT_E_ARG;
     if (nl->n == 0 || nf == 0) return VCT_OK;
     if (!phi_sorted || !out) return VCT_E_ARG;
-    a.nf = nf; a.f = phi_sorted; a.out = out;
     hipStream_t s = as_stream(stream);
     const int64_t cap = zero_cap(nl, g);
-#define VCT_OPS0(D, K) VCT_LAUNCH("k_ops0", (k_ops0<D, K>), dim3((unsigned)cap), dim3(kZThreads), 0, s, a, mp)
-    if (nl->dim == 2) {
-        if (kernel == VCT_KERNEL_WENDLAND_C2) VCT_OPS0(2, VCT_KERNEL_WENDLAND_C2);
-        else VCT_OPS0(2, VCT_KERNEL_CUBIC_SPLINE);
-    } else {
-        if (kernel == VCT_KERNEL_WENDLAND_C2) VCT_OPS0(3, VCT_KERNEL_WENDLAND_C2);
-        else VCT_OPS0(3, VCT_KERNEL_CUBIC_SPLINE);
+    const int64_t mean = mean_row(nl);
+#define VCT_OPS0(D, K, C)                                                                                   \
+    VCT_LAUNCH("k_ops0", (k_ops0<D, K, C>), dim3((unsigned)cap, (unsigned)nfl), dim3(kChunk * RowShape<C>::lanes), 0, \
+               s, a, mp)
+#define VCT_OPS0_ROWS(D, K, S)                                       \
+    do {                                                             \
+        if (mean <= short_row<D>()) VCT_OPS0(D, K, S);                \
+        else VCT_OPS0(D, K, kRowsLong);                               \
+    } while (0)
+    constexpr int kGridFields = 65535;   // the grid's limit
+    for (int f0 = 0; f0 < nf; f0 += kGridFields) {
+        const int nfl = nf - f0 < kGridFields ? nf - f0 : kGridFields;
+        a.f = phi_sorted + (int64_t)f0 * nl->n;
+        a.out = out + (int64_t)f0 * nl->n * a.nrows;
+        if (nl->dim == 2) {
+            if (kernel == VCT_KERNEL_WENDLAND_C2) VCT_OPS0_ROWS(2, VCT_KERNEL_WENDLAND_C2, kRowsShort2);
+            else VCT_OPS0_ROWS(2, VCT_KERNEL_CUBIC_SPLINE, kRowsShort2);
+        } else {
+            if (kernel == VCT_KERNEL_WENDLAND_C2) VCT_OPS0_ROWS(3, VCT_KERNEL_WENDLAND_C2, kRowsShort3);
+            else VCT_OPS0_ROWS(3, VCT_KERNEL_CUBIC_SPLINE, kRowsShort3);
+        }
+        VCT_LAUNCH_CHECK();
     }
+#undef VCT_OPS0_ROWS
 #undef VCT_OPS0
-    VCT_LAUNCH_CHECK();
     return VCT_OK;
 }
 
@@ -326,17 +367,25 @@ extern "C" int vct_grad_sum(const vct_nlist* nl, const double* pos_sorted, const
     if (!rho && !(rho0 != 0.0 && isfinite(rho0))) return VCT_E_ARG;
     if (nl->n == 0) return VCT_OK;
     if (!p || !out) return VCT_E_ARG;
-    a.nf = 1; a.f = p; a.rho = rho; a.rho0 = rho0; a.out = out;
+    a.f = p; a.rho = rho; a.rho0 = rho0; a.out = out;
     hipStream_t s = as_stream(stream);
     const int64_t cap = zero_cap(nl, g);
-#define VCT_GSUM(D, K) VCT_LAUNCH("k_grad_sum", (k_grad_sum<D, K>), dim3((unsigned)cap), dim3(kZThreads), 0, s, a, mp)
+    const int64_t mean = mean_row(nl);
+#define VCT_GSUM(D, K, C)                                                                                            \
+    VCT_LAUNCH("k_grad_sum", (k_grad_sum<D, K, C>), dim3((unsigned)cap), dim3(kChunk * RowShape<C>::lanes), 0, s, a, mp)
+#define VCT_GSUM_ROWS(D, K, S)                                       \
+    do {                                                             \
+        if (mean <= short_row<D>()) VCT_GSUM(D, K, S);                \
+        else VCT_GSUM(D, K, kRowsLong);                               \
+    } while (0)
     if (nl->dim == 2) {
-        if (kernel == VCT_KERNEL_WENDLAND_C2) VCT_GSUM(2, VCT_KERNEL_WENDLAND_C2);
-        else VCT_GSUM(2, VCT_KERNEL_CUBIC_SPLINE);
+        if (kernel == VCT_KERNEL_WENDLAND_C2) VCT_GSUM_ROWS(2, VCT_KERNEL_WENDLAND_C2, kRowsShort2);
+        else VCT_GSUM_ROWS(2, VCT_KERNEL_CUBIC_SPLINE, kRowsShort2);
     } else {
-        if (kernel == VCT_KERNEL_WENDLAND_C2) VCT_GSUM(3, VCT_KERNEL_WENDLAND_C2);
-        else VCT_GSUM(3, VCT_KERNEL_CUBIC_SPLINE);
+        if (kernel == VCT_KERNEL_WENDLAND_C2) VCT_GSUM_ROWS(3, VCT_KERNEL_WENDLAND_C2, kRowsShort3);
+        else VCT_GSUM_ROWS(3, VCT_KERNEL_CUBIC_SPLINE, kRowsShort3);
     }
+#undef VCT_GSUM_ROWS
 #undef VCT_GSUM
     VCT_LAUNCH_CHECK();
     return VCT_OK;

@@ -22,11 +22,6 @@ int nlist_check(const vct_nlist* nl, Grid& g);
 int apply_lap(const vct_nlist* nl, const Grid& g, const double* x, const double* pos, const double* vol, int kernel,
               const double* state, uint32_t mask, const uint8_t* dirichlet, double* out, hipStream_t s);
 
-constexpr int kQLanes = 8;                    // lanes per particle
-constexpr int kQThreads = kChunk * kQLanes;   // one chunk per work-group
-constexpr int kQWin = 1600;                   // LDS window capacity (records)
-constexpr int kQWinF = 1400;                  // the same with the fields beside the records
-
 struct PpeArgs {
     int64_t n;
     double invR, R;
@@ -76,20 +71,35 @@ __device__ __forceinline__ double kernel_value(double q, double R) {
     }
 }
 
-// One chunk per work-group, kQLanes lanes per particle: the first-order sums
-// a_c = sum_j V_j c~ f_c,ij r~_ij of nc fields (and, MODE 0, the kernel sum),
-// then the particle's epilogue:
+// One record of a first-order sweep: position and volume, and the fields.
+template <int NC> struct FirstRec {
+    double4 q;
+    double f[NC];
+};
+
+// One chunk per work-group, RowShape<C>::lanes lanes per particle: the
+// first-order sums a_c = sum_j V_j c~ f_c,ij r~_ij of nc fields (and, MODE 0,
+// the kernel sum), then the particles' epilogue:
 //   MODE 0: right-hand side (nc = dim velocity components);
 //   MODE 1: corrector (nc = 1, the pressure).
-template <int D, int KERNEL, int MODE>
-__global__ __launch_bounds__(kQThreads, 4) void k_ppe_first(PpeArgs A, MapParams mp) {
+// The sums go through LDS (in the place of the window) to the first wave, one
+// particle per lane, which forms the gradients and the mapping; done by the
+// first lane of every group it took every wave the instructions of a whole
+// one.  1,048,352 particles in 3-D: right-hand side 0.97 -> 0.47 ms, corrector
+// 0.54 -> 0.38 ms; 524,288 in 2-D 0.13 -> 0.050 and 0.13 -> 0.042 ms.
+template <int D, int KERNEL, int MODE, int C>
+__global__ __launch_bounds__((kChunk * RowShape<C>::lanes), RowShape<C>::waves) void k_ppe_first(PpeArgs A,
+                                                                                                MapParams mp) {
     using Dm = Dims<D>;
-    constexpr int nL = Dm::nL;
+    using Sh = RowShape<C>;
+    constexpr int nL = Dm::nL, kLanes = Sh::lanes, kThreads = kChunk * kLanes, kWin = Sh::win;
     constexpr int NC = MODE == 0 ? D : 1;
+    constexpr int kSums = NC * D + (MODE == 0 ? 1 : 0);
     // window records in LDS: position and volume, and the fields
-    __shared__ double4 sd[kQWinF];
-    __shared__ double sf[NC][kQWinF];
+    __shared__ double4 sd[kWin];
+    __shared__ double sf[NC][kWin];
     __shared__ WindowT<D> w;
+    static_assert(kSums * kChunk * 8 <= kWin * 32, "the sums fit the window buffer");
     uint32_t b;
     if (!chunk_of_block(A.nchunks, b)) return;   // uniform over the work-group
     const int64_t n = A.n;
@@ -98,8 +108,8 @@ __global__ __launch_bounds__(kQThreads, 4) void k_ppe_first(PpeArgs A, MapParams
         if (A.cwin) window_load<D>(A.cwin, b, w);
         else chunk_window_wave<D>(A.g, A.cs, A.cinfo[b], w);
     }
-    const int lane = threadIdx.x % kQLanes;
-    const int64_t i = p0 + threadIdx.x / kQLanes;
+    const int lane = threadIdx.x % kLanes, pl = threadIdx.x / kLanes;
+    const int64_t i = p0 + pl;
     const bool valid = i < p1;
     const int64_t ii = valid ? i : p0;
     double xi[3];
@@ -108,17 +118,24 @@ __global__ __launch_bounds__(kQThreads, 4) void k_ppe_first(PpeArgs A, MapParams
     double fi[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) fi[c] = A.f[(int64_t)c * n + ii];
-    __syncthreads();
-    const int W = w.off[w.nr];
-    const bool in_lds = W <= kQWinF;
-    if (in_lds) {
-        for (int t = threadIdx.x; t < W; t += kQThreads) {
-            const int64_t j = window_global<D>(w, t);
-            sd[t] = make_double4(A.pos[j], A.pos[n + j], D == 3 ? A.pos[2 * n + j] : 0.0, A.vol[j]);
+    const RowSlots<kLanes, Sh::slots> rs(A.col16, valid ? A.row_ptr[ii] : 0, valid ? A.row_ptr[ii + 1] : 0, lane);
+    auto record = [&](int t) -> FirstRec<NC> {
+        const int64_t j = window_global<D>(w, t);
+        FirstRec<NC> z;
+        z.q = make_double4(A.pos[j], A.pos[n + j], D == 3 ? A.pos[2 * n + j] : 0.0, A.vol[j]);
 #pragma unroll
-            for (int c = 0; c < NC; ++c) sf[c][t] = A.f[(int64_t)c * n + j];
-        }
-    }
+        for (int c = 0; c < NC; ++c) z.f[c] = A.f[(int64_t)c * n + j];
+        return z;
+    };
+    __syncthreads();
+    const int W = __builtin_amdgcn_readfirstlane(w.off[w.nr]);
+    const bool in_lds = W <= kWin;
+    if (in_lds)
+        stage_window<kWin, kThreads>(W, record, [&](int t, const FirstRec<NC>& z) {
+            sd[t] = z.q;
+#pragma unroll
+            for (int c = 0; c < NC; ++c) sf[c][t] = z.f[c];
+        });
     __syncthreads();
     double acc[NC][D];
 #pragma unroll
@@ -126,50 +143,58 @@ __global__ __launch_bounds__(kQThreads, 4) void k_ppe_first(PpeArgs A, MapParams
 #pragma unroll
         for (int a = 0; a < D; ++a) acc[c][a] = 0.0;
     double ksum = 0.0;
-    const int64_t rb = valid ? A.row_ptr[ii] : 0, re = valid ? A.row_ptr[ii + 1] : 0;
-    for (int64_t e = rb + lane; e < re; e += kQLanes) {
-        const int t = dcheck((int)A.col16[e], W, kChkWindow);
-        double4 q;
-        double fj[NC];
-        if (in_lds) {
-            q = sd[t];
+    sweep_row(rs, A.col16, W, in_lds,
+        [&](int t) -> FirstRec<NC> {
+            if (!in_lds) return record(t);
+            FirstRec<NC> z;
+            z.q = sd[t];
 #pragma unroll
-            for (int c = 0; c < NC; ++c) fj[c] = sf[c][t];
-        } else {
-            const int64_t j = window_global<D>(w, t);
-            q = make_double4(A.pos[j], A.pos[n + j], D == 3 ? A.pos[2 * n + j] : 0.0, A.vol[j]);
+            for (int c = 0; c < NC; ++c) z.f[c] = sf[c][t];
+            return z;
+        },
+        [&](const FirstRec<NC>& z) {
+            const double4& q = z.q;
+            double r[D];
+            r[0] = (q.x - xi[0]) * A.invR;
+            r[1] = (q.y - xi[1]) * A.invR;
+            if (D == 3) r[D - 1] = (q.z - xi[2]) * A.invR;
+            double q2 = r[0] * r[0];
 #pragma unroll
-            for (int c = 0; c < NC; ++c) fj[c] = A.f[(int64_t)c * n + j];
-        }
-        double r[D];
-        r[0] = (q.x - xi[0]) * A.invR;
-        r[1] = (q.y - xi[1]) * A.invR;
-        if (D == 3) r[D - 1] = (q.z - xi[2]) * A.invR;
-        double q2 = r[0] * r[0];
+            for (int a = 1; a < D; ++a) q2 = fma(r[a], r[a], q2);
+            const double qn = vsqrt(q2);
+            const double vc = q.w * kernel_shape<KERNEL>(qn);
 #pragma unroll
-        for (int a = 1; a < D; ++a) q2 = fma(r[a], r[a], q2);
-        const double qn = vsqrt(q2);
-        const double vc = q.w * kernel_shape<KERNEL>(qn);
+            for (int c = 0; c < NC; ++c) {
+                const double fij = vc * (z.f[c] - fi[c]);
 #pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            const double fij = vc * (fj[c] - fi[c]);
-#pragma unroll
-            for (int a = 0; a < D; ++a) acc[c][a] = fma(fij, r[a], acc[c][a]);
-        }
-        if (MODE == 0) ksum = fma(q.w, kernel_value<D, KERNEL>(qn, A.R), ksum);
-    }
+                for (int a = 0; a < D; ++a) acc[c][a] = fma(fij, r[a], acc[c][a]);
+            }
+            if (MODE == 0) ksum = fma(q.w, kernel_value<D, KERNEL>(qn, A.R), ksum);
+        });
 #pragma unroll
     for (int c = 0; c < NC; ++c)
 #pragma unroll
-        for (int a = 0; a < D; ++a) acc[c][a] = group_sum(acc[c][a], kQLanes);
-    if (MODE == 0) ksum = group_sum(ksum, kQLanes);
-    if (!valid || lane != 0) return;
+        for (int a = 0; a < D; ++a) acc[c][a] = group_sum(acc[c][a], kLanes);
+    if (MODE == 0) ksum = group_sum(ksum, kLanes);
+    __syncthreads();   // the window is no longer needed
+    double* ssum = reinterpret_cast<double*>(sd);   // [kSums][kChunk]
+    if (lane == 0) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int a = 0; a < D; ++a) ssum[(c * D + a) * kChunk + pl] = acc[c][a];
+        if (MODE == 0) ssum[NC * D * kChunk + pl] = ksum;
+    }
+    __syncthreads();
+    if (threadIdx.x >= kChunk || p0 + threadIdx.x >= p1) return;
+    const int pq = threadIdx.x;
+    const int64_t iq = p0 + pq;
     // first-order projected gradients G_c = L~ a_c / R
     double L2[nL];
     bool ok = true;
 #pragma unroll
     for (int p = 0; p < nL; ++p) {
-        L2[p] = A.state[(int64_t)p * n + ii];
+        L2[p] = A.state[(int64_t)p * n + iq];
         ok = ok && isfinite(L2[p]);
     }
     double G[NC][3];
@@ -180,7 +205,7 @@ __global__ __launch_bounds__(kQThreads, 4) void k_ppe_first(PpeArgs A, MapParams
         for (int a = 0; a < D; ++a) {
             double t = 0.0;
 #pragma unroll
-            for (int bb = 0; bb < D; ++bb) t += L2[sym_index<D>(a, bb)] * acc[c][bb];
+            for (int bb = 0; bb < D; ++bb) t += L2[sym_index<D>(a, bb)] * ssum[(c * D + bb) * kChunk + pq];
             g[a] = t * A.invR;
         }
         // 3-D component order (2-D: x^, 0, z^)
@@ -189,7 +214,8 @@ __global__ __launch_bounds__(kQThreads, 4) void k_ppe_first(PpeArgs A, MapParams
         G[c][2] = g[D - 1];
     }
     // the Jacobian column of z^ at the particle: J = [[1,0,gx],[0,1,gy],[0,0,alpha]]
-    const MapCoef<double> mc = map_coef_at(mp, ii, xi[0], D == 3 ? xi[1] : 0.0, xi[D - 1]);
+    const MapCoef<double> mc =
+        map_coef_at(mp, iq, A.pos[iq], D == 3 ? A.pos[n + iq] : 0.0, A.pos[(int64_t)(D - 1) * n + iq]);
     const double nanv = __builtin_nan("");
     if (MODE == 0) {
         // physical divergence: sum_I (J grad^ v_I)_I; component I along physical axis I
@@ -201,13 +227,13 @@ __global__ __launch_bounds__(kQThreads, 4) void k_ppe_first(PpeArgs A, MapParams
             dv += Ip < 2 ? G[c][Ip] + gxy[Ip] * G[c][2] : mc.alpha * G[c][2];
         }
         double wself = kernel_value<D, KERNEL>(0.0, A.R);
-        double ds = A.rho * fma(A.vol[ii], wself, ksum);
+        double ds = A.rho * fma(A.vol[iq], wself, ssum[NC * D * kChunk + pq]);
         if (!ok) dv = ds = nanv;
-        if (A.div) A.div[ii] = dv;
-        if (A.dens) A.dens[ii] = ds;
-        const double jri = A.jr ? A.jr[ii] : 1.0;
-        const bool dir = A.dirichlet && A.dirichlet[ii];
-        A.rhs[ii] = dir ? (A.pbc ? A.pbc[ii] : 0.0)
+        if (A.div) A.div[iq] = dv;
+        if (A.dens) A.dens[iq] = ds;
+        const double jri = A.jr ? A.jr[iq] : 1.0;
+        const bool dir = A.dirichlet && A.dirichlet[iq];
+        A.rhs[iq] = dir ? (A.pbc ? A.pbc[iq] : 0.0)
                         : A.rho / A.dt * dv + A.gamma * (A.rho * jri - ds) / (A.dt * A.dt);
     } else {
         // physical pressure gradient J grad^ p
@@ -216,18 +242,20 @@ __global__ __launch_bounds__(kQThreads, 4) void k_ppe_first(PpeArgs A, MapParams
         for (int c = 0; c < D; ++c) {
             const int Ip = D == 3 ? c : (c == 0 ? 0 : 2);
             const double g = ok ? gp[Ip] : nanv;
-            A.vout[(int64_t)c * n + ii] = A.vstar[(int64_t)c * n + ii] - A.dt / A.rho * g;
+            A.vout[(int64_t)c * n + iq] = A.vstar[(int64_t)c * n + iq] - A.dt / A.rho * g;
         }
     }
 }
 
 // Jacobi diagonal of the pressure system: the coefficient of p_i in row i,
 // -sum_j W_ij on ordinary rows, 1 on Dirichlet rows; dinv = its inverse.
-template <int D, int KERNEL>
-__global__ __launch_bounds__(kQThreads, 2) void k_ppe_diag(PpeArgs A) {
+// 1,048,352 particles in 3-D 0.42 -> 0.34 ms, 524,288 in 2-D 0.058 -> 0.033 ms.
+template <int D, int KERNEL, int C>
+__global__ __launch_bounds__((kChunk * RowShape<C>::lanes), RowShape<C>::waves) void k_ppe_diag(PpeArgs A) {
     using Dm = Dims<D>;
-    constexpr int nL = Dm::nL, nk = Dm::nk;
-    __shared__ double4 sd[kQWin];
+    using Sh = RowShape<C>;
+    constexpr int nL = Dm::nL, nk = Dm::nk, kLanes = Sh::lanes, kThreads = kChunk * kLanes, kWin = Sh::win;
+    __shared__ double4 sd[kWin];
     __shared__ WindowT<D> w;
     uint32_t b;
     if (!chunk_of_block(A.nchunks, b)) return;   // uniform over the work-group
@@ -237,8 +265,8 @@ __global__ __launch_bounds__(kQThreads, 2) void k_ppe_diag(PpeArgs A) {
         if (A.cwin) window_load<D>(A.cwin, b, w);
         else chunk_window_wave<D>(A.g, A.cs, A.cinfo[b], w);
     }
-    const int lane = threadIdx.x % kQLanes;
-    const int64_t i = p0 + threadIdx.x / kQLanes;
+    const int lane = threadIdx.x % kLanes;
+    const int64_t i = p0 + threadIdx.x / kLanes;
     const bool valid = i < p1;
     const int64_t ii = valid ? i : p0;
     double xi[3];
@@ -249,30 +277,20 @@ __global__ __launch_bounds__(kQThreads, 2) void k_ppe_diag(PpeArgs A) {
     for (int p = 0; p < nL; ++p) L2[p] = (pair_a<D>(p) == pair_b<D>(p) ? 1.0 : 2.0) * A.state[(int64_t)p * n + ii];
 #pragma unroll
     for (int c = 0; c < nk; ++c) Pl[c] = A.state[(int64_t)(nL + A.lap_row * nk + c) * n + ii];
+    const RowSlots<kLanes, Sh::slots> rs(A.col16, valid ? A.row_ptr[ii] : 0, valid ? A.row_ptr[ii + 1] : 0, lane);
+    auto record = [&](int t) -> double4 {
+        const int64_t j = window_global<D>(w, t);
+        return make_double4(A.pos[j], A.pos[n + j], D == 3 ? A.pos[2 * n + j] : 0.0, A.vol[j]);
+    };
     __syncthreads();
-    const int W = w.off[w.nr];
-    const bool in_lds = W <= kQWin;
-    if (in_lds) {
-        for (int t = threadIdx.x; t < W; t += kQThreads) {
-            const int64_t j = window_global<D>(w, t);
-            sd[t] = make_double4(A.pos[j], A.pos[n + j], D == 3 ? A.pos[2 * n + j] : 0.0, A.vol[j]);
-        }
-    }
+    const int W = __builtin_amdgcn_readfirstlane(w.off[w.nr]);
+    const bool in_lds = W <= kWin;
+    if (in_lds) stage_window<kWin, kThreads>(W, record, [&](int t, const double4& q) { sd[t] = q; });
     __syncthreads();
     double s = 0.0;
-    const int64_t rb = valid ? A.row_ptr[ii] : 0, re = valid ? A.row_ptr[ii + 1] : 0;
-    for (int64_t e = rb + lane; e < re; e += kQLanes) {
-        const int t = dcheck((int)A.col16[e], W, kChkWindow);
-        double4 q;
-        if (in_lds) {
-            q = sd[t];
-        } else {
-            const int64_t j = window_global<D>(w, t);
-            q = make_double4(A.pos[j], A.pos[n + j], D == 3 ? A.pos[2 * n + j] : 0.0, A.vol[j]);
-        }
-        s += lap_weight<D, KERNEL>(q, xi, A.invR, L2, Pl);
-    }
-    s = group_sum(s, kQLanes);
+    sweep_row(rs, A.col16, W, in_lds, [&](int t) -> double4 { return in_lds ? sd[t] : record(t); },
+              [&](const double4& q) { s += lap_weight<D, KERNEL>(q, xi, A.invR, L2, Pl); });
+    s = group_sum(s, kLanes);
     if (valid && lane == 0) {
         const bool dir = A.dirichlet && A.dirichlet[ii];
         A.dinv[ii] = dir ? 1.0 : 1.0 / (-s);
@@ -477,18 +495,40 @@ static int64_t chunk_cap(const vct_nlist* nl, const Grid& g) {
     return ncols + nl->n / kChunk + 1;
 }
 
-template <int MODE>
-static int launch_first(int dim, int kernel, const PpeArgs& a, const MapParams& mp, int64_t cap, hipStream_t s) {
+template <int MODE, int D, int KERNEL>
+static int launch_first(const PpeArgs& a, const MapParams& mp, int64_t mean, int64_t cap, hipStream_t s) {
     const char* name = MODE == 0 ? "k_ppe_first (rhs)" : "k_ppe_first (correct)";
-#define VCT_PPE_FIRST(D, K) VCT_LAUNCH(name, (k_ppe_first<D, K, MODE>), dim3((unsigned)cap), dim3(kQThreads), 0, s, a, mp)
-    if (dim == 2) {
-        if (kernel == VCT_KERNEL_WENDLAND_C2) VCT_PPE_FIRST(2, VCT_KERNEL_WENDLAND_C2);
-        else VCT_PPE_FIRST(2, VCT_KERNEL_CUBIC_SPLINE);
-    } else {
-        if (kernel == VCT_KERNEL_WENDLAND_C2) VCT_PPE_FIRST(3, VCT_KERNEL_WENDLAND_C2);
-        else VCT_PPE_FIRST(3, VCT_KERNEL_CUBIC_SPLINE);
-    }
-#undef VCT_PPE_FIRST
+    constexpr int kShort = D == 2 ? kRowsShort2 : kRowsShort3;
+    if (mean <= short_row<D>())
+        VCT_LAUNCH(name, (k_ppe_first<D, KERNEL, MODE, kShort>), dim3((unsigned)cap),
+                   dim3(kChunk * RowShape<kShort>::lanes), 0, s, a, mp);
+    else
+        VCT_LAUNCH(name, (k_ppe_first<D, KERNEL, MODE, kRowsLong>), dim3((unsigned)cap),
+                   dim3(kChunk * RowShape<kRowsLong>::lanes), 0, s, a, mp);
+    VCT_LAUNCH_CHECK();
+    return VCT_OK;
+}
+
+template <int MODE>
+static int launch_first(const vct_nlist* nl, int kernel, const PpeArgs& a, const MapParams& mp, int64_t cap,
+                        hipStream_t s) {
+    const int64_t mean = mean_row(nl);
+    if (nl->dim == 2)
+        return kernel == VCT_KERNEL_WENDLAND_C2 ? launch_first<MODE, 2, VCT_KERNEL_WENDLAND_C2>(a, mp, mean, cap, s)
+                                                : launch_first<MODE, 2, VCT_KERNEL_CUBIC_SPLINE>(a, mp, mean, cap, s);
+    return kernel == VCT_KERNEL_WENDLAND_C2 ? launch_first<MODE, 3, VCT_KERNEL_WENDLAND_C2>(a, mp, mean, cap, s)
+                                            : launch_first<MODE, 3, VCT_KERNEL_CUBIC_SPLINE>(a, mp, mean, cap, s);
+}
+
+template <int D, int KERNEL>
+static int launch_diag(const PpeArgs& a, int64_t mean, int64_t cap, hipStream_t s) {
+    constexpr int kShort = D == 2 ? kRowsShort2 : kRowsShort3;
+    if (mean <= short_row<D>())
+        VCT_LAUNCH("k_ppe_diag", (k_ppe_diag<D, KERNEL, kShort>), dim3((unsigned)cap),
+                   dim3(kChunk * RowShape<kShort>::lanes), 0, s, a);
+    else
+        VCT_LAUNCH("k_ppe_diag", (k_ppe_diag<D, KERNEL, kRowsLong>), dim3((unsigned)cap),
+                   dim3(kChunk * RowShape<kRowsLong>::lanes), 0, s, a);
     VCT_LAUNCH_CHECK();
     return VCT_OK;
 }
@@ -516,7 +556,7 @@ extern "C" int vct_ppe_rhs(const vct_nlist* nl, const double* pos_sorted, const 
     if (!vstar || !rhs) return VCT_E_ARG;
     a.f = vstar; a.jr = jr; a.dirichlet = dirichlet; a.pbc = pbc; a.rho = rho; a.dt = dt; a.gamma = gamma;
     a.rhs = rhs; a.div = div; a.dens = dens;
-    return launch_first<0>(nl->dim, kernel, a, mp, chunk_cap(nl, g), as_stream(stream));
+    return launch_first<0>(nl, kernel, a, mp, chunk_cap(nl, g), as_stream(stream));
 }
 
 extern "C" int vct_ppe_correct(const vct_nlist* nl, const double* pos_sorted, const double* vol_sorted, int kernel,
@@ -534,7 +574,7 @@ extern "C" int vct_ppe_correct(const vct_nlist* nl, const double* pos_sorted, co
     if (nl->n == 0) return VCT_OK;
     if (!p || !vstar || !vout) return VCT_E_ARG;
     a.f = p; a.vstar = vstar; a.vout = vout; a.rho = rho; a.dt = dt;
-    return launch_first<1>(nl->dim, kernel, a, mp, chunk_cap(nl, g), as_stream(stream));
+    return launch_first<1>(nl, kernel, a, mp, chunk_cap(nl, g), as_stream(stream));
 }
 
 extern "C" size_t vct_ppe_workspace_size(int dim, int64_t n, uint32_t out_mask) {
@@ -572,14 +612,14 @@ extern "C" int vct_ppe_solve(const vct_nlist* nl, const double* pos_sorted, cons
     V.sc = cv.take<double>(kNScalars);
     const int64_t cap = chunk_cap(nl, g);
     a.dirichlet = dirichlet; a.dinv = V.dinv;
-    if (dim == 2) {
-        if (kernel == VCT_KERNEL_WENDLAND_C2) VCT_LAUNCH("k_ppe_diag", (k_ppe_diag<2, VCT_KERNEL_WENDLAND_C2>), dim3((unsigned)cap), dim3(kQThreads), 0, s, a);
-        else VCT_LAUNCH("k_ppe_diag", (k_ppe_diag<2, VCT_KERNEL_CUBIC_SPLINE>), dim3((unsigned)cap), dim3(kQThreads), 0, s, a);
-    } else {
-        if (kernel == VCT_KERNEL_WENDLAND_C2) VCT_LAUNCH("k_ppe_diag", (k_ppe_diag<3, VCT_KERNEL_WENDLAND_C2>), dim3((unsigned)cap), dim3(kQThreads), 0, s, a);
-        else VCT_LAUNCH("k_ppe_diag", (k_ppe_diag<3, VCT_KERNEL_CUBIC_SPLINE>), dim3((unsigned)cap), dim3(kQThreads), 0, s, a);
-    }
-    VCT_LAUNCH_CHECK();
+    const int64_t mean = mean_row(nl);
+    if (dim == 2)
+        st = kernel == VCT_KERNEL_WENDLAND_C2 ? launch_diag<2, VCT_KERNEL_WENDLAND_C2>(a, mean, cap, s)
+                                              : launch_diag<2, VCT_KERNEL_CUBIC_SPLINE>(a, mean, cap, s);
+    else
+        st = kernel == VCT_KERNEL_WENDLAND_C2 ? launch_diag<3, VCT_KERNEL_WENDLAND_C2>(a, mean, cap, s)
+                                              : launch_diag<3, VCT_KERNEL_CUBIC_SPLINE>(a, mean, cap, s);
+    if (st) return st;
     const double tol2 = tol * tol;
     auto matvec = [&](const double* xin, double* out) {
         return apply_lap(nl, g, xin, pos_sorted, vol_sorted, kernel, state64, out_mask, dirichlet, out, s);

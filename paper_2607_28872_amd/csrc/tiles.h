@@ -183,4 +183,85 @@ __device__ __forceinline__ int64_t window_global(const WindowT<D>& w, int t) {
     return w.gstart[r] + (t - w.off[r]);
 }
 
+// ------------------------------------------------------------------ row sweeps
+
+// Launch shapes of the one-sweep kernels (conventional operators, pressure
+// right-hand side, corrector and diagonal): lanes per particle, row entries a
+// lane holds in registers, LDS window (records) and waves per SIMD, by class of
+// the mean row length (short_row).  The offsets of a row are read once, up
+// front, and the records one slot ahead of the arithmetic; read entry by entry
+// inside the loop they cost a trip to the L2 per entry.
+enum { kRowsLong = 0, kRowsShort3 = 1, kRowsShort2 = 2 };
+template <int C> struct RowShape;
+template <> struct RowShape<kRowsLong> { static constexpr int lanes = 8, slots = 14, win = 1400, waves = 4; };
+template <> struct RowShape<kRowsShort3> { static constexpr int lanes = 4, slots = 16, win = 1184, waves = 3; };
+template <> struct RowShape<kRowsShort2> { static constexpr int lanes = 4, slots = 8, win = 448, waves = 4; };
+
+// A lane's share of a row: entries rb + lane + LANES s, s < SLOTS, two 16-bit
+// window offsets per register (slots past the row's end repeat its first).
+template <int LANES, int SLOTS> struct RowSlots {
+    uint32_t pk[(SLOTS + 1) / 2];
+    int n = 0;   // filled slots
+    int64_t tail, end;
+    __device__ __forceinline__ RowSlots(const uint16_t* __restrict__ col16, int64_t rb, int64_t re, int lane) {
+        const int len = (int)(re - rb);
+        const uint16_t* c = col16 + rb + lane;
+        const uint32_t first = len > 0 ? (uint32_t)col16[rb] : 0u;
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s) {
+            const bool in = lane + LANES * s < len;
+            const uint32_t v = in ? (uint32_t)c[LANES * s] : first;
+            n += in ? 1 : 0;
+            if (s % 2 == 0) pk[s / 2] = v;
+            else pk[s / 2] |= v << 16;
+        }
+        tail = rb + lane + (int64_t)LANES * SLOTS;
+        end = re;
+    }
+    __device__ __forceinline__ int at(int s, int W) const {
+        return dcheck((int)((pk[s / 2] >> (16 * (s % 2))) & 0xffffu), W, kChkWindow);
+    }
+};
+
+// Stages the records of window offsets [0, W), W <= WIN: every load of a thread
+// before its first LDS store.
+template <int WIN, int THREADS, class Load, class Store>
+__device__ __forceinline__ void stage_window(int W, Load&& load, Store&& store) {
+    constexpr int kRep = (WIN + THREADS - 1) / THREADS;
+    decltype(load(0)) v[kRep];
+#pragma unroll
+    for (int k = 0; k < kRep; ++k) {
+        const int t = threadIdx.x + k * THREADS;
+        if (t < W) v[k] = load(t);   // lanes past the window load nothing (whole waves skip)
+    }
+#pragma unroll
+    for (int k = 0; k < kRep; ++k) {
+        const int t = threadIdx.x + k * THREADS;
+        if (t < W) store(t, v[k]);
+    }
+}
+
+// Visits every entry of a row: REC rec(t) of each window offset t, the records
+// of the register slots requested one slot ahead, then the entries past them.
+// in_lds (uniform): rec reads LDS, else memory (no read-ahead).
+template <int LANES, int SLOTS, class Rec, class Body>
+__device__ __forceinline__ void sweep_row(const RowSlots<LANES, SLOTS>& rs, const uint16_t* __restrict__ col16, int W,
+                                          bool in_lds, Rec&& rec, Body&& body) {
+    if (in_lds) {
+        auto next = rec(rs.at(0, W));
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s) {
+            const auto q = next;
+            if (s + 1 < SLOTS) next = rec(rs.at(s + 1, W));
+            __builtin_amdgcn_sched_barrier(0);
+            if (s < rs.n) body(q);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    // (from memory the whole row by its offsets: a loop over the slots would
+    // index the registers by a variable, which puts them in scratch memory)
+    const int64_t e0 = in_lds ? rs.tail : rs.tail - (int64_t)LANES * SLOTS;
+    for (int64_t e = e0; e < rs.end; e += LANES) body(rec(dcheck((int)col16[e], W, kChkWindow)));
+}
+
 }  // namespace vct
