@@ -23,12 +23,12 @@
 //
 // Within one row the neighbours are distinct, so their values are read at
 // once, and v_i after the first k exchanges is the composition of the affine
-// maps x -> (1 - c_k) x + c_k v_jk: one prefix scan over the lanes (64
-// entries at a time) gives v_i before every exchange, and with it every
-// neighbour's new value (the scan runs on DPP row shifts and broadcasts).
-// The v values of the cell's block are staged in LDS
-// (blocks larger than the LDS area are updated in place in memory, the same
-// arithmetic).  J / Jbar is formed once before the phases and J / v once
+// maps x -> (1 - c_k) x + c_k v_jk: one prefix scan over the lanes (128
+// entries at a time, two to a lane) gives v_i before every exchange, and with
+// it every neighbour's new value (the scan runs on DPP row shifts and
+// broadcasts).  The v values of the cell's block are staged in LDS (blocks
+// larger than the LDS area are updated in place in memory by one wave, 64
+// entries to a scan, the same maps).  J / Jbar is formed once before the phases and J / v once
 // after.
 #include "common.h"
 #include "map_dev.h"
@@ -38,7 +38,16 @@ namespace vct {
 
 int nlist_check(const vct_nlist* nl, Grid& g);
 
-constexpr int kJCap = 1024;   // block values staged in LDS (8 KB)
+constexpr int kJCap = 1024;   // block values staged in LDS
+// Launch shapes: waves of a cell's work-group, doubles of its LDS area, and the
+// block size up to which the neighbours' positions are staged with the values
+// (kJLong3: 5 groups to a CU; a block at R = 3 d0 has about 800).  Long rows in
+// 3-D take the first, by the mean row length (short_row).
+enum { kJLong3 = 0, kJShort3 = 1, kJ2 = 2 };
+template <int C> struct JShape;
+template <> struct JShape<kJLong3> { static constexpr int kD = 3, kWaves = 3, kArea = 3840, kPos = 960; };
+template <> struct JShape<kJShort3> { static constexpr int kD = 3, kWaves = 1, kArea = kJCap, kPos = 0; };
+template <> struct JShape<kJ2> { static constexpr int kD = 2, kWaves = 1, kArea = kJCap, kPos = 0; };
 
 struct JbarArgs {
     int64_t n;
@@ -61,6 +70,20 @@ __global__ __launch_bounds__(256) void k_jbar_ratio(int64_t n, const double* __r
     if (i < n) out[i] = a[i] / b[i];
 }
 
+// Orders the LDS accesses of one wave around it (the hardware takes a wave's
+// LDS instructions in order, so there is nothing to wait for; the compiler must
+// not move or forward across lanes).
+__device__ __forceinline__ void wave_order() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+__device__ __forceinline__ double lane_of(double v, int lane) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                            __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+
 // position of sorted index i in a window (the range holding it), or -1
 template <int D>
 __device__ __forceinline__ int window_offset_of(const WindowT<D>& w, int64_t i) {
@@ -74,11 +97,14 @@ __device__ __forceinline__ int window_offset_of(const WindowT<D>& w, int64_t i) 
 
 // A 64-bit value moved across lanes by a DPP control (row shifts, row
 // broadcasts, wave shift); lanes without a source, or masked by the row mask,
-// keep `id`.
-template <int CTRL, int ROWMASK = 0xF>
-__device__ __forceinline__ double dpp_move64(double v, double id) {
-    const int lo = __builtin_amdgcn_update_dpp(__double2loint(id), __double2loint(v), CTRL, ROWMASK, 0xF, false);
-    const int hi = __builtin_amdgcn_update_dpp(__double2hiint(id), __double2hiint(v), CTRL, ROWMASK, 0xF, false);
+// take `ID` (1 or 0).  Zero words come with the move itself where every row
+// takes part.
+template <int CTRL, int ROWMASK, int ID>
+__device__ __forceinline__ double dpp_move64(double v) {
+    constexpr int id_hi = ID ? 0x3ff00000 : 0;
+    constexpr bool zero = ROWMASK == 0xF;
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWMASK, 0xF, zero);
+    const int hi = __builtin_amdgcn_update_dpp(id_hi, __double2hiint(v), CTRL, ROWMASK, 0xF, zero && !ID);
     return __hiloint2double(hi, lo);
 }
 
@@ -87,7 +113,7 @@ __device__ __forceinline__ double dpp_move64(double v, double id) {
 // (1, 0) for lanes without one leaves a and b exactly as they are).
 template <int CTRL, int ROWMASK = 0xF>
 __device__ __forceinline__ void affine_step(double& a, double& b) {
-    const double ao = dpp_move64<CTRL, ROWMASK>(a, 1.0), bo = dpp_move64<CTRL, ROWMASK>(b, 0.0);
+    const double ao = dpp_move64<CTRL, ROWMASK, 1>(a), bo = dpp_move64<CTRL, ROWMASK, 0>(b);
     b = fma(a, bo, b);
     a = a * ao;
 }
@@ -145,7 +171,7 @@ __device__ __forceinline__ void row_geometry(const JbarArgs& A, const WindowT<D>
     }
 }
 
-// The exchanges of one cell (the body of k_jbar_phase).  FAST: the block's
+// The exchanges of one cell by one wave (the general form).  FAST: the block's
 // values are in LDS (vp = s_v, addressed by block offset); otherwise in
 // memory (vp = A.v, addressed by sorted index).  The geometry of the next
 // target's row (its window offsets and neighbour positions, which no exchange
@@ -175,7 +201,7 @@ __device__ __forceinline__ void jbar_cell(const JbarArgs& A, int64_t col, int64_
     int cur = 0;
     int64_t bcur = chunk_of(p0);
     load_window(bcur, cw[cur]);
-    __syncthreads();
+    wave_order();
     int64_t rb = row_ptr_of(p0), re = p0 + 1 - q0 < kJRows ? row_ptr_of(p0 + 1) : A.row_ptr[p0 + 1];
     double c[kJSlots];
     int64_t jj[kJSlots];
@@ -200,7 +226,7 @@ __device__ __forceinline__ void jbar_cell(const JbarArgs& A, int64_t col, int64_
                 nxt = 1 - cur;
                 load_window(b1, cw[nxt]);
                 bcur = b1;
-                __syncthreads();
+                wave_order();
             }
             row_geometry<D>(A, cw[nxt], blk, FAST, i + 1, rb1, re1, c1, jj1);
         }
@@ -217,7 +243,7 @@ __device__ __forceinline__ void jbar_cell(const JbarArgs& A, int64_t col, int64_
             for (int s = 0; s < kJSlots; ++s) {
                 double am = 1.0 - c[s], bm = c[s] * vj[s];
                 affine_scan(am, bm);
-                const double ap = dpp_move64<0x138>(am, 1.0), bp = dpp_move64<0x138>(bm, 0.0);   // wave_shr:1
+                const double ap = dpp_move64<0x138, 0xF, 1>(am), bp = dpp_move64<0x138, 0xF, 0>(bm);   // wave_shr:1
                 const double xk = fma(ap, vi, bp);
                 if (jj[s] >= 0) vp[jj[s]] = vj[s] - c[s] * (vj[s] - xk);
                 const double aT = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(am), kWave - 1),
@@ -228,7 +254,8 @@ __device__ __forceinline__ void jbar_cell(const JbarArgs& A, int64_t col, int64_
             }
         }
         if (lane == 0) vp[ii] = vi;
-        __syncthreads();   // this row's values before the next row reads them
+        if (!FAST) __threadfence_block();
+        wave_order();   // this row's values before the next row reads them
         cur = nxt;
         rb = rb1;
         re = re1;
@@ -240,197 +267,327 @@ __device__ __forceinline__ void jbar_cell(const JbarArgs& A, int64_t col, int64_
     }
 }
 
-constexpr int kJWins = 4;   // chunk windows of one cell held in LDS on the pipelined path
+constexpr int kJWins = 4;   // chunk windows of one cell held in LDS
+
+// A hand-over between the waves of the group: LDS writes before it are seen by
+// LDS reads after it (loads from memory stay in flight across it).
+template <int WAVES>
+__device__ __forceinline__ void turn_over() {
+    if (WAVES == 1) return wave_order();
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// The part of a row's exchanges that no value enters.  Entries 2 lane and
+// 2 lane + 1 of up to 128 are the lane's: their weights c (0 past the row's
+// end) and LDS places jl (-1 there), and the slopes of the scan over the lanes'
+// composed maps x -> (1 - c1) ((1 - c0) x + ..) + ..: before each step, before
+// the lane (ap) and of the whole row (aT).
+struct RowMaps {
+    int len;
+    int jl[2];
+    double c[2], a[6], ap, aT;
+};
+__device__ __forceinline__ int row_last(int len) { return len > 64 ? kWave - 1 : len > 32 ? 31 : 15; }
+__device__ __forceinline__ void row_slopes(RowMaps& m) {
+    m.a[0] = (1.0 - m.c[0]) * (1.0 - m.c[1]);
+    m.a[1] = m.a[0] * dpp_move64<0x111, 0xF, 1>(m.a[0]);   // row_shr:1, 2, 4, 8
+    m.a[2] = m.a[1] * dpp_move64<0x112, 0xF, 1>(m.a[1]);
+    m.a[3] = m.a[2] * dpp_move64<0x114, 0xF, 1>(m.a[2]);
+    m.a[4] = m.a[3] * dpp_move64<0x118, 0xF, 1>(m.a[3]);
+    m.a[5] = m.a[4];
+    if (m.len > 32) m.a[5] *= dpp_move64<0x142, 0xA, 1>(m.a[4]);   // uniform; row_bcast:15 into rows 1 and 3
+    double t = m.a[5];
+    if (m.len > 64) t *= dpp_move64<0x143, 0xC, 1>(t);   // uniform; row_bcast:31 into rows 2 and 3
+    m.ap = dpp_move64<0x138, 0xF, 1>(t);                 // wave_shr:1
+    m.aT = lane_of(t, row_last(m.len));
+}
+// The exchanges of one row from target value vi; returns the target's value
+// after them.  The scan gives the target's value before each lane's pair.
+__device__ __forceinline__ double exchange_row(double* s_v, const RowMaps& m, double vi) {
+    double v[2];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) v[s] = m.jl[s] >= 0 ? s_v[m.jl[s]] : 0.0;
+    double b = fma(1.0 - m.c[1], m.c[0] * v[0], m.c[1] * v[1]);
+    b = fma(m.a[0], dpp_move64<0x111, 0xF, 0>(b), b);
+    b = fma(m.a[1], dpp_move64<0x112, 0xF, 0>(b), b);
+    b = fma(m.a[2], dpp_move64<0x114, 0xF, 0>(b), b);
+    b = fma(m.a[3], dpp_move64<0x118, 0xF, 0>(b), b);
+    if (m.len > 32) b = fma(m.a[4], dpp_move64<0x142, 0xA, 0>(b), b);
+    if (m.len > 64) b = fma(m.a[5], dpp_move64<0x143, 0xC, 0>(b), b);
+    const double x0 = fma(m.ap, vi, dpp_move64<0x138, 0xF, 0>(b));
+    const double d0 = m.c[0] * (v[0] - x0), d1 = m.c[1] * (v[1] - (x0 + d0));
+    if (m.jl[0] >= 0) s_v[m.jl[0]] = v[0] - d0;
+    if (m.jl[1] >= 0) s_v[m.jl[1]] = v[1] - d1;
+    return fma(m.aT, vi, lane_of(b, row_last(m.len)));
+}
 
 // The exchanges of one cell whose block fits the LDS area and whose targets
 // lie in at most kJWins chunks (whose windows are all in LDS, cwa[k] for
-// chunk b0 + k, starting at sorted index cst[k]).  A three-stage pipeline
-// over the targets: while target i's exchanges run, the neighbour positions
-// of target i + 1 and the window offsets of target i + 2 are in flight (none
-// of them depends on an exchange); the pair weights of i + 1 are formed after
-// i's exchanges (the distance by the refined reciprocal square root, C_V / r_e
-// formed once: the same weights to within an ulp).
-template <int D>
-__device__ __forceinline__ void jbar_cell_pipelined(const JbarArgs& A, int64_t p0, int64_t p1, double* s_v,
-                                                    const WindowT<D>& blk, const WindowT<D>* cwa,
-                                                    const int64_t (&cst)[kJWins], int nchk,
-                                                    const int (*shl)[kMaxRanges], const int64_t (*shg)[kMaxRanges]) {
-    const int lane = threadIdx.x;
+// chunk b0 + k, starting at sorted index cst[k]; sh[k][r] the shifts of its
+// range r from window offset to sorted index and to block offset).  ii0 is the
+// first target's place in the block.
+// What bounds it: the rows of a cell are a serial chain, and a phase has only
+// two or three cells per SIMD, the slowest of which (a cell of 4 planes where
+// the others have 3) ends it; per row about 190 vector instructions.  So a row
+// costs one scan (two entries per lane composed first) instead of two, all that
+// is uniform sits in scalar registers, and where rows are long the waves of the
+// group take the rows in turn: each prepares its next row (offsets, positions,
+// weights, slopes of the scan) while the others have the turn, and the
+// neighbours' positions come from LDS.  2,097,152 particles, R = 3 d0: 0.135 ->
+// 0.072 ms a phase (one wave, positions from memory: 0.083); 72,000: 0.109 ->
+// 0.028 ms.  Short rows (cubic spline at 2.4 d0, 14 targets a cell; 2-D, 9) keep
+// one wave, whose smaller LDS area lets all cells of a phase run at once:
+// 1,065,547 particles 0.077 -> 0.048 ms a phase (the long shape 0.054), 2-D,
+// 524,288: 0.051 -> 0.039 (three waves 0.045).
+template <int C, bool POS>
+__device__ __forceinline__ void jbar_cell_shared(const JbarArgs& A, int p0, int p1, double* s_v, int ii0,
+                                                 const WindowT<JShape<C>::kD>* cwa, const int (&cst)[kJWins],
+                                                 const int2 (*sh)[kMaxRanges]) {
+    constexpr int D = JShape<C>::kD, kN = JShape<C>::kWaves, kP = JShape<C>::kPos;
+    constexpr int kR = D == 3 ? 9 : 3;
+    constexpr int kRow = 2 * kWave;
+    const int lane = threadIdx.x % kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int64_t n = A.n;
     const double cvr = A.cv / A.re;
-    auto win_of = [&](int64_t i) {
+    auto uni = [](int x) { return __builtin_amdgcn_readfirstlane(x); };
+    // the window of the target whose positions are loaded next
+    int kw = -1, off[kR], wlen = 0;
+    auto window_of = [&](int i) {   // uniform
         int k = 0;
 #pragma unroll
-        for (int q = 1; q < kJWins; ++q)
-            if (q < nchk && i >= cst[q]) k = q;
-        return k;
-    };
-    // row pointers of targets [q0, q0 + 63], lane k holding row_ptr[q0 + k];
-    // queried for increasing targets only
-    int64_t q0 = p0;
-    int64_t rp = A.row_ptr[q0 + lane < p1 ? q0 + lane : p1];
-    auto row_range = [&](int64_t i, int64_t& rb, int64_t& re) {   // uniform i < p1
-        if (i + 1 - q0 >= kJRows) {
-            q0 = i;
-            rp = A.row_ptr[q0 + lane < p1 ? q0 + lane : p1];
-        }
-        rb = __shfl(rp, (int)(i - q0), kWave);
-        re = __shfl(rp, (int)(i + 1 - q0), kWave);
-    };
-    // window offsets of the first kJSlots x 64 entries of a row (-1 past its end)
-    auto load_offsets = [&](int64_t rb, int64_t re, int (&t)[kJSlots]) {
+        for (int q = 1; q < kJWins; ++q) k = i >= cst[q] ? q : k;   // starts past the cell's chunks: p1
+        k = uni(k);
+        if (k != kw) {
+            kw = k;
+            const int nr = uni(cwa[k].nr);
+            wlen = uni(cwa[k].off[nr]);
 #pragma unroll
-        for (int s = 0; s < kJSlots; ++s) {
-            const int64_t e = rb + s * kWave + lane;
-            t[s] = e < re ? (int)A.col16[e] : -1;
-        }
-    };
-    // sorted index and block offset of window offset t of chunk window k:
-    // its range r is the number of range starts at or below t, and each
-    // range's two shifts are looked up in LDS
-    auto decode = [&](int k, int t, int64_t& j, int64_t& jl) {
-        const WindowT<D>& w = cwa[k];
-        t = dcheck(t, w.off[w.nr], kChkWindow);
-        int r = 0;
-#pragma unroll
-        for (int q = 1; q < kMaxRanges; ++q) r += (q < w.nr && t >= w.off[q]) ? 1 : 0;
-        j = t + shg[k][r];
-        jl = t + shl[k][r];
-    };
-    // neighbour positions of the decoded offsets (loads only) ...
-    auto load_positions = [&](int k, const int (&t)[kJSlots], double (&xj)[kJSlots][3], int64_t (&jl)[kJSlots]) {
-#pragma unroll
-        for (int s = 0; s < kJSlots; ++s) {
-            jl[s] = -1;
-#pragma unroll
-            for (int a = 0; a < 3; ++a) xj[s][a] = 0.0;
-            if (t[s] >= 0) {
-                int64_t j;
-                decode(k, t[s], j, jl[s]);
-#pragma unroll
-                for (int a = 0; a < D; ++a) xj[s][a] = A.pos[a * n + j];
+            for (int q = 0; q < kR; ++q) {
+                const int o = uni(cwa[k].off[q]);
+                off[q] = q < nr ? o : INT32_MAX;
             }
         }
     };
-    // ... and the pair weights c = C_V (r_e - |r^_ij|) / r_e from them
-    auto weights = [&](const double (&xi)[3], const double (&xj)[kJSlots][3], const int64_t (&jl)[kJSlots],
-                       double (&c)[kJSlots]) {
+    // entries of the targets' rows, counted from the cell's first: lane k holds
+    // the row start of target q0 + k; asked for in increasing order
+    const int64_t e0 = A.row_ptr[p0];
+    const int ne = uni((int)(A.row_ptr[p1] - e0));
+    if (ne == 0) return;   // uniform over the group
+    const uint16_t* c16 = A.col16 + e0;
+    int q0 = p0;
+    auto row_starts = [&] { return (int)(A.row_ptr[q0 + lane < p1 ? q0 + lane : p1] - e0); };
+    int rp = row_starts();
+    // and the position of target x0 + k
+    int x0 = p0;
+    double px[D];
+    auto target_pos = [&] {
 #pragma unroll
-        for (int s = 0; s < kJSlots; ++s) {
+        for (int a = 0; a < D; ++a) px[a] = A.pos[a * n + (x0 + lane < p1 ? x0 + lane : p1 - 1)];
+        // waited for here, in the rare branch that reloads them: left in flight, every use would wait for all loads
+#pragma unroll
+        for (int a = 0; a < D; ++a) asm volatile("" : "+v"(px[a]));
+    };
+    target_pos();
+
+    // A row on its way.  The loads are issued by every lane (lanes past the
+    // row's end read the cell's last entry and the window's first particle): a
+    // load under a branch could not stay in flight past it.
+    int rb, re, t[2];              // the row whose offsets are under way
+    int frb = 0, flen, fjl[2];     // the row whose positions are under way
+    double xj[2][D];
+    auto start = [&](int i) {   // offsets; rows past the cell's last are empty
+        rb = re = 0;
+        if (i < p1) {   // uniform
+            if (i < q0 || i + 1 - q0 >= kJRows) {   // (back only after a long row)
+                q0 = i;
+                rp = row_starts();
+                asm volatile("" : "+v"(rp));   // waited for here, as the target positions
+            }
+            rb = __builtin_amdgcn_readlane(rp, i - q0);
+            re = __builtin_amdgcn_readlane(rp, i + 1 - q0);
+        }
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const int e = rb + 2 * lane + s;
+            t[s] = c16[(unsigned)(e < ne ? e : ne - 1)];
+        }
+    };
+    auto fetch = [&](int i) {   // positions of the started row, target i's
+        window_of(i < p1 ? i : p1 - 1);
+        frb = rb;
+        flen = re - rb;
+        bool in[2];
+        int tt[2];
+        int2 d[2];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            in[s] = 2 * lane + s < flen;
+            tt[s] = dcheck(in[s] ? t[s] : 0, wlen, kChkWindow);
+            int r = 0;
+#pragma unroll
+            for (int q = 1; q < kR; ++q) r += tt[s] >= off[q] ? 1 : 0;
+            d[s] = sh[kw][r];
+        }
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            // (a window's first particle may lie outside the block: its own place 0 serves as well)
+            fjl[s] = in[s] ? tt[s] + d[s].y : -1;
+            const int jl = in[s] ? tt[s] + d[s].y : 0;
+#pragma unroll
+            for (int a = 0; a < D; ++a)
+                xj[s][a] = POS ? s_v[(1 + a) * kP + jl] : A.pos[a * n + (unsigned)(tt[s] + d[s].x)];
+        }
+    };
+    // the pair weights c = C_V (r_e - |r^_ij|) / r_e of target i's entries
+    auto weights = [&](int i, RowMaps& m) {
+        if (i - x0 >= kWave) {   // uniform
+            x0 = i;
+            target_pos();
+        }
+        double xi[D];
+#pragma unroll
+        for (int a = 0; a < D; ++a) xi[a] = lane_of(px[a], i - x0);
+        m.len = flen;
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
             double r2 = 0.0;
 #pragma unroll
             for (int a = 0; a < D; ++a) {
                 const double d = xj[s][a] - xi[a];
                 r2 += d * d;
             }
-            c[s] = jl[s] >= 0 ? cvr * (A.re - vsqrt(r2)) : 0.0;
+            m.jl[s] = fjl[s];
+            const double c = cvr * (A.re - vsqrt(r2));
+            m.c[s] = m.jl[s] >= 0 ? c : 0.0;
         }
+        row_slopes(m);
     };
-    auto target_pos = [&](int64_t i, double (&xi)[3]) {
-#pragma unroll
-        for (int a = 0; a < 3; ++a) xi[a] = a < D ? A.pos[a * n + i] : 0.0;
-    };
 
-    // prologue: target p0 complete, target p0 + 1's offsets
-    int64_t rb, re, rb1 = 0, re1 = 0;
-    row_range(p0, rb, re);
-    double c[kJSlots], xi[3];
-    int64_t jl[kJSlots];
-    {
-        int t0[kJSlots];
-        double xj[kJSlots][3];
-        load_offsets(rb, re, t0);
-        load_positions(win_of(p0), t0, xj, jl);
-        target_pos(p0, xi);
-        weights(xi, xj, jl, c);
+    RowMaps m;
+    int mrb;   // first entry of m's row
+    // wave w takes targets p0 + w, + kN, ..: its first row complete, the
+    // second's positions and the third's offsets under way
+    start(p0 + wave);
+    fetch(p0 + wave);
+    start(p0 + wave + kN);
+    weights(p0 + wave < p1 ? p0 + wave : p1 - 1, m);
+    mrb = frb;
+    fetch(p0 + wave + kN);
+    start(p0 + wave + 2 * kN);
+    int mine = p0 + wave;
+    bool ahead = false;   // the second part of the preparation is still to do
+    for (int i = p0; i < p1; ++i) {
+        const bool turn = kN == 1 || i == mine;   // uniform per wave
+        if (turn) {
+            const int ii = ii0 + (i - p0);
+            double vi = exchange_row(s_v, m, s_v[ii]);
+            if (m.len > kRow) {   // uniform: more entries than the lanes hold; the rest in place
+                const int len = m.len;
+                for (int eb = kRow; eb < len; eb += kRow) {
+                    rb = mrb + eb;
+                    re = mrb + len;
+#pragma unroll
+                    for (int s = 0; s < 2; ++s) t[s] = c16[(unsigned)(rb + 2 * lane + s < ne ? rb + 2 * lane + s : ne - 1)];
+                    fetch(i);
+                    weights(i, m);
+                    wave_order();
+                    vi = exchange_row(s_v, m, vi);
+                }
+                start(i + kN);   // what was under way, again
+                fetch(i + kN);
+                start(i + 2 * kN);
+            }
+            if (lane == 0) s_v[ii] = vi;
+        }
+        turn_over<kN>();   // this row's values before the next row reads them
+        // the wave's next rows, while the other waves take their turns
+        if (turn) {
+            weights(i + kN < p1 ? i + kN : p1 - 1, m);
+            mrb = frb;
+            mine = i + kN;
+        }
+        if (kN <= 2 ? turn : ahead) {
+            fetch(mine + kN);
+            start(mine + 2 * kN);
+        }
+        ahead = turn;
     }
-    int t1[kJSlots] = {-1, -1};
-    if (p0 + 1 < p1) {
-        row_range(p0 + 1, rb1, re1);
-        load_offsets(rb1, re1, t1);
+}
+
+// A block between memory and LDS, range by range (a range is a run of
+// consecutive particles of one column), the ranges over the waves: the values,
+// and with POS the positions; every load before the first LDS store, as far as
+// ranges of up to 128 go.
+template <int C, bool POS>
+__device__ __forceinline__ void block_load(const WindowT<JShape<C>::kD>& blk, const double* __restrict__ v,
+                                           const double* __restrict__ pos, int64_t n, double* s_v) {
+    constexpr int D = JShape<C>::kD, kN = JShape<C>::kWaves, kP = JShape<C>::kPos;
+    constexpr int kR = D == 3 ? 9 : 3, kRep = (kR + kN - 1) / kN, kA = POS ? 1 + D : 1;
+    const int lane = threadIdx.x % kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    double x[kRep][2][kA];
+#pragma unroll
+    for (int k = 0; k < kRep; ++k) {
+        const int r = wave + k * kN;
+        const int len = r < blk.nr ? blk.off[r + 1] - blk.off[r] : 0;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int t = lane + h * kWave;
+            if (t < len) {
+                const int64_t j = blk.gstart[r] + t;
+                x[k][h][0] = v[j];
+#pragma unroll
+                for (int a = 1; a < kA; ++a) x[k][h][a] = pos[(a - 1) * n + j];
+            }
+        }
     }
-
-    for (int64_t i = p0; i < p1; ++i) {
-        // in flight during i's exchanges: offsets of i + 2, positions of i + 1
-        int64_t rb2 = 0, re2 = 0;
-        int t2[kJSlots] = {-1, -1};
-        if (i + 2 < p1) {   // uniform
-            row_range(i + 2, rb2, re2);
-            load_offsets(rb2, re2, t2);
+#pragma unroll
+    for (int k = 0; k < kRep; ++k) {
+        const int r = wave + k * kN;
+        const int len = r < blk.nr ? blk.off[r + 1] - blk.off[r] : 0;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int t = lane + h * kWave;
+#pragma unroll
+            for (int a = 0; a < kA; ++a)
+                if (t < len) s_v[a * kP + blk.off[r] + t] = x[k][h][a];
         }
-        double xj1[kJSlots][3], xi1[3] = {0.0, 0.0, 0.0};
-        int64_t jl1[kJSlots] = {-1, -1};
-        if (i + 1 < p1) {   // uniform
-            load_positions(win_of(i + 1), t1, xj1, jl1);
-            target_pos(i + 1, xi1);
-        }
-
-        // target i's exchanges
-        const int ki = win_of(i);
-        const int64_t ii = window_offset_of<D>(blk, i);
-        double vi = s_v[ii];
-        for (int64_t e0 = rb; e0 < re; e0 += kWave * kJSlots) {
-            if (e0 != rb) {   // rows longer than kJSlots x 64 entries: the rest in place
-                int tt[kJSlots];
-                double xj[kJSlots][3];
-                load_offsets(e0, re, tt);
-                load_positions(ki, tt, xj, jl);
-                weights(xi, xj, jl, c);
-            }
-            double vj[kJSlots];
+        for (int t = lane + 2 * kWave; t < len; t += kWave) {
+            const int64_t j = blk.gstart[r] + t;
+            s_v[blk.off[r] + t] = v[j];
 #pragma unroll
-            for (int s = 0; s < kJSlots; ++s) vj[s] = jl[s] >= 0 ? s_v[jl[s]] : 0.0;
-            // slot by slot: the scan of the maps x -> (1 - c) x + c v_j gives
-            // v_i before every lane's exchange (padding lanes are the identity)
-#pragma unroll
-            for (int s = 0; s < kJSlots; ++s) {
-                double am = 1.0 - c[s], bm = c[s] * vj[s];
-                affine_scan(am, bm);
-                const double ap = dpp_move64<0x138>(am, 1.0), bp = dpp_move64<0x138>(bm, 0.0);   // wave_shr:1
-                const double xk = fma(ap, vi, bp);
-                if (jl[s] >= 0) s_v[jl[s]] = vj[s] - c[s] * (vj[s] - xk);
-                const double aT = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(am), kWave - 1),
-                                                   __builtin_amdgcn_readlane(__double2loint(am), kWave - 1));
-                const double bT = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(bm), kWave - 1),
-                                                   __builtin_amdgcn_readlane(__double2loint(bm), kWave - 1));
-                vi = fma(aT, vi, bT);
-            }
-        }
-        if (lane == 0) s_v[ii] = vi;
-        __syncthreads();   // this row's values before the next row reads them
-
-        // target i + 1's weights, then shift the pipeline
-        if (i + 1 < p1) {   // uniform
-#pragma unroll
-            for (int a = 0; a < 3; ++a) xi[a] = xi1[a];
-            weights(xi, xj1, jl1, c);
-#pragma unroll
-            for (int s = 0; s < kJSlots; ++s) {
-                jl[s] = jl1[s];
-                t1[s] = t2[s];
-            }
-            rb = rb1;
-            re = re1;
-            rb1 = rb2;
-            re1 = re2;
+            for (int a = 1; a < kA; ++a) s_v[a * kP + blk.off[r] + t] = pos[(a - 1) * n + j];
         }
     }
 }
 
-// One cell of phase `phase` per work-group (one wave).
-template <int D>
-__global__ __launch_bounds__(kWave) void k_jbar_phase(JbarArgs A, int phase, int64_t uy, int64_t uz) {
-    __shared__ double s_v[kJCap];
+template <int C>
+__device__ __forceinline__ void block_store(const WindowT<JShape<C>::kD>& blk, const double* s_v, double* v) {
+    const int lane = threadIdx.x % kWave;
+    for (int r = threadIdx.x / kWave; r < blk.nr; r += JShape<C>::kWaves) {
+        const int len = blk.off[r + 1] - blk.off[r];
+        for (int t = lane; t < len; t += kWave) v[blk.gstart[r] + t] = s_v[blk.off[r] + t];
+    }
+}
+
+// One cell of phase `phase` per work-group.
+template <int C>
+__global__ __launch_bounds__(kWave* JShape<C>::kWaves) void k_jbar_phase(JbarArgs A, int phase, uint32_t uy, uint32_t uz) {
+    constexpr int D = JShape<C>::kD;
+    __shared__ double s_v[JShape<C>::kArea];   // the block's values, and its positions
     __shared__ WindowT<D> blk;     // the 3^d cells around the cell
     __shared__ WindowT<D> cw[2];   // windows of the chunks of the current and the next target
-    __shared__ WindowT<D> cwa[kJWins];   // windows of the cell's chunks (pipelined path)
-    __shared__ int s_shl[kJWins][kMaxRanges];       // their offset -> block offset shifts
-    __shared__ int64_t s_shg[kJWins][kMaxRanges];   // their offset -> sorted index shifts
-    const int lane = threadIdx.x;
+    __shared__ WindowT<D> cwa[kJWins];          // windows of the cell's chunks
+    __shared__ int2 s_sh[kJWins][kMaxRanges];   // per range: shifts to the sorted index and to the block offset
+    const int lane = threadIdx.x % kWave;
+    const bool first = threadIdx.x < kWave;   // the wave that fills the tables
     const Grid& g = A.g;
     // the cell: z (last axis) fastest over the phase's cells
-    int64_t b = blockIdx.x;
-    int64_t cx, cy = 0, cz;
+    uint32_t b = blockIdx.x;
+    int cx, cy = 0, cz;
     if (D == 3) {
         cz = phase / 9 + 3 * (b % uz);
         b /= uz;
@@ -442,50 +599,70 @@ __global__ __launch_bounds__(kWave) void k_jbar_phase(JbarArgs A, int phase, int
         b /= uz;
         cx = phase % 3 + 3 * b;
     }
-    const int64_t col = D == 3 ? cx * g.nc[1] + cy : cx;
+    const int64_t col = D == 3 ? (int64_t)cx * g.nc[1] + cy : cx;
     const int64_t key = col_key<D>(g, col, cz);
     const int64_t p0 = A.cs[key], p1 = A.cs[key + 1];
+    int64_t b0 = A.chunk_off[col];
+    const int64_t bend = A.chunk_off[col + 1];
     if (p0 == p1) return;   // uniform over the work-group
-    chunk_window_wave<D>(g, A.cs, make_int4((int)col, (int)cz, (int)cz, 0), blk);
+    // the chunks holding the cell's targets: the column's chunk starts over the
+    // lanes, b0 moved up until lane 0 has the chunk of the first target or the
+    // rest of the column is in the lanes
+    auto starts = [&] { return b0 + lane < bend ? A.cstart[b0 + lane] : INT32_MAX; };
+    int st = starts();
+    int k0 = __popcll(__ballot(st <= p0)) - 1;
+    while (k0 + kJWins >= kWave - 1 && b0 + kWave < bend) {   // uniform; rare (columns of over 59 chunks)
+        b0 += k0;
+        st = starts();
+        k0 = __popcll(__ballot(st <= p0)) - 1;
+        if (k0 == 0) break;
+    }
+    const int nchk = __popcll(__ballot(st < p1)) - k0;
+    b0 += k0;
+    if (first) chunk_window_wave<D>(g, A.cs, make_int4((int)col, cz, cz, 0), blk);
     __syncthreads();
     const int W = blk.off[blk.nr];
     if (W <= kJCap) {   // uniform
-        for (int t = lane; t < W; t += kWave) s_v[t] = A.v[window_global<D>(blk, t)];
-        // the chunks holding the cell's targets
-        int64_t b0 = A.chunk_off[col];
-        while (A.cstart[b0 + 1] <= p0) ++b0;
-        int64_t bl = b0;
-        while (A.cstart[bl + 1] < p1) ++bl;
-        const int nchk = (int)(bl - b0 + 1);
         if (nchk <= kJWins) {   // uniform
-            int64_t cst[kJWins];
+            int cst[kJWins];
 #pragma unroll
             for (int k = 0; k < kJWins; ++k) {
-                cst[k] = k < nchk ? (int64_t)A.cstart[b0 + k] : p1;
-                if (k < nchk) {
+                cst[k] = k < nchk ? __builtin_amdgcn_readlane(st, k0 + k) : (int)p1;
+                if (first && k < nchk) {
                     if (A.cwin) window_load<D>(A.cwin, (uint32_t)(b0 + k), cwa[k]);
                     else chunk_window_wave<D>(g, A.cs, A.cinfo[b0 + k], cwa[k]);
                 }
             }
+            const bool pos = W <= JShape<C>::kPos;   // uniform
+            if constexpr (JShape<C>::kPos > 0) {
+                if (pos) block_load<C, true>(blk, A.v, A.pos, A.n, s_v);
+            }
+            if (!pos) block_load<C, false>(blk, A.v, A.pos, A.n, s_v);
             __syncthreads();
             // per window and range: window offset -> sorted index and -> block
             // offset (the chunk windows and the block list the same columns
             // in the same order)
-            if (lane < nchk * kMaxRanges) {
+            if (first && lane < nchk * kMaxRanges) {
                 const int k = lane / kMaxRanges, r = lane % kMaxRanges;
                 const WindowT<D>& w = cwa[k];
                 const int64_t g0 = r < w.nr ? w.gstart[r] - w.off[r] : 0;
-                s_shg[k][r] = g0;
-                s_shl[k][r] = r < w.nr ? (int)(g0 - blk.gstart[r]) + blk.off[r] : 0;
+                s_sh[k][r] = make_int2((int)g0, r < w.nr ? (int)(g0 - blk.gstart[r]) + blk.off[r] : 0);
             }
             __syncthreads();
-            jbar_cell_pipelined<D>(A, p0, p1, s_v, blk, cwa, cst, nchk, s_shl, s_shg);
+            auto uni = [](int64_t x) { return __builtin_amdgcn_readfirstlane((int)x); };
+            const int ii0 = uni(window_offset_of<D>(blk, p0));
+            if constexpr (JShape<C>::kPos > 0) {
+                if (pos) jbar_cell_shared<C, true>(A, uni(p0), uni(p1), s_v, ii0, cwa, cst, s_sh);
+            }
+            if (!pos) jbar_cell_shared<C, false>(A, uni(p0), uni(p1), s_v, ii0, cwa, cst, s_sh);
         } else {
-            jbar_cell<D, true>(A, col, p0, p1, s_v, blk, cw);
+            block_load<C, false>(blk, A.v, A.pos, A.n, s_v);
+            __syncthreads();
+            if (first) jbar_cell<D, true>(A, col, p0, p1, s_v, blk, cw);
         }
         __syncthreads();
-        for (int t = lane; t < W; t += kWave) A.v[window_global<D>(blk, t)] = s_v[t];
-    } else {
+        block_store<C>(blk, s_v, A.v);
+    } else if (first) {
         jbar_cell<D, false>(A, col, p0, p1, A.v, blk, cw);
     }
 }
@@ -552,8 +729,13 @@ extern "C" int vct_jbar_smooth(const vct_nlist* nl, const double* pos_sorted, co
         const int64_t uz = count(nz, dim == 3 ? ph / 9 : ph / 3);
         const int64_t cells = ux * uy * uz;
         if (cells == 0) continue;
-        if (dim == 3) VCT_LAUNCH("k_jbar_phase", k_jbar_phase<3>, dim3((unsigned)cells), dim3(kWave), 0, s, a, ph, uy, uz);
-        else VCT_LAUNCH("k_jbar_phase", k_jbar_phase<2>, dim3((unsigned)cells), dim3(kWave), 0, s, a, ph, uy, uz);
+        const dim3 gr((unsigned)cells);
+        const uint32_t vy = (uint32_t)uy, vz = (uint32_t)uz;
+        if (dim == 2) VCT_LAUNCH("k_jbar_phase", k_jbar_phase<kJ2>, gr, dim3(kWave), 0, s, a, ph, vy, vz);
+        else if (mean_row(nl) <= short_row<3>())
+            VCT_LAUNCH("k_jbar_phase", k_jbar_phase<kJShort3>, gr, dim3(kWave), 0, s, a, ph, vy, vz);
+        else
+            VCT_LAUNCH("k_jbar_phase", k_jbar_phase<kJLong3>, gr, dim3(kWave * JShape<kJLong3>::kWaves), 0, s, a, ph, vy, vz);
         VCT_LAUNCH_CHECK();
     }
     VCT_LAUNCH("k_jbar_ratio", k_jbar_ratio, dim3(nb), dim3(256), 0, s, n, J, v, jbar);

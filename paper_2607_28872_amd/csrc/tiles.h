@@ -122,8 +122,9 @@ __device__ __forceinline__ void chunk_window_wave(const Grid& g, const int64_t* 
     constexpr int ncand = D == 3 ? 9 : 3;
     int64_t x, y = 0, colid;
     if (D == 3) {
-        x = info.x / g.nc[1] + lane / 3 - 1;
-        y = info.x % g.nc[1] + lane % 3 - 1;
+        const int nc1 = (int)g.nc[1];   // columns are numbered in 32 bits
+        x = info.x / nc1 + lane / 3 - 1;
+        y = info.x % nc1 + lane % 3 - 1;
         colid = x * g.nc[1] + y;
     } else {
         x = info.x + lane - 1;
