@@ -485,7 +485,7 @@ __global__ __launch_bounds__(kAThreads, 2) void k_r2_prep(AdjArgs A, double* __r
 //
 // The accumulation is exact and order-free.  With a per-column bound M on the
 // terms (below) and d_max the longest row of the set, every term w is scaled
-// by 2^k, k = 62 - ilogb(M) - bitlen(d_max), rounded to the integer
+// by 2^k, k = 62 - ilogb(M) - bitlen(d_max) (60 - .. in R2), rounded to the integer
 // X = rint(w 2^k), and added by a 64-bit integer atomic.  |w 2^k| is below
 // 2^(63 - bitlen(d_max)) and the accumulator of particle j receives at most one
 // term per neighbour of j (the neighbour relation is symmetric), so its sum
@@ -684,7 +684,11 @@ __device__ __forceinline__ void push_column(const AdjArgs& A, double* __restrict
     const double Mb = vmax * 1.0625 * bmax;   // the factor covers |r~| rounded above 1
     // terms reaching one accumulator: at most one per neighbour of its particle
     const double nterm = (double)wave_max(wide[kWideMaxDeg + tid % kWave]);
-    const int k = (Mb > 0.0 && Mb <= 1.7976931348623157e308) ? 62 - ilogb(Mb) - (ilogb(fmax(nterm, 1.0)) + 1) : 0;
+    // R2: two bits fewer, the scale its results have always been rounded at
+    // (dtheta is a sum over all particles that cancels to as little as 1e-5 of
+    // its terms, so another scale shows in it at parts in 1e9)
+    const int top = OP::kR2 ? 60 : 62;
+    const int k = (Mb > 0.0 && Mb <= 1.7976931348623157e308) ? top - ilogb(Mb) - (ilogb(fmax(nterm, 1.0)) + 1) : 0;
 
     const int lane = tid % kALanes;
     const int slot = tid / kALanes;
