@@ -77,31 +77,24 @@ __device__ __forceinline__ double sym_at(const double (&S)[Dims<D>::nL], int a, 
 
 // ------------------------------------------------------------------ kernel 1: sweeps
 
-// Launch shape (overridable at build time for tuning).  A work-group is one
-// chunk with kMLanes lanes per particle; its LDS (window records plus the L
-// and B sums of the chunk, about 53 KB at 1400 records) and its registers (at
-// most 168 VGPRs) let three work-groups share a CU, so the staging of one
-// overlaps the sweeps of the others.  Windows larger than kMWin (about 1% at
-// the 8.4M-particle sigma set) read their records from global memory.
-#ifndef VCT_MLANES
-#define VCT_MLANES 4
-#endif
-#ifndef VCT_MWIN
-#define VCT_MWIN 1400
-#endif
-#ifndef VCT_SWEEP_WAVES
-#define VCT_SWEEP_WAVES 3
-#endif
-#ifndef VCT_MSLOTS
-#define VCT_MSLOTS 28
-#endif
-#ifndef VCT_SWEEP2_AHEAD
-#define VCT_SWEEP2_AHEAD true
-#endif
-constexpr int kMLanes = VCT_MLANES;           // lanes per particle
-constexpr int kMThreads = kChunk * kMLanes;   // one chunk per work-group
-constexpr int kMWin = VCT_MWIN;               // LDS window capacity (records)
-constexpr int kMSlots = VCT_MSLOTS;           // row entries per lane held in registers
+// Launch shapes by class of the mean row length (the row classes of tiles.h):
+// lanes per particle, row entries a lane holds in registers, LDS window
+// (records) and waves per SIMD.  A work-group is one chunk.  Long rows: its LDS
+// (window records plus the L and B sums of the chunk, about 53 KB at 1400
+// records) and its registers (at most 168 VGPRs) let three work-groups share a
+// CU, so the staging of one overlaps the sweeps of the others; windows beyond
+// (about 1% at the 8.4M-particle sigma set) read their records from memory.
+// Short rows: the long shape runs 28 slots per lane for rows that fill 7 (2-D,
+// about 26 entries) or 15 (cubic spline in 3-D, 57), and its window keeps the
+// work-groups of a CU at three where a 2-D window has about 400 records.  2-D,
+// 1,048,576 particles: 0.208 -> 0.119 ms (two lanes of 14 slots 0.116 there but
+// 0.029 against 0.027 on 22,176 particles); cubic spline in 3-D, 2,097,152
+// particles: 0.93 -> 0.88 ms (a window of 1,000 and four groups 0.94, two lanes
+// 1.16).
+template <int C> struct MomShape;
+template <> struct MomShape<kRowsLong> { static constexpr int lanes = 4, slots = 28, win = 1400, waves = 3; };
+template <> struct MomShape<kRowsShort3> { static constexpr int lanes = 4, slots = 16, win = 1184, waves = 3; };
+template <> struct MomShape<kRowsShort2> { static constexpr int lanes = 4, slots = 8, win = 448, waves = 4; };
 
 struct SweepArgs {
     int64_t n;
@@ -121,15 +114,17 @@ struct SweepArgs {
 };
 
 // One chunk per work-group: the window's positions and volumes are staged in
-// LDS (x, y, z, V per record), kMLanes lanes per particle hold their share of
+// LDS (x, y, z, V per record), kLanes lanes per particle hold their share of
 // the row's window offsets in registers and read the records from LDS one
 // entry ahead of the arithmetic, for both sweeps; the sums are reduced across
 // the group and written through LDS with unit stride.
-template <int D, int KERNEL>
-__global__ __launch_bounds__(kMThreads, VCT_SWEEP_WAVES) void k_moment_sweeps(SweepArgs A) {
+template <int D, int KERNEL, int C>
+__global__ __launch_bounds__(kChunk* MomShape<C>::lanes, MomShape<C>::waves) void k_moment_sweeps(SweepArgs A) {
     using Dm = Dims<D>;
     using ML = MomLayout<D>;
-    __shared__ double4 sd[kMWin];
+    constexpr int kLanes = MomShape<C>::lanes, kSlots = MomShape<C>::slots, kWin = MomShape<C>::win;
+    constexpr int kThreads = kChunk * kLanes;
+    __shared__ double4 sd[kWin];
     __shared__ double sLB[ML::oC * kChunk];   // L and B of every particle, kept out of registers in sweep 2
     __shared__ WindowT<D> w;
     uint32_t b;
@@ -140,8 +135,8 @@ __global__ __launch_bounds__(kMThreads, VCT_SWEEP_WAVES) void k_moment_sweeps(Sw
         if (A.cwin) window_load<D>(A.cwin, b, w);
         else chunk_window_wave<D>(A.g, A.cs, A.cinfo[b], w);
     }
-    const int lane = threadIdx.x % kMLanes;
-    const int pl = threadIdx.x / kMLanes;
+    const int lane = threadIdx.x % kLanes;
+    const int pl = threadIdx.x / kLanes;
     const int64_t i = p0 + pl;
     const bool valid = i < p1;
     const int64_t ii = valid ? i : p0;
@@ -150,50 +145,17 @@ __global__ __launch_bounds__(kMThreads, VCT_SWEEP_WAVES) void k_moment_sweeps(Sw
     for (int a = 0; a < 3; ++a) xi[a] = a < D ? A.pos[a * n + ii] : 0.0;
     const double Vi = A.vol[ii];
     const int64_t rb = valid ? A.row_ptr[ii] : 0, re = valid ? A.row_ptr[ii + 1] : 0;
-    uint32_t cpk[(kMSlots + 1) / 2];
-    int nslot = 0;
-    {
-        const uint32_t first = re > rb ? (uint32_t)A.col16[rb] : 0u;
-        const int len = (int)(re - rb);        // 32-bit row-local indices: one base address,
-        const uint16_t* crow = A.col16 + rb + lane;   // immediate offsets per slot
-#pragma unroll
-        for (int s = 0; s < kMSlots; ++s) {
-            const bool in = lane + kMLanes * s < len;
-            const uint32_t c = in ? (uint32_t)crow[kMLanes * s] : first;
-            nslot += in ? 1 : 0;
-            if (s % 2 == 0) cpk[s / 2] = c;
-            else cpk[s / 2] |= c << 16;
-        }
-    }
+    const RowSlots<kLanes, kSlots> rs(A.col16, rb, re, lane);
     __syncthreads();
     const int W = __builtin_amdgcn_readfirstlane(w.off[w.nr]);
-    auto cols = [&](int s) -> int { return dcheck((int)((cpk[s / 2] >> (16 * (s % 2))) & 0xffffu), W, kChkWindow); };
-    const bool in_lds = W <= kMWin;
-    if (in_lds) {
-        // every load of a thread is issued before its first LDS store
-        constexpr int kRep = (kMWin + kMThreads - 1) / kMThreads;
-        double4 q[kRep];
-#pragma unroll
-        for (int k = 0; k < kRep; ++k) {
-            const int t = threadIdx.x + k * kMThreads;
-            if (t < W) {   // lanes past the window load nothing (whole waves skip)
-                const int64_t j = window_global<D>(w, t);
-                q[k] = make_double4(A.pos[j], A.pos[n + j], D == 3 ? A.pos[2 * n + j] : 0.0, A.vol[j]);
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < kRep; ++k) {
-            const int t = threadIdx.x + k * kMThreads;
-            if (t < W) sd[t] = q[k];
-        }
-    }
-    __syncthreads();
-    auto fetch = [&](int t) -> double4 {
-        t = dcheck(t, W, kChkWindow);
-        if (in_lds) return sd[t];
+    const bool in_lds = W <= kWin;
+    auto record = [&](int t) {
         const int64_t j = window_global<D>(w, t);
         return make_double4(A.pos[j], A.pos[n + j], D == 3 ? A.pos[2 * n + j] : 0.0, A.vol[j]);
     };
+    if (in_lds) stage_window<kWin, kThreads>(W, record, [&](int t, const double4& q) { sd[t] = q; });
+    __syncthreads();
+    auto fetch = [&](int t) -> double4 { return in_lds ? sd[t] : record(t); };
     // The offsets r = r^_j - r^_i and their pair products q, unscaled (q
     // holds the squares first, so |r|^2 is their sum): every sum below is a
     // homogeneous polynomial in r, so the scaling by 1/R of the moment
@@ -211,30 +173,7 @@ __global__ __launch_bounds__(kMThreads, VCT_SWEEP_WAVES) void k_moment_sweeps(Sw
 #pragma unroll
         for (int a = 1; a < D; ++a) q2 += qv[a];
     };
-    // visits every row entry: the register slots (records read one ahead
-    // when the window is in LDS), then the rest of a long row
-    auto sweep = [&](auto&& body, auto ahead) {
-        if (in_lds && decltype(ahead)::value) {
-            double4 qn = sd[cols(0)];
-#pragma unroll
-            for (int s = 0; s < kMSlots; ++s) {
-                const double4 q = qn;
-                if (s + 1 < kMSlots) qn = sd[cols(s + 1)];
-                __builtin_amdgcn_sched_barrier(0);
-                if (s < nslot) body(q);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        } else if (in_lds) {
-#pragma unroll
-            for (int s = 0; s < kMSlots; ++s)
-                if (s < nslot) body(sd[cols(s)]);
-        } else {
-#pragma unroll 1
-            for (int s = 0; s < kMSlots; ++s)
-                if (s < nslot) body(fetch(cols(s)));
-        }
-        for (int64_t e = rb + lane + (int64_t)kMLanes * kMSlots; e < re; e += kMLanes) body(fetch(A.col16[e]));
-    };
+    auto sweep = [&](auto&& body) { sweep_row(rs, A.col16, W, in_lds, fetch, body); };
     int fl = 0;
     if (valid && re - rb < D + Dm::m) fl |= VCT_FLAG_FEW;
     bool fin = isfinite(Vi);
@@ -264,13 +203,13 @@ __global__ __launch_bounds__(kMThreads, VCT_SWEEP_WAVES) void k_moment_sweeps(Sw
 #pragma unroll
         for (int t = 0; t < Dm::n3; ++t)
             B[t] += wr[mono_comp<D, 3>(t, 0)] * qv[sym_index<D>(mono_comp<D, 3>(t, 1), mono_comp<D, 3>(t, 2))];
-    }, std::true_type{});
+    });
     if (q2min == 0.0) fl |= VCT_FLAG_DUPLICATE;
     const double invR2 = A.invR * A.invR;
 #pragma unroll
-    for (int p = 0; p < Dm::nL; ++p) Am[p] = group_sum(Am[p], kMLanes) * invR2;
+    for (int p = 0; p < Dm::nL; ++p) Am[p] = group_sum(Am[p], kLanes) * invR2;
 #pragma unroll
-    for (int t = 0; t < Dm::n3; ++t) B[t] = group_sum(B[t], kMLanes) * (invR2 * A.invR);
+    for (int t = 0; t < Dm::n3; ++t) B[t] = group_sum(B[t], kLanes) * (invR2 * A.invR);
     // a non-finite neighbour position or volume makes some sum non-finite
     // (every weight is positive), which is cheaper to test once than per pair
     {
@@ -281,7 +220,7 @@ __global__ __launch_bounds__(kMThreads, VCT_SWEEP_WAVES) void k_moment_sweeps(Sw
         for (int t = 0; t < Dm::n3; ++t) sf = sf && isfinite(B[t]);
         if (!sf) fl |= VCT_FLAG_NONFINITE;
     }
-    for (int m_ = kMLanes >> 1; m_ >= 1; m_ >>= 1) fl |= __shfl_xor(fl, m_, kWave);
+    for (int m_ = kLanes >> 1; m_ >= 1; m_ >>= 1) fl |= __shfl_xor(fl, m_, kWave);
 
     double L[Dm::nL];
     if (!sym_inverse<D>(Am, L)) fl |= VCT_FLAG_SINGULAR_A;
@@ -290,7 +229,7 @@ __global__ __launch_bounds__(kMThreads, VCT_SWEEP_WAVES) void k_moment_sweeps(Sw
     for (int p = 0; p < Dm::nL; ++p) L2[p] = (pair_a<D>(p) == pair_b<D>(p) ? 1.0 : 2.0) * L[p];
 #pragma unroll
     for (int v = 0; v < ML::oC; ++v)
-        if (v % kMLanes == lane) sLB[v * kChunk + pl] = v < ML::oB ? L[v] : B[v - ML::oB];
+        if (v % kLanes == lane) sLB[v * kChunk + pl] = v < ML::oB ? L[v] : B[v - ML::oB];
 
     // sweep 2: C (3rd order) and E (4th order), weights V F~ (skipped for a
     // flagged particle: its state is NaN anyway)
@@ -318,27 +257,27 @@ __global__ __launch_bounds__(kMThreads, VCT_SWEEP_WAVES) void k_moment_sweeps(Sw
         for (int t = 0; t < Dm::n4; ++t)
             E[t] += wq[sym_index<D>(mono_comp<D, 4>(t, 0), mono_comp<D, 4>(t, 1))] *
                     qv[sym_index<D>(mono_comp<D, 4>(t, 2), mono_comp<D, 4>(t, 3))];
-    }, std::integral_constant<bool, VCT_SWEEP2_AHEAD>{});
+    });
 #pragma unroll
-    for (int t = 0; t < Dm::n3; ++t) Cm[t] = group_sum(Cm[t], kMLanes) * A.invR;
+    for (int t = 0; t < Dm::n3; ++t) Cm[t] = group_sum(Cm[t], kLanes) * A.invR;
 #pragma unroll
-    for (int t = 0; t < Dm::n4; ++t) E[t] = group_sum(E[t], kMLanes) * invR2;
+    for (int t = 0; t < Dm::n4; ++t) E[t] = group_sum(E[t], kLanes) * invR2;
 
     // the sums through LDS (the window is no longer needed), then unit-stride
     // stores: thread t writes entries (v, q) with q = t % kChunk
-    static_assert(ML::total * kChunk * 8 <= kMWin * 32, "sum staging must fit the window buffer");
+    static_assert(ML::total * kChunk * 8 <= kWin * 32, "sum staging must fit the window buffer");
     double* ssum = reinterpret_cast<double*>(sd);
     __syncthreads();
 #pragma unroll
     for (int v = ML::oC; v < ML::total; ++v) {
-        if (v % kMLanes != lane) continue;
+        if (v % kLanes != lane) continue;
         ssum[(v - ML::oC) * kChunk + pl] = v < ML::oE ? Cm[v - ML::oC] : E[v - ML::oE];
     }
     __syncthreads();
     {
         const int q = threadIdx.x % kChunk;
         if (p0 + q < p1)
-            for (int v = threadIdx.x / kChunk; v < ML::total; v += kMThreads / kChunk)
+            for (int v = threadIdx.x / kChunk; v < ML::total; v += kThreads / kChunk)
                 A.mom[(int64_t)v * n + p0 + q] = v < ML::oC ? sLB[v * kChunk + q] : ssum[(v - ML::oC) * kChunk + q];
     }
     if (valid && lane == 0) A.mflags[ii] = (uint8_t)fl;
@@ -605,7 +544,13 @@ static int launch_moments(const vct_nlist* nl, const Grid& g, const double* pos,
     a.cwin = nl->chunk_win;
     a.nchunks = nl->chunk_off + ncols; a.mom = mom; a.mflags = mflags;
     const int64_t cap = ncols + n / kChunk + 1;
-    VCT_LAUNCH("k_moment_sweeps", (k_moment_sweeps<D, KERNEL>), dim3((unsigned)cap), dim3(kMThreads), 0, s, a);
+    constexpr int S = D == 2 ? kRowsShort2 : kRowsShort3;
+    if (mean_row(nl) <= short_row<D>())
+        VCT_LAUNCH("k_moment_sweeps", (k_moment_sweeps<D, KERNEL, S>), dim3((unsigned)cap),
+                   dim3(kChunk * MomShape<S>::lanes), 0, s, a);
+    else
+        VCT_LAUNCH("k_moment_sweeps", (k_moment_sweeps<D, KERNEL, kRowsLong>), dim3((unsigned)cap),
+                   dim3(kChunk * MomShape<kRowsLong>::lanes), 0, s, a);
     VCT_LAUNCH_CHECK();
     return launch_solve<D>(n, pos, mom, mflags, invR, mp, o1, o2, flags, nflag, s);
 }
