@@ -377,32 +377,40 @@ __device__ __forceinline__ bool within_exact(double dx, double dy, double dz, do
     return d2 < R2;
 }
 
-// d2 - lim for an FP32 window record q (offset from the chunk origin, with
-// |q|^2 in q.w) and the particle's FP32 offset f, expanded as
-// |q|^2 + (|f|^2 - lim) - 2 q . f: c = |f|^2 - lim and m = -2 f per
-// particle, so a candidate costs one add and three multiply-adds.  The
-// expansion's rounding grows with the offsets' size M instead of with d2
-// (bound below, where the band is set).
-__device__ __forceinline__ float d2_minus(const float4& q, float m0, float m1, float m2, float c) {
-    return fmaf(q.x, m0, fmaf(q.y, m1, fmaf(q.z, m2, q.w + c)));
-}
-
 constexpr int kNbWaves = 4;                    // waves per work-group
-constexpr int kNbThreads = kNbWaves * kWave;   // one chunk per work-group, lane = particle
+constexpr int kNbThreads = kNbWaves * kWave;   // one chunk per work-group
 constexpr int kNbSeg = 1536;                   // window records per LDS segment (24 KB)
+constexpr int kNbBlock = 128;                  // candidates of a matrix block: four words
+constexpr int kNbRep = 2;                      // records a thread stages at a time
+constexpr float kNbFar = 3e38f;                // |q|^2 of a record that is nobody's neighbour
+constexpr int kNbStride = kNbSeg + 16;         // floats between the components (16 mod 64 banks)
 constexpr int kNbWords = kNbSeg / 32;          // 32-candidate words per segment
 constexpr int kStage = 128;                    // 16-bit staging slots per particle in the workspace
 constexpr int kBmWords = kStage / 2;           // hit words per particle slot: windows up to 2048 candidates
 
-// One chunk per work-group; every wave holds the whole chunk, lane = particle,
-// and takes a quarter of the window's candidates.  The window is staged in
-// LDS segment by segment as FP32 offsets from the chunk's first particle; all
-// lanes of a wave test the same candidate (one broadcast LDS read), so a test
-// costs a few VALU instructions.  A candidate whose FP32 squared distance is
-// inside or outside R^2 by more than a bound on its rounding error is decided
-// by it; the few near the support edge are re-tested with the exact FP64
-// predicate on the stored positions.  Hits are collected as one bit per
-// candidate (32-candidate words).
+// One chunk per work-group, a wave for 16 of its particles.  The window is staged
+// in LDS segment by segment as FP32 offsets from the chunk's middle particle in
+// units of R, and the squared distances come from the matrix cores: with
+// m = -2 f and c = |f|^2 - lim for a particle at offset f,
+//     d2 - lim = q_x m_x + q_y m_y + q_z m_z + |q|^2 * 1 + c
+// is one 16 x 16 x 4 product of 16 records (x, y, z, |q|^2) and 16 columns
+// (m_x, m_y, m_z, 1) on top of c.  A candidate whose FP32 value is inside or
+// outside by more than a bound on its rounding error is decided by its sign; the
+// few near the support edge are re-tested with the exact FP64 predicate on the
+// stored positions.  Hits are collected as one bit per candidate (32-candidate
+// words).  The records of a block of 128 candidates are stored so that row i of
+// product u holds candidate 32 (i / 4) + 4 u + i % 4: the four results of a
+// lane, over the block's eight products, are then the 32 bits of one word, and
+// no lane needs another's.
+//
+// What bounds it: the vector instructions (61% of the busy time at 8,388,608
+// particles with five waves on a SIMD; the matrix cores 29%), then the waits of
+// the staging.  A candidate costs a lane one shift and half a minimum, next to
+// six operations and a 16-byte LDS read per candidate when the lanes test one
+// candidate each; two records of a thread staged at a time keep the registers at
+// six work-groups per CU (six at a time: 125 registers, 2.1 ms).  8,388,608
+// particles: 2.48 -> 2.01 ms; 1,049,800 in 3-D 0.318 -> 0.257; cubic spline,
+// 2,097,152: 0.474 -> 0.355; 2-D, 1,048,576: 0.129 -> 0.092.
 // MODE 0 writes the counts.  MODE 1 writes the columns at row_ptr (sorted
 // indices and/or 16-bit window offsets): the words go to LDS ([word][particle])
 // and a per-particle prefix over the waves' hit counts places every wave's
@@ -414,25 +422,28 @@ constexpr int kBmWords = kStage / 2;           // hit words per particle slot: w
 // counts k_nb_wide adds.  head->overflow flags windows beyond 65535.
 template <int D, int MODE>
 __device__ __forceinline__ void nb_chunk(uint32_t b, int64_t n, const double* __restrict__ pos, const Grid& g, double R2,
-                                         const int64_t* __restrict__ cs, const int32_t* __restrict__ cstart,
+                                         double sc, const int64_t* __restrict__ cs, const int32_t* __restrict__ cstart,
                                          const int4* __restrict__ cinfo, int32_t* __restrict__ counts,
                                          const int64_t* __restrict__ row_ptr, int32_t* __restrict__ col,
                                          uint16_t* __restrict__ col16, SearchHead* __restrict__ head,
                                          int32_t* __restrict__ wide, int32_t* __restrict__ win_tab) {
     constexpr bool FILL = MODE == 1, STAGE = MODE == 2;
-    static_assert(kChunk == kWave, "lane = particle");
-    static_assert(kNbSeg % 32 == 0, "segments hold whole words");
-    __shared__ float4 win[kNbSeg];
+    static_assert(kChunk == kWave && kChunk == 16 * kNbWaves, "16 particles to a wave");
+    static_assert(kNbSeg % kNbBlock == 0, "segments hold whole blocks");
+    __shared__ float win[4][kNbStride];
     __shared__ uint32_t bm[FILL ? kNbWords : 1][kChunk];
     __shared__ int32_t wcnt[kNbWaves][kChunk];
     __shared__ float wmax[kNbWaves];
     __shared__ WindowT<D> w;
     const int64_t p0 = cstart[b], p1 = cstart[b + 1];
     const int np = (int)(p1 - p0);
-    const int wv = threadIdx.x / kWave, pl = threadIdx.x % kWave;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), pl = threadIdx.x % kWave;
     if (wv == 0) chunk_window_wave<D>(g, cs, cinfo[b], w);
-    const int64_t i = p0 + pl;
-    const bool valid = pl < np;
+    // the lane's column of the products: one of the wave's 16 particles, and
+    // the component (of records and columns) or word (of results) it holds
+    const int cpl = 16 * wv + pl % 16, quad = pl / 16;
+    const int64_t i = p0 + cpl;
+    const bool valid = cpl < np;
     const int64_t ii = valid ? i : p0;
     // the chunk origin: its middle particle, which keeps the offsets (and the
     // rounding of the expanded distance) small
@@ -440,20 +451,25 @@ __device__ __forceinline__ void nb_chunk(uint32_t b, int64_t n, const double* __
     const double o0 = pos[pm], o1 = pos[n + pm], o2 = (D == 3) ? pos[2 * n + pm] : 0.0;
     const double xi0 = pos[ii], xi1 = pos[n + ii], xi2 = (D == 3) ? pos[2 * n + ii] : 0.0;
     // offsets from the chunk origin in FP32 (the same rounding as the records)
-    const float f0 = (float)(xi0 - o0), f1 = (float)(xi1 - o1), f2 = (float)(xi2 - o2);
-    const float fmax_own = fmaxf(fabsf(f0), fmaxf(fabsf(f1), fabsf(f2)));
-    const float m0 = -2.0f * f0, m1 = -2.0f * f1, m2 = -2.0f * f2;   // exact
+    const float f0 = (float)((xi0 - o0) * sc), f1 = (float)((xi1 - o1) * sc), f2 = (float)((xi2 - o2) * sc);
     const float ff = fmaf(f2, f2, fmaf(f1, f1, f0 * f0));
-    const int64_t rlo = FILL ? row_ptr[ii] : 0, rlen = FILL ? row_ptr[ii + 1] - rlo : 0;
+    const float colv = quad == 0 ? -2.0f * f0 : quad == 1 ? -2.0f * f1 : quad == 2 ? -2.0f * f2 : 1.0f;   // exact
+    // MODE 1, lane = particle: the row to fill
+    const int64_t rlo = FILL ? row_ptr[p0 + (pl < np ? pl : 0)] : 0;
+    const int64_t rlen = FILL ? row_ptr[p0 + (pl < np ? pl : 0) + 1] - rlo : 0;
     __syncthreads();
     const int W = w.off[w.nr];
     if ((FILL || STAGE) && threadIdx.x == 0 && W > 65535) atomicOr(&head->overflow, 1);
     if (win_tab && wv == 0) window_store<D>(w, win_tab, b);   // for the later calls
-    // the particle's own window offset (it is never its own neighbour)
-    int self_t = -1;
-    for (int r = 0; r < w.nr; ++r) {
-        const int64_t d = i - w.gstart[r];
-        if (d >= 0 && d < w.off[r + 1] - w.off[r]) self_t = w.off[r] + (int)d;
+    // the chunk's and the particle's own window offsets (it is never its own
+    // neighbour; the chunk is a run of one range: lane r looks for its start in range r)
+    int self_t, run0;
+    {
+        const int64_t d = pl < w.nr ? p0 - w.gstart[pl] : -1;
+        const int len = pl < w.nr ? w.off[pl + 1] - w.off[pl] : 0, at = pl < w.nr ? w.off[pl] + (int)d : 0;
+        const uint64_t own = __ballot(d >= 0 && d < len);
+        run0 = __builtin_amdgcn_readlane(at, __builtin_ctzll(own));
+        self_t = run0 + cpl;
     }
     // the chunk's hit words (MODE 2), np per word; only when they fit its
     // share of the staging buffer (np * kBmWords words)
@@ -463,32 +479,46 @@ __device__ __forceinline__ void nb_chunk(uint32_t b, int64_t n, const double* __
     }
     uint32_t* bmg = STAGE ? reinterpret_cast<uint32_t*>(col16) + p0 * kBmWords : nullptr;
     int rowpos = 0;                     // entries of the row found so far (MODE 1)
-    int mycnt = 0;                      // hits of this wave's candidates (MODES 0, 2)
+    int mycnt = 0;                      // hits of this lane's words (MODES 0, 2)
     for (int s0 = 0; s0 < W; s0 += kNbSeg) {
         const int sW = W - s0 < kNbSeg ? W - s0 : kNbSeg;
+        const int nb = (sW + kNbBlock - 1) / kNbBlock;
         if (s0 > 0) __syncthreads();   // the previous segment is consumed
-        // stage the segment: every load of a thread before its first LDS store
+        // stage the segment, kNbRep records of a thread at a time (their loads
+        // before the first LDS store); the last block is filled up with records
+        // far outside
         {
-            constexpr int kRep = kNbSeg / kNbThreads;
-            double px[kRep], py[kRep], pz[kRep];
+            float mo = 0.0f;   // largest |q|^2
+            for (int t0 = 0; t0 < nb * kNbBlock; t0 += kNbRep * kNbThreads) {   // uniform
+                double px[kNbRep], py[kNbRep], pz[kNbRep];
 #pragma unroll
-            for (int k = 0; k < kRep; ++k) {
-                const int t = threadIdx.x + k * kNbThreads;
-                const int64_t j = window_global<D>(w, s0 + (t < sW ? t : 0));
-                px[k] = pos[j];
-                py[k] = pos[n + j];
-                pz[k] = D == 3 ? pos[2 * n + j] : 0.0;
-            }
-            float mo = 0.0f;
+                for (int k = 0; k < kNbRep; ++k) {
+                    const int t = t0 + threadIdx.x + k * kNbThreads;
+                    const int64_t j = window_global<D>(w, s0 + (t < sW ? t : 0));
+                    px[k] = pos[j];
+                    py[k] = pos[n + j];
+                    pz[k] = D == 3 ? pos[2 * n + j] : 0.0;
+                }
 #pragma unroll
-            for (int k = 0; k < kRep; ++k) {
-                const int t = threadIdx.x + k * kNbThreads;
-                if (t < sW) {
-                    float4 q = make_float4((float)(px[k] - o0), (float)(py[k] - o1),
-                                           D == 3 ? (float)(pz[k] - o2) : 0.0f, 0.0f);
-                    q.w = fmaf(q.z, q.z, fmaf(q.y, q.y, q.x * q.x));
-                    win[t] = q;
-                    mo = fmaxf(mo, fmaxf(fabsf(q.x), fmaxf(fabsf(q.y), fabsf(q.z))));
+                for (int k = 0; k < kNbRep; ++k) {
+                    const int t = t0 + threadIdx.x + k * kNbThreads;
+                    if (t >= nb * kNbBlock) continue;
+                    float q0 = (float)((px[k] - o0) * sc), q1 = (float)((py[k] - o1) * sc);
+                    float q2 = D == 3 ? (float)((pz[k] - o2) * sc) : 0.0f;
+                    float qq = fmaf(q2, q2, fmaf(q1, q1, q0 * q0));
+                    mo = fmaxf(mo, qq);   // (the filling repeats a record of the window)
+                    if (t >= sW) qq = kNbFar;
+                    if (__any(qq != qq)) {   // rare: a position that is not a number is no neighbour
+                        if (qq != qq) {
+                            q0 = q1 = q2 = 0.0f;
+                            qq = kNbFar;
+                        }
+                    }
+                    const int at = (t & ~(kNbBlock - 1)) + ((t >> 2) & 7) * 16 + ((t >> 5) & 3) * 4 + (t & 3);
+                    win[0][at] = q0;
+                    win[1][at] = q1;
+                    win[2][at] = q2;
+                    win[3][at] = qq;
                 }
             }
 #pragma unroll
@@ -496,75 +526,77 @@ __device__ __forceinline__ void nb_chunk(uint32_t b, int64_t n, const double* __
             if (pl == 0) wmax[wv] = mo;
         }
         __syncthreads();
-        // Absolute bound on the FP32 error of t against the exact d2 - R^2,
-        // with M the largest offset component (staged or own) and u = 2^-24:
-        // the rounded offsets, |d2(q, f) - d2| <= 4 sqrt(3) u M |q - f| <=
-        // 24 u M^2; the three roundings of each of |q|^2 and |f|^2 (3 u
-        // 3M^2 each), the rounding of |f|^2 - lim, of the add and of the three
-        // multiply-adds, each relative to a partial result below 12 M^2 + R^2
-        // (57 u M^2 + 5 u R^2 in all); and the rounding of lim to FP32 (u R^2).
-        // 96 u M^2 + 8 u R^2 covers the sum.
-        const float mseg = fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3]));
-        const double maxoff = (double)fmaxf(mseg, fmax_own);
-        const double margin = (96.0 * maxoff * maxoff + 8.0 * R2) * 0x1p-24;
-        const float in_lim = (float)(R2 - margin), out_lim = (float)(R2 + margin);
-        const float cf = ff - in_lim;
+        // Absolute bound on the error of t against the exact d2 - lim in units
+        // of R, with u = 2^-24, Q the largest |q|^2 of the segment, F = |f|^2
+        // and T = 2 (Q + F) >= (|q| + |f|)^2: the rounded offsets (at most u |q|
+        // and u |f| off), 2 u T; the roundings of |q|^2 and |f|^2, 3 u Q and 3 u F; of |f|^2 - lim, u (F + 1), and of lim, u; the four
+        // products and sums of the matrix core, each partial result below
+        // T + 1 and taken as truncated (2 u), 8 u (T + 1) and 2 u T.
+        // 20 u T + 16 u covers the sum.
+        const float seg = fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3]));
+        const float T = 2.0f * (seg + ff);
+        const bool odd = valid && !(T < 1e30f);   // offsets beyond FP32, or not a number: the exact predicate decides all
+        const double margin = (20.0 * (double)T + 16.0) * 0x1p-24;
+        const float in_lim = (float)(1.0 - margin), out_lim = (float)(1.0 + margin);
+        const float cf = valid ? ff - in_lim : kNbFar;   // (an idle column has no hits)
         // t = d2 - in_lim: t < 0 is a certain hit, 0 <= t <= band is the
         // uncertain band (as unsigned integers, exactly the non-negative t up
         // to band: a negative t has its sign bit set), t > band certainly
         // lies outside.  band = out_lim - in_lim, rounded up if the FP32
-        // difference is inexact (offsets beyond about 240 R).
+        // difference is inexact.
         const double band_d = (double)out_lim - (double)in_lim;   // exact in FP64
         float band = (float)band_d;
         if ((double)band < band_d) band = nextafterf(band, INFINITY);
         const uint32_t band_u = __float_as_uint(band);
-        const int nw = (sW + 31) / 32;
-        const int k0 = wv * nw / kNbWaves, k1 = (wv + 1) * nw / kNbWaves;
-        [[maybe_unused]] int cnt = 0;   // this segment's hits of this wave (MODE 1)
-        for (int k = k0; k < k1; ++k) {
+        using f4 = float __attribute__((ext_vector_type(4)));
+        const f4 c4 = {cf, cf, cf, cf};
+        const int nblk = 16 * wv < np ? nb : 0;   // uniform: a wave without particles has nothing to test
+        for (int blk = 0; blk < nblk; ++blk) {
+            const float* ap = &win[quad][blk * kNbBlock + pl % 16];
+            float rec[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) rec[u] = ap[16 * u];
             // Hits shift in as the sign bits of t (the first candidate ends in
-            // bit 31, reversed below); whether any candidate of the word lies
-            // in the band is one flag per lane, rarely set.
-            uint32_t bits = 0u;
-            bool amb_any = false;
-            const float4* wp = win + 32 * k;
-            // records read eight at a time, the next eight while the current
-            // ones are tested
-            float4 rec[8], nxt[8];
+            // bit 31, reversed below); the smallest t as an unsigned integer
+            // tells whether any candidate of the word lies in the band.
+            uint32_t bits = 0u, low = 0xffffffffu;
 #pragma unroll
-            for (int u = 0; u < 8; ++u) rec[u] = wp[u];   // same record, every lane
+            for (int u = 0; u < 8; ++u) {
+                const f4 t = __builtin_amdgcn_mfma_f32_16x16x4f32(rec[u], colv, c4, 0, 0, 0);
 #pragma unroll
-            for (int u0 = 0; u0 < 32; u0 += 8) {
-                if (u0 + 8 < 32) {
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) nxt[u] = wp[u0 + 8 + u];
+                for (int v = 0; v < 4; ++v) {
+                    const uint32_t tu = __float_as_uint(t[v]);
+                    bits = __builtin_amdgcn_alignbit(bits, tu, 31);
+                    low = low < tu ? low : tu;
                 }
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const uint32_t t = __float_as_uint(d2_minus(rec[u], m0, m1, m2, cf));
-                    bits = __builtin_amdgcn_alignbit(bits, t, 31);
-                    amb_any = amb_any || t <= band_u;
-                }
-#pragma unroll
-                for (int u = 0; u < 8; ++u) rec[u] = nxt[u];
             }
             bits = __builtin_bitreverse32(bits);
-            // drop the tail beyond the segment, the particle itself, idle lanes
-            const int tb = s0 + 32 * k;
-            uint32_t keep = (sW - 32 * k) >= 32 ? 0xffffffffu : ((1u << (sW - 32 * k)) - 1u);
-            if (self_t >= tb && self_t < tb + 32) keep &= ~(1u << (self_t - tb));
-            if (!valid) keep = 0u;
-            bits &= keep;
-            if (amb_any) {
-                // the word's candidates in the band, from the same arithmetic
+            // drop the particle itself (its run's blocks alone)
+            const int tb = s0 + blk * kNbBlock + 32 * quad;   // the lane's word
+            const int me = self_t - tb;
+            if (run0 < s0 + (blk + 1) * kNbBlock && run0 + np > s0 + blk * kNbBlock)   // uniform
+                bits &= ~((unsigned)me < 32u ? 1u << me : 0u);
+            if (__ballot(low <= band_u || odd)) {   // uniform; rare
+                const int left = s0 + sW - tb;
+                uint32_t keep = left >= 32 ? 0xffffffffu : left > 0 ? (1u << left) - 1u : 0u;
+                if ((unsigned)me < 32u) keep &= ~(1u << me);
+                // the words' candidates in the band, from the same products
                 // (the empty asm keeps the compiler from carrying the t of the
                 // loop above over to here), then the exact FP64 predicate
-                float g0 = m0, g1 = m1, g2 = m2, gc = cf;
-                asm volatile("" : "+v"(g0), "+v"(g1), "+v"(g2), "+v"(gc));
+                float col2 = colv;
+                asm volatile("" : "+v"(col2));
                 uint32_t amb = 0u;
-#pragma unroll 1
-                for (int u = 0; u < 32; ++u)
-                    if (__float_as_uint(d2_minus(wp[u], g0, g1, g2, gc)) <= band_u) amb |= 1u << u;
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const f4 t = __builtin_amdgcn_mfma_f32_16x16x4f32(rec[u], col2, c4, 0, 0, 0);
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        if (__float_as_uint(t[v]) <= band_u) amb |= 1u << (4 * u + v);
+                }
+                if (odd) {
+                    amb = 0xffffffffu;
+                    bits = 0u;
+                }
                 amb &= keep;
                 while (amb) {
                     const int u = __builtin_ctz(amb);
@@ -575,16 +607,21 @@ __device__ __forceinline__ void nb_chunk(uint32_t b, int64_t n, const double* __
                 }
             }
             if constexpr (FILL) {
-                bm[k][pl] = bits;
-                cnt += __popc(bits);
+                bm[blk * 4 + quad][cpl] = bits;
             } else {
-                if (STAGE && valid)
-                    bmg[dcheck((s0 / 32 + k) * np + pl, np * kBmWords, kChkCapacity)] = bits;
+                if (STAGE && valid && tb < W)
+                    bmg[dcheck((tb / 32) * np + cpl, np * kBmWords, kChkCapacity)] = bits;
                 mycnt += __popc(bits);
             }
         }
         // MODES 0 and 2 sum the counts once, after the last segment
         if constexpr (FILL) {
+            // lane = particle, a quarter of the words to each wave
+            __syncthreads();
+            const int nw = (sW + 31) / 32;
+            const int k0 = wv * nw / kNbWaves, k1 = (wv + 1) * nw / kNbWaves;
+            int cnt = 0;
+            for (int k = k0; k < k1; ++k) cnt += __popc(bm[k][pl]);
             wcnt[wv][pl] = cnt;
             __syncthreads();
             // place this wave's hits after those of the earlier waves
@@ -595,7 +632,7 @@ __device__ __forceinline__ void nb_chunk(uint32_t b, int64_t n, const double* __
                 if (v < wv) pos0 += c;
                 total += c;
             }
-            if (valid) {
+            if (pl < np) {
                 int at = pos0;
                 for (int k = k0; k < k1; ++k) {
                     uint32_t bits = bm[k][pl];
@@ -614,21 +651,21 @@ __device__ __forceinline__ void nb_chunk(uint32_t b, int64_t n, const double* __
         }
     }
     if constexpr (!FILL) {
-        wcnt[wv][pl] = mycnt;
+        wcnt[quad][cpl] = mycnt;
         __syncthreads();
-        if (wv == 0 && valid) {
+        if (wv == 0 && pl < np) {
             int c = 0;
 #pragma unroll
             for (int v = 0; v < kNbWaves; ++v) c += wcnt[v][pl];
-            counts[i] = c;
+            counts[p0 + pl] = c;
         }
     }
 }
 
 // One chunk per work-group.
 template <int D, int MODE>
-__global__ __launch_bounds__(kNbThreads) void k_nb_chunk(int64_t n, const double* __restrict__ pos, Grid g,
-                                                         double R2, const int64_t* __restrict__ cs,
+__global__ __launch_bounds__(kNbThreads, 6) void k_nb_chunk(int64_t n, const double* __restrict__ pos, Grid g,
+                                                         double R2, double sc, const int64_t* __restrict__ cs,
                                                          const int32_t* __restrict__ cstart,
                                                          const int4* __restrict__ cinfo,
                                                          const int64_t* __restrict__ nchunks,
@@ -639,7 +676,7 @@ __global__ __launch_bounds__(kNbThreads) void k_nb_chunk(int64_t n, const double
                                                          int32_t* __restrict__ win_tab) {
     uint32_t b;
     if (!chunk_of_block(nchunks, b)) return;   // uniform over the work-group
-    nb_chunk<D, MODE>(b, n, pos, g, R2, cs, cstart, cinfo, counts, row_ptr, col, col16, head, wide, win_tab);
+    nb_chunk<D, MODE>(b, n, pos, g, R2, sc, cs, cstart, cinfo, counts, row_ptr, col, col16, head, wide, win_tab);
 }
 
 // The counts of the listed wide chunks, taken in turn by a fixed grid (none at
@@ -647,14 +684,14 @@ __global__ __launch_bounds__(kNbThreads) void k_nb_chunk(int64_t n, const double
 constexpr int kWideBlocks = 512;
 template <int D>
 __global__ __launch_bounds__(kNbThreads) void k_nb_wide(int64_t n, const double* __restrict__ pos, Grid g, double R2,
-                                                        const int64_t* __restrict__ cs,
+                                                        double sc, const int64_t* __restrict__ cs,
                                                         const int32_t* __restrict__ cstart,
                                                         const int4* __restrict__ cinfo, int32_t* __restrict__ counts,
                                                         SearchHead* __restrict__ head,
                                                         const int32_t* __restrict__ wide) {
     const int cnt = head->wide;
     for (int k = blockIdx.x; k < cnt; k += gridDim.x) {
-        nb_chunk<D, 0>((uint32_t)wide[k], n, pos, g, R2, cs, cstart, cinfo, counts, nullptr, nullptr, nullptr, head,
+        nb_chunk<D, 0>((uint32_t)wide[k], n, pos, g, R2, sc, cs, cstart, cinfo, counts, nullptr, nullptr, nullptr, head,
                        nullptr, nullptr);
         __syncthreads();   // the chunk's LDS is consumed
     }
@@ -1128,14 +1165,15 @@ static int launch_nb(const vct_nlist* nl, const double* pos, const Grid& g, cons
     const int64_t cap = ncols + nl->n / kChunk + 1;   // upper bound of the chunk count
     const char* name = MODE == 0 ? "k_nb_chunk (count)" : MODE == 1 ? "k_nb_chunk (fill)" : "k_nb_chunk (stage)";
     const int4* cinfo = reinterpret_cast<const int4*>(nl->chunk_info);
+    const double R2 = nl->R * nl->R;
     VCT_LAUNCH(name, (k_nb_chunk<D, MODE>), dim3((unsigned)cap), dim3(kNbThreads), 0, s, nl->n, pos, g,
-               nl->R * nl->R, nl->cell_start, nl->chunk_start, cinfo, nl->chunk_off + ncols,
+               R2, 1.0 / sqrt(R2), nl->cell_start, nl->chunk_start, cinfo, nl->chunk_off + ncols,
                MODE == 1 ? nullptr : ws.counts, nl->row_ptr, MODE == 1 ? nl->col : nullptr,
                MODE == 1 ? nl->col16 : ws.staged, ws.head, ws.wide, nl->chunk_win);
     VCT_LAUNCH_CHECK();
     if (MODE == 2) {
         VCT_LAUNCH("k_nb_chunk (count)", (k_nb_wide<D>), dim3((unsigned)(cap < kWideBlocks ? cap : kWideBlocks)),
-                   dim3(kNbThreads), 0, s, nl->n, pos, g, nl->R * nl->R, nl->cell_start, nl->chunk_start, cinfo,
+                   dim3(kNbThreads), 0, s, nl->n, pos, g, R2, 1.0 / sqrt(R2), nl->cell_start, nl->chunk_start, cinfo,
                    ws.counts, ws.head, ws.wide);
         VCT_LAUNCH_CHECK();
     }
