@@ -551,13 +551,18 @@ int vct_ppe_correct(const vct_nlist* nl, const double* pos_sorted, const double*
                     const double* state64, uint32_t out_mask, const vct_map* map /* host */, const double* p,
                     const double* vstar, double rho, double dt, double* vout, void* stream);
 
+/* Room for the solver's vectors and, up to 16 GiB, for the matrix's
+ * coefficients (128 entries per particle in 3-D, 40 in 2-D).  The vectors alone
+ * (72 n bytes and about 25 KB) are enough for vct_ppe_solve: it then forms the
+ * coefficients in every product.                                             */
 size_t vct_ppe_workspace_size(int dim, int64_t n, uint32_t out_mask);
 
 /* vct_ppe_solve: the pressure Poisson equation c_trans . <D^ p>_i = rhs_i
  * (Eq. VCT_ppe) on rows with dirichlet[i] == 0 and p_i = rhs_i on the others
  * (dirichlet may be NULL), by BiCGSTAB with the Jacobi preconditioner on the
- * right (diagonal: the coefficient of p_i in row i).  The operator is
- * matrix-free: the FP64 Laplacian of vct_apply_ops on the fixed state.  `p`
+ * right (diagonal: the coefficient of p_i in row i).  The operator is the FP64
+ * Laplacian of vct_apply_ops on the fixed state; its coefficients are formed
+ * once and kept in the workspace where they fit, or in every product.  `p`
  * holds the initial guess on entry and the solution on return.  Stops when
  * ||r|| <= tol ||rhs|| (the recurrence residual) or after max_iter
  * iterations.  The scalars of the method stay on the device; every inner

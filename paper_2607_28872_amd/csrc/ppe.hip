@@ -48,6 +48,7 @@ struct PpeArgs {
     double* dens;
     double* vout;             // [dim][n] (corrector)
     double* dinv;             // [n] (Jacobi diagonal)
+    double* wmat;             // [entries] the matrix's coefficients W_ij, or NULL: not kept
 };
 
 // Normalised kernel value w(q R) (unit integral): Wendland C2
@@ -248,8 +249,10 @@ __global__ __launch_bounds__((kChunk * RowShape<C>::lanes), RowShape<C>::waves) 
 }
 
 // Jacobi diagonal of the pressure system: the coefficient of p_i in row i,
-// -sum_j W_ij on ordinary rows, 1 on Dirichlet rows; dinv = its inverse.
-// 1,048,352 particles in 3-D 0.42 -> 0.34 ms, 524,288 in 2-D 0.058 -> 0.033 ms.
+// -sum_j W_ij on ordinary rows, 1 on Dirichlet rows; dinv = its inverse.  With
+// wmat the coefficients W_ij are kept for k_ppe_matvec, in row order.
+// 1,048,352 particles in 3-D 0.42 -> 0.34 ms (0.52 with the coefficients),
+// 524,288 in 2-D 0.058 -> 0.033 ms.
 template <int D, int KERNEL, int C>
 __global__ __launch_bounds__((kChunk * RowShape<C>::lanes), RowShape<C>::waves) void k_ppe_diag(PpeArgs A) {
     using Dm = Dims<D>;
@@ -288,13 +291,78 @@ __global__ __launch_bounds__((kChunk * RowShape<C>::lanes), RowShape<C>::waves) 
     if (in_lds) stage_window<kWin, kThreads>(W, record, [&](int t, const double4& q) { sd[t] = q; });
     __syncthreads();
     double s = 0.0;
+    int64_t e = (valid ? A.row_ptr[ii] : 0) + lane;   // the lane's entries come in order
     sweep_row(rs, A.col16, W, in_lds, [&](int t) -> double4 { return in_lds ? sd[t] : record(t); },
-              [&](const double4& q) { s += lap_weight<D, KERNEL>(q, xi, A.invR, L2, Pl); });
+              [&](const double4& q) {
+                  const double wij = lap_weight<D, KERNEL>(q, xi, A.invR, L2, Pl);
+                  s += wij;
+                  if (A.wmat) {
+                      A.wmat[e] = wij;
+                      e += kLanes;
+                  }
+              });
     s = group_sum(s, kLanes);
     if (valid && lane == 0) {
         const bool dir = A.dirichlet && A.dirichlet[ii];
         A.dinv[ii] = dir ? 1.0 : 1.0 / (-s);
     }
+}
+
+// The product with the kept matrix: sum_j W_ij (x_j - x_i), on Dirichlet rows x_i.
+// The coefficients are read once in row order, all of a lane's before the
+// window's values are in LDS.  Bound by that read: 1,048,352 particles in 3-D
+// (108M entries of 10 bytes), 0.228 ms, 4.8 TB/s, where forming the coefficients
+// in each product takes 0.46 ms; cubic spline 0.143 against 0.316; 2-D, 524,288
+// particles, 0.027 against 0.049.  (Non-temporal loads give up the part of the
+// matrix that stays in the last-level cache: 0.297; eight waves per SIMD spill:
+// 0.35.)
+constexpr int kMatRow3 = 128, kMatRow2 = 40;       // entries per particle of the workspace (3-D, 2-D)
+constexpr size_t kMatMax = (size_t)16 << 30;       // the largest kept matrix (bytes)
+constexpr int kMatIters = 1;                       // iterations from which one is kept
+template <int D, int C>
+__global__ __launch_bounds__((kChunk * RowShape<C>::lanes), 4) void k_ppe_matvec(PpeArgs A,
+                                                                                const double* __restrict__ x,
+                                                                                double* __restrict__ out) {
+    using Sh = RowShape<C>;
+    constexpr int kLanes = Sh::lanes, kThreads = kChunk * kLanes, kSlots = Sh::slots, kWin = D == 3 ? 2048 : 1024;
+    __shared__ double sx[kWin];
+    __shared__ WindowT<D> w;
+    uint32_t b;
+    if (!chunk_of_block(A.nchunks, b)) return;   // uniform over the work-group
+    const int64_t p0 = A.cstart[b], p1 = A.cstart[b + 1];
+    if (threadIdx.x < kWave) {
+        if (A.cwin) window_load<D>(A.cwin, b, w);
+        else chunk_window_wave<D>(A.g, A.cs, A.cinfo[b], w);
+    }
+    const int lane = threadIdx.x % kLanes;
+    const int64_t i = p0 + threadIdx.x / kLanes;
+    const bool valid = i < p1;
+    const int64_t ii = valid ? i : p0;
+    const double xi = x[ii];
+    const int64_t rb = valid ? A.row_ptr[ii] : 0, re = valid ? A.row_ptr[ii + 1] : 0;
+    const RowSlots<kLanes, kSlots> rs(A.col16, rb, re, lane);
+    const double* wr = A.wmat + rb + lane;
+    double wij[kSlots];
+#pragma unroll
+    for (int s = 0; s < kSlots; ++s) wij[s] = s < rs.n ? wr[kLanes * s] : 0.0;
+    __syncthreads();
+    const int W = __builtin_amdgcn_readfirstlane(w.off[w.nr]);
+    const bool in_lds = W <= kWin;
+    auto value = [&](int t) { return x[window_global<D>(w, t)]; };
+    if (in_lds) stage_window<kWin, kThreads>(W, value, [&](int t, double v) { sx[t] = v; });
+    __syncthreads();
+    double sum = 0.0;
+    if (in_lds) {
+#pragma unroll
+        for (int s = 0; s < kSlots; ++s)
+            if (s < rs.n) sum = fma(wij[s], sx[rs.at(s, W)] - xi, sum);
+    }
+    for (int64_t e = in_lds ? rs.tail : rb + lane; e < re; e += kLanes) {
+        const int t = dcheck((int)A.col16[e], W, kChkWindow);
+        sum = fma(A.wmat[e], (in_lds ? sx[t] : value(t)) - xi, sum);
+    }
+    sum = group_sum(sum, kLanes);
+    if (valid && lane == 0) out[ii] = A.dirichlet && A.dirichlet[ii] ? xi : sum;
 }
 
 // ------------------------------------------------------------------ BiCGSTAB
@@ -533,6 +601,30 @@ static int launch_diag(const PpeArgs& a, int64_t mean, int64_t cap, hipStream_t 
     return VCT_OK;
 }
 
+template <int D>
+static int launch_matvec(const PpeArgs& a, int64_t mean, int64_t cap, const double* x, double* out, hipStream_t s) {
+    constexpr int kShort = D == 2 ? kRowsShort2 : kRowsShort3;
+    if (mean <= short_row<D>())
+        VCT_LAUNCH("k_ppe_matvec", (k_ppe_matvec<D, kShort>), dim3((unsigned)cap),
+                   dim3(kChunk * RowShape<kShort>::lanes), 0, s, a, x, out);
+    else
+        VCT_LAUNCH("k_ppe_matvec", (k_ppe_matvec<D, kRowsLong>), dim3((unsigned)cap),
+                   dim3(kChunk * RowShape<kRowsLong>::lanes), 0, s, a, x, out);
+    VCT_LAUNCH_CHECK();
+    return VCT_OK;
+}
+
+// Workspace without the kept matrix (enough for the matrix-free product), and
+// the bytes of the matrix (0: too many particles for one).
+static size_t ppe_ws_base(int64_t n) {
+    return aligned_sum({(size_t)n * 9 * sizeof(double), (size_t)kVSlots * kVBlocks * sizeof(double),
+                        (size_t)kNScalars * sizeof(double)});
+}
+static int64_t mat_entries(int dim, int64_t n) {
+    const int64_t e = n * (dim == 3 ? kMatRow3 : kMatRow2);
+    return (size_t)e * sizeof(double) <= kMatMax ? e : 0;
+}
+
 VCT_CHECKS_TU(checks_ppe)
 
 }  // namespace vct
@@ -579,9 +671,8 @@ extern "C" int vct_ppe_correct(const vct_nlist* nl, const double* pos_sorted, co
 
 extern "C" size_t vct_ppe_workspace_size(int dim, int64_t n, uint32_t out_mask) {
     if ((dim != 2 && dim != 3) || n < 0 || !mask_valid(out_mask)) return 0;
-    const size_t nn = (size_t)(n > 0 ? n : 1);
-    return aligned_sum({nn * 9 * sizeof(double),
-                        (size_t)kVSlots * kVBlocks * sizeof(double), (size_t)kNScalars * sizeof(double)});
+    const int64_t nn = n > 0 ? n : 1;
+    return aligned_sum({ppe_ws_base(nn), (size_t)mat_entries(dim, nn) * sizeof(double)});
 }
 
 extern "C" int vct_ppe_solve(const vct_nlist* nl, const double* pos_sorted, const double* vol_sorted, int kernel,
@@ -600,7 +691,7 @@ extern "C" int vct_ppe_solve(const vct_nlist* nl, const double* pos_sorted, cons
     if (relres) *relres = 0.0;
     if (n == 0) return VCT_OK;
     if (!rhs || !p) return VCT_E_ARG;
-    if (!ws || ws_bytes < vct_ppe_workspace_size(dim, n, out_mask)) return VCT_E_WORKSPACE;
+    if (!ws || ws_bytes < ppe_ws_base(n)) return VCT_E_WORKSPACE;
     hipStream_t s = as_stream(stream);
     Carver cv(ws, ws_bytes);
     BicgVec V;
@@ -613,6 +704,16 @@ extern "C" int vct_ppe_solve(const vct_nlist* nl, const double* pos_sorted, cons
     const int64_t cap = chunk_cap(nl, g);
     a.dirichlet = dirichlet; a.dinv = V.dinv;
     const int64_t mean = mean_row(nl);
+    // The matrix is kept where its entries fit the workspace and an iteration
+    // may follow: storing it costs less than one product saves in 3-D (0.18
+    // against 0.23 ms, 1,048,352 particles), three in 2-D (0.07 against 0.023,
+    // 1,048,576), and an iteration takes two besides the two residuals.
+    if (max_iter >= kMatIters && mat_entries(dim, n) > 0 && ws_bytes >= vct_ppe_workspace_size(dim, n, out_mask)) {
+        int64_t nnz = 0;
+        VCT_HIP_CHECK(hipMemcpyAsync(&nnz, nl->row_ptr + n, sizeof(nnz), hipMemcpyDeviceToHost, s));
+        VCT_HIP_CHECK(hipStreamSynchronize(s));
+        if (nnz <= mat_entries(dim, n)) a.wmat = cv.take<double>((size_t)mat_entries(dim, n));
+    }
     if (dim == 2)
         st = kernel == VCT_KERNEL_WENDLAND_C2 ? launch_diag<2, VCT_KERNEL_WENDLAND_C2>(a, mean, cap, s)
                                               : launch_diag<2, VCT_KERNEL_CUBIC_SPLINE>(a, mean, cap, s);
@@ -622,6 +723,8 @@ extern "C" int vct_ppe_solve(const vct_nlist* nl, const double* pos_sorted, cons
     if (st) return st;
     const double tol2 = tol * tol;
     auto matvec = [&](const double* xin, double* out) {
+        if (a.wmat)
+            return dim == 2 ? launch_matvec<2>(a, mean, cap, xin, out, s) : launch_matvec<3>(a, mean, cap, xin, out, s);
         return apply_lap(nl, g, xin, pos_sorted, vol_sorted, kernel, state64, out_mask, dirichlet, out, s);
     };
     const dim3 vg(kVBlocks), vb(kVThreads);
