@@ -665,15 +665,15 @@ __device__ __forceinline__ void nb_chunk(uint32_t b, int64_t n, const double* __
 // One chunk per work-group.
 template <int D, int MODE>
 __global__ __launch_bounds__(kNbThreads, 6) void k_nb_chunk(int64_t n, const double* __restrict__ pos, Grid g,
-                                                         double R2, double sc, const int64_t* __restrict__ cs,
-                                                         const int32_t* __restrict__ cstart,
-                                                         const int4* __restrict__ cinfo,
-                                                         const int64_t* __restrict__ nchunks,
-                                                         int32_t* __restrict__ counts,
-                                                         const int64_t* __restrict__ row_ptr,
-                                                         int32_t* __restrict__ col, uint16_t* __restrict__ col16,
-                                                         SearchHead* __restrict__ head, int32_t* __restrict__ wide,
-                                                         int32_t* __restrict__ win_tab) {
+                                                            double R2, double sc, const int64_t* __restrict__ cs,
+                                                            const int32_t* __restrict__ cstart,
+                                                            const int4* __restrict__ cinfo,
+                                                            const int64_t* __restrict__ nchunks,
+                                                            int32_t* __restrict__ counts,
+                                                            const int64_t* __restrict__ row_ptr,
+                                                            int32_t* __restrict__ col, uint16_t* __restrict__ col16,
+                                                            SearchHead* __restrict__ head, int32_t* __restrict__ wide,
+                                                            int32_t* __restrict__ win_tab){
     uint32_t b;
     if (!chunk_of_block(nchunks, b)) return;   // uniform over the work-group
     nb_chunk<D, MODE>(b, n, pos, g, R2, sc, cs, cstart, cinfo, counts, row_ptr, col, col16, head, wide, win_tab);

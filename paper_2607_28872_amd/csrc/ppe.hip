@@ -7,7 +7,8 @@
 //                    projected-space kernel-sum density and jr_i = Jbar_i / J_i;
 //   pressure solve   c_trans . <D^ p>_i = rhs_i on ordinary rows, p_i = rhs_i on
 //                    Dirichlet rows, by BiCGSTAB with the SPH(2) Laplacian of
-//                    vct_apply_ops as the matrix-free operator;
+//                    vct_apply_ops as the operator, its coefficients kept for the
+//                    call where they fit;
 //   corrector        v_i = v*_i - dt/rho J <grad^ p>^(1)_i (Eqs. gra_1st, grad_VCT).
 #include <string.h>
 
@@ -614,7 +615,7 @@ static int launch_matvec(const PpeArgs& a, int64_t mean, int64_t cap, const doub
     return VCT_OK;
 }
 
-// Workspace without the kept matrix (enough for the matrix-free product), and
+// Workspace without the kept matrix (enough for the product that forms it), and
 // the bytes of the matrix (0: too many particles for one).
 static size_t ppe_ws_base(int64_t n) {
     return aligned_sum({(size_t)n * 9 * sizeof(double), (size_t)kVSlots * kVBlocks * sizeof(double),
