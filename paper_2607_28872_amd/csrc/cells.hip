@@ -673,7 +673,7 @@ __global__ __launch_bounds__(kNbThreads, 6) void k_nb_chunk(int64_t n, const dou
                                                             const int64_t* __restrict__ row_ptr,
                                                             int32_t* __restrict__ col, uint16_t* __restrict__ col16,
                                                             SearchHead* __restrict__ head, int32_t* __restrict__ wide,
-                                                            int32_t* __restrict__ win_tab){
+                                                            int32_t* __restrict__ win_tab) {
     uint32_t b;
     if (!chunk_of_block(nchunks, b)) return;   // uniform over the work-group
     nb_chunk<D, MODE>(b, n, pos, g, R2, sc, cs, cstart, cinfo, counts, row_ptr, col, col16, head, wide, win_tab);
