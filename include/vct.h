@@ -553,7 +553,7 @@ int vct_ppe_correct(const vct_nlist* nl, const double* pos_sorted, const double*
 
 /* Room for the solver's vectors and, up to 16 GiB, for the matrix's
  * coefficients (128 entries per particle in 3-D, 40 in 2-D).  The vectors alone
- * (72 n bytes and about 25 KB) are enough for vct_ppe_solve: it then forms the
+ * (72 n bytes and about 41 KB) are enough for vct_ppe_solve: it then forms the
  * coefficients in every product.                                             */
 size_t vct_ppe_workspace_size(int dim, int64_t n, uint32_t out_mask);
 
