@@ -30,7 +30,7 @@ struct PpeArgs {
     const double* pos;
     const double* vol;
     const double* state;
-    int lap_row;
+    int lap_row, nrows;
     const int64_t* row_ptr;
     const uint16_t* col16;
     const int64_t* cs;
@@ -251,7 +251,9 @@ __global__ __launch_bounds__((kChunk * RowShape<C>::lanes), RowShape<C>::waves) 
 
 // Jacobi diagonal of the pressure system: the coefficient of p_i in row i,
 // -sum_j W_ij on ordinary rows, 1 on Dirichlet rows; dinv = its inverse.  With
-// wmat the coefficients W_ij are kept for k_ppe_matvec, in row order.
+// wmat the coefficients W_ij are kept for k_ppe_matvec, in row order.  A row
+// whose state is not finite (a flagged particle) has NaN for all of them and
+// for dinv, so that a row without entries says so too.
 // 1,048,352 particles in 3-D 0.42 -> 0.34 ms (0.52 with the coefficients),
 // 524,288 in 2-D 0.058 -> 0.033 ms.
 template <int D, int KERNEL, int C>
@@ -281,6 +283,14 @@ __global__ __launch_bounds__((kChunk * RowShape<C>::lanes), RowShape<C>::waves) 
     for (int p = 0; p < nL; ++p) L2[p] = (pair_a<D>(p) == pair_b<D>(p) ? 1.0 : 2.0) * A.state[(int64_t)p * n + ii];
 #pragma unroll
     for (int c = 0; c < nk; ++c) Pl[c] = A.state[(int64_t)(nL + A.lap_row * nk + c) * n + ii];
+    double bad = 0.0;   // 0, or NaN where the state (the response to a gradient included) is not finite
+#pragma unroll
+    for (int p = 0; p < nL; ++p) bad += 0.0 * L2[p];
+#pragma unroll
+    for (int c = 0; c < nk; ++c) bad += 0.0 * Pl[c];
+#pragma unroll
+    for (int a = 0; a < D; ++a) bad += 0.0 * A.state[(int64_t)(nL + A.nrows * nk + A.lap_row * D + a) * n + ii];
+    L2[0] += bad;
     const RowSlots<kLanes, Sh::slots> rs(A.col16, valid ? A.row_ptr[ii] : 0, valid ? A.row_ptr[ii + 1] : 0, lane);
     auto record = [&](int t) -> double4 {
         const int64_t j = window_global<D>(w, t);
@@ -305,11 +315,13 @@ __global__ __launch_bounds__((kChunk * RowShape<C>::lanes), RowShape<C>::waves) 
     s = group_sum(s, kLanes);
     if (valid && lane == 0) {
         const bool dir = A.dirichlet && A.dirichlet[ii];
-        A.dinv[ii] = dir ? 1.0 : 1.0 / (-s);
+        A.dinv[ii] = dir ? 1.0 : 1.0 / (-(s + bad));
     }
 }
 
-// The product with the kept matrix: sum_j W_ij (x_j - x_i), on Dirichlet rows x_i.
+// The product with the kept matrix: sum_j W_ij (x_j - x_i), on Dirichlet rows
+// x_i.  A row without entries takes the NaN of its dinv where its state is not
+// finite, as the product that forms the coefficients does.
 // The coefficients are read once in row order, all of a lane's before the
 // window's values are in LDS.  Bound by that read: 1,048,352 particles in 3-D
 // (108M entries of 10 bytes), 0.228 ms, 4.8 TB/s, where forming the coefficients
@@ -363,7 +375,10 @@ __global__ __launch_bounds__((kChunk * RowShape<C>::lanes), 4) void k_ppe_matvec
         sum = fma(A.wmat[e], (in_lds ? sx[t] : value(t)) - xi, sum);
     }
     sum = group_sum(sum, kLanes);
-    if (valid && lane == 0) out[ii] = A.dirichlet && A.dirichlet[ii] ? xi : sum;
+    if (valid && lane == 0) {
+        if (rb == re && A.dinv[ii] != A.dinv[ii]) sum = __builtin_nan("");   // rare: no coefficient carries it
+        out[ii] = A.dirichlet && A.dirichlet[ii] ? xi : sum;
+    }
 }
 
 // ------------------------------------------------------------------ BiCGSTAB
@@ -620,6 +635,7 @@ static int ppe_common(const vct_nlist* nl, Grid& g, const double* pos_sorted, co
     memset(&a, 0, sizeof(a));
     a.n = n; a.R = nl->R; a.invR = 1.0 / nl->R; a.g = g; a.pos = pos_sorted; a.vol = vol_sorted; a.state = state64;
     a.lap_row = group_row(dim, out_mask, VCT_OUT_LAP);
+    a.nrows = n_out_rows(dim, out_mask);
     a.row_ptr = nl->row_ptr; a.col16 = nl->col16; a.cs = nl->cell_start; a.cstart = nl->chunk_start;
     a.cinfo = reinterpret_cast<const int4*>(nl->chunk_info); a.cwin = nl->chunk_win;
     a.nchunks = nl->chunk_off + ncols;
