@@ -441,8 +441,8 @@ size_t vct_adjoint_workspace_size(int dim, int64_t n, int64_t nnz, int nterms);
  *   dtheta_t = sum_i u_i (d c_trans_i / d coef_t) . D^ phi_i
  *              for every bathymetry term t of `map` (projected positions held
  *              fixed).
- * dphi, two forms; each evaluates every weight W_ij once and gives the same
- * bits on every run (no floating-point atomics):
+ * dphi, two forms; both give the same bits on every run (no floating-point
+ * atomics):
  *   transposed form (nl->col_t given, and either nl->chunk_win is not or the
  *     mean window of a cell column is beyond 3264 particles): every particle i
  *     writes u_i W_ij for its row into the workspace at the transposed position
@@ -450,11 +450,17 @@ size_t vct_adjoint_workspace_size(int dim, int64_t n, int64_t nnz, int nterms);
  *   push form (otherwise; needs nl->chunk_win, VCT_E_ARG without it and
  *     without nl->col_t): per background-cell column, every particle i adds
  *     u_i W_ij to accumulators of the column's window held in LDS as exact
- *     integers: each term is scaled by 2^k from a per-column bound M on the
- *     terms (k = 62 - ilogb(M) - bitlen(longest row)), rounded and summed in
- *     64-bit integers, so the order of arrival does not matter; the column's
- *     totals go to one of 3^(d-1) slots per particle, summed in slot order,
- *     and the row sum u_i sum_j W_ij is subtracted.
+ *     integers, so the order of arrival does not matter: each term is scaled by
+ *     2^k from a per-column bound M on the terms (k = 62 - ilogb(M) -
+ *     bitlen(longest row)) and rounded to a 64-bit integer; what that rounds
+ *     off, times 2^51 (less for rows beyond 4095), is rounded to a second one.
+ *     The column's totals go to one of 3^(d-1) slots per particle, summed in
+ *     slot order; a particle for which the second rounding may exceed 2^-53 of
+ *     its total in a column takes its sum in FP64 from its neighbours' states
+ *     instead.  So each entry of dphi is as accurate as an FP64 sum of its own
+ *     terms.  (Without nl->col_t, columns of more than 3264 window particles
+ *     sum the first integer alone: their entries are accurate to about
+ *     2^-62 x longest row x M.)  The row sum u_i sum_j W_ij is subtracted.
  * dtheta: per particle from D^ phi_i, reduced in a fixed order.
  * `state64` must come from vct_moments (or vct_moments_resolve) with out_mask
  * containing VCT_OUT_LAP and either VCT_OUT_PZ or both VCT_OUT_PGRAD and
