@@ -663,7 +663,7 @@ __device__ __forceinline__ void push_column(const AdjArgs& A, double* __restrict
         if constexpr (OP::kR2) {
             bnd = A.r2b[i];
         } else {
-            double pa2 = 0.0, rL[D] = {}, rS[D] = {};
+            double pv[D], pm = 0.0, pa2, rL[D] = {}, rS[D] = {};
 #pragma unroll
             for (int p = 0; p < nL; ++p) {
                 const double v = fabs(A.state[(int64_t)p * n + i]);
@@ -672,9 +672,15 @@ __device__ __forceinline__ void push_column(const AdjArgs& A, double* __restrict
             }
 #pragma unroll
             for (int a = 0; a < D; ++a) {
-                const double v = A.state[(int64_t)(nL + A.lap_row * nk + a) * n + i];
-                pa2 = fma(v, v, pa2);
+                pv[a] = A.state[(int64_t)(nL + A.lap_row * nk + a) * n + i];
+                pm = fmax(pm, fabs(pv[a]));
             }
+            // |P_a| by its largest component: the squares of its own overflow at
+            // units of length and volume whose results are still in range
+            const double pi = pm > 0x1p-1000 ? 1.0 / pm : 0.0;
+            pa2 = pi > 0.0 ? 0.0 : 4.0;   // no larger than sqrt(D) of it
+#pragma unroll
+            for (int a = 0; a < D; ++a) pa2 = fma(pv[a] * pi, pv[a] * pi, pa2);
 #pragma unroll
             for (int p = 0; p < m; ++p) {
                 const double v = fabs(A.state[(int64_t)(nL + A.lap_row * nk + D + p) * n + i]);
@@ -694,7 +700,7 @@ __device__ __forceinline__ void push_column(const AdjArgs& A, double* __restrict
             const double cmax = KERNEL == VCT_KERNEL_WENDLAND_C2 ? 1.0 : 3.0;
             const double qcmax = KERNEL == VCT_KERNEL_WENDLAND_C2 ? 27.0 / 256.0 : 0.5;
             // (a NaN in the state makes the particle's bound NaN: fmax alone would drop it)
-            bnd = fabs(A.u[i]) * (qcmax * sqrt(pa2) + cmax * (mL * mS)) + 0.0 * (pa2 + rL[0] + rS[0]);
+            bnd = fabs(A.u[i]) * (qcmax * (pm * sqrt(pa2)) + cmax * (mL * mS)) + 0.0 * (pa2 + rL[0] + rS[0]);
         }
         if (bnd <= 1.7976931348623157e308) bmax = fmax(bmax, bnd);   // skips NaN and infinity
     }
