@@ -268,7 +268,8 @@ int vct_scatter_sorted(int64_t n, int ncomp, const int32_t* perm, const double* 
  * aligned (VCT_E_ARG otherwise).                                             */
 typedef struct {
     int32_t dim;            /* 2 or 3 */
-    int32_t reserved;
+    int32_t wide_particles; /* written by vct_neighbors: 1 + the particles of cell columns whose window
+                               (the columns around, all z cells) holds more than 3200 (0: not known) */
     int64_t n;              /* particles */
     int64_t ncell;          /* cells (vct_grid_dims) */
     int64_t chunk_cap;      /* capacity of the chunk arrays, >= vct_chunk_capacity() */
@@ -443,8 +444,9 @@ size_t vct_adjoint_workspace_size(int dim, int64_t n, int64_t nnz, int nterms);
  *              fixed).
  * dphi, two forms; both give the same bits on every run (no floating-point
  * atomics):
- *   transposed form (nl->col_t given, and either nl->chunk_win is not or the
- *     mean window of a cell column is beyond 3264 particles): every particle i
+ *   transposed form (nl->col_t given, unless the push form is the faster one:
+ *     in 3-D, long rows, many entries and few wide columns; or the set has at
+ *     most 10,240 particles; it needs nl->chunk_win): every particle i
  *     writes u_i W_ij for its row into the workspace at the transposed position
  *     col_t[e], then every particle k sums its row of that buffer in row order;
  *   push form (otherwise; needs nl->chunk_win, VCT_E_ARG without it and
@@ -458,7 +460,7 @@ size_t vct_adjoint_workspace_size(int dim, int64_t n, int64_t nnz, int nterms);
  *     slot order; a particle for which the second rounding may exceed 2^-53 of
  *     its total in a column takes its sum in FP64 from its neighbours' states
  *     instead.  So each entry of dphi is as accurate as an FP64 sum of its own
- *     terms.  (Without nl->col_t, columns of more than 3264 window particles
+ *     terms.  (Without nl->col_t, columns of more than 3200 window particles
  *     sum the first integer alone: their entries are accurate to about
  *     2^-62 x longest row x M.)  The row sum u_i sum_j W_ij is subtracted.
  * dtheta: per particle from D^ phi_i, reduced in a fixed order.

@@ -66,6 +66,8 @@ struct AdjArgs {
     double* partial;   // [3^(d-1)][n] per-source-column totals of the push form
     int32_t* wide;     // [kWideList + n / 256 + 2]: see kWideCount, kWideMaxDeg, kWideList
     bool two_only;     // push form: every column in two-word sums
+    bool wide_cols;    // there may be columns of more than kPushWindow window particles
+    bool own_maxdeg;   // push form: every column finds the longest row of the (small) set itself
     double* wbuf;      // [nnz]: u_i W_ij at the transposed position
     double* rowsum;    // [n]:  u_i sum_j W_ij
     double* dphi;
@@ -529,7 +531,7 @@ __global__ __launch_bounds__(kAThreads, 2) void k_r2_prep(AdjArgs A, double* __r
 // is the transposed form's).
 constexpr int kPThreads = 1024;   // 128 particles at a time, 8 lanes each (the field adjoint)
 constexpr int kPAcc = 3840;       // accumulators (and staged records) per pass over a column's window
-constexpr int kPTwo = 3264;       // the same with two-word accumulators beside staged records (LDS)
+constexpr int kPTwo = kPushWindow;   // the same with two-word accumulators beside staged records (LDS)
 constexpr int kPChunks = 24;      // chunk windows of one column held in LDS
 constexpr int kPSlots = 16;       // row entries per lane loaded into registers at a time
 // the int32 side buffer of the push form: count of wide columns, the longest
@@ -569,7 +571,7 @@ struct PushLap {
     static constexpr bool kR2 = false, kShiftWin = false;
 };
 struct PushR2 {
-    static constexpr int kAcc = 3200, kThreads = kPThreads / 2;
+    static constexpr int kAcc = kPushWindow, kThreads = kPThreads / 2;
     static constexpr bool kR2 = true, kShiftWin = true;
 };
 
@@ -609,6 +611,7 @@ __device__ __forceinline__ void push_column(const AdjArgs& A, double* __restrict
     __shared__ int s_sh[kPChunks][kMaxRanges];
     __shared__ int s_slot[kMaxRanges];
     __shared__ double s_red[2][kW];
+    __shared__ int s_deg[kW];
 
     const int64_t n = A.n;
     const int tid = threadIdx.x;
@@ -704,11 +707,19 @@ __device__ __forceinline__ void push_column(const AdjArgs& A, double* __restrict
         }
         if (bnd <= 1.7976931348623157e308) bmax = fmax(bmax, bnd);   // skips NaN and infinity
     }
+    int deg = 0;
+    if (A.own_maxdeg) {   // uniform
+        for (int64_t i = tid; i < n; i += kThreads) deg = max(deg, (int)(A.row_ptr[i + 1] - A.row_ptr[i]));
+    } else {
+        deg = wide[kWideMaxDeg + tid % kWave];
+    }
+    deg = wave_max(deg);
     vmax = wave_max(vmax);
     bmax = wave_max(bmax);
     if (tid % kWave == 0) {
         s_red[0][wv] = vmax;
         s_red[1][wv] = bmax;
+        s_deg[wv] = deg;
     }
     __syncthreads();
     vmax = 0.0;
@@ -717,11 +728,12 @@ __device__ __forceinline__ void push_column(const AdjArgs& A, double* __restrict
     for (int w = 0; w < kW; ++w) {
         vmax = fmax(vmax, s_red[0][w]);
         bmax = fmax(bmax, s_red[1][w]);
+        deg = max(deg, s_deg[w]);
     }
     // (both bounds hold the kernel-shape factors)
     const double Mb = vmax * 1.0625 * bmax;   // the factor covers |r~| rounded above 1
     // terms reaching one accumulator: at most one per neighbour of its particle
-    const double nterm = (double)wave_max(wide[kWideMaxDeg + tid % kWave]);
+    const double nterm = (double)deg;
     // R2: two bits fewer, the scale its results have always been rounded at
     // (dtheta is a sum over all particles that cancels to as little as 1e-5 of
     // its terms, so another scale shows in it at parts in 1e9)
@@ -957,7 +969,10 @@ __global__ __launch_bounds__(OP::kThreads, 1) void k_adjoint_push_wide(AdjArgs A
 // columns cleared for the push kernel.  64 blocks whose results the push kernel
 // reads as one wave: with one atomic per wave on a single word the 2,048
 // atomics took 25 us, whatever the size, and needed a launch to clear it.
+// Up to kOwnMaxDeg particles (ten rows per thread) the push kernel of a list
+// without wide columns looks for itself, one launch less.
 constexpr int kMaxDegThreads = 1024;
+constexpr int64_t kOwnMaxDeg = 10240;
 __global__ __launch_bounds__(kMaxDegThreads) void k_adjoint_maxdeg(int64_t n, const int64_t* __restrict__ row_ptr,
                                                                   int32_t* __restrict__ wide) {
     __shared__ int s_d[kMaxDegThreads / kWave];
@@ -1254,16 +1269,19 @@ static int launch_adjoint(AdjArgs a, int64_t cap, const MapParams& mp, double* d
         VCT_LAUNCH_CHECK();
     } else if (a.dphi) {
         const int64_t ncols = D == 3 ? a.g.nc[0] * a.g.nc[1] : a.g.nc[0];
-        VCT_LAUNCH("k_adjoint_maxdeg", k_adjoint_maxdeg, dim3(kMaxDegBlocks), dim3(kMaxDegThreads), 0, s, n, a.row_ptr,
-               a.wide);
-        VCT_LAUNCH_CHECK();
+        a.own_maxdeg = n <= kOwnMaxDeg && !a.wide_cols;
+        if (!a.own_maxdeg) {
+            VCT_LAUNCH("k_adjoint_maxdeg", k_adjoint_maxdeg, dim3(kMaxDegBlocks), dim3(kMaxDegThreads), 0, s, n,
+                       a.row_ptr, a.wide);
+            VCT_LAUNCH_CHECK();
+        }
         VCT_LAUNCH("k_adjoint_push", (k_adjoint_push<D, KERNEL, PushLap>), dim3((unsigned)ncols), dim3(PushLap::kThreads),
                    0, s, a, a.partial, a.wide);
         VCT_LAUNCH_CHECK();
-        if (a.two_only)
+        if (a.wide_cols && a.two_only)
             VCT_LAUNCH("k_adjoint_push (wide)", (k_adjoint_push_wide<D, KERNEL, PushLap, true>), dim3(256),
                        dim3(PushLap::kThreads), 0, s, a, a.partial, a.wide);
-        else
+        else if (a.wide_cols)
             VCT_LAUNCH("k_adjoint_push (wide)", (k_adjoint_push_wide<D, KERNEL, PushLap, false>), dim3(256),
                        dim3(PushLap::kThreads), 0, s, a, a.partial, a.wide);
         VCT_LAUNCH_CHECK();
@@ -1296,8 +1314,9 @@ static int launch_r2(AdjArgs a, int64_t cap, const MapParams& mp, double* gz, do
     VCT_LAUNCH("k_adjoint_push (R2)", (k_adjoint_push<D, KERNEL, PushR2>), dim3((unsigned)ncols), dim3(PushR2::kThreads), 0,
                s, a, a.partial, a.wide);
     VCT_LAUNCH_CHECK();
-    VCT_LAUNCH("k_adjoint_push (R2, wide)", (k_adjoint_push_wide<D, KERNEL, PushR2, false>), dim3(256), dim3(PushR2::kThreads), 0,
-               s, a, a.partial, a.wide);
+    if (a.wide_cols)
+        VCT_LAUNCH("k_adjoint_push (R2, wide)", (k_adjoint_push_wide<D, KERNEL, PushR2, false>), dim3(256), dim3(PushR2::kThreads),
+                   0, s, a, a.partial, a.wide);
     VCT_LAUNCH_CHECK();
     VCT_LAUNCH("k_adjoint_combine", (k_adjoint_combine<D, KERNEL, false>), dim3((unsigned)((n + 255) / 256)),
                dim3(256), 0, s, a, gz);
@@ -1340,16 +1359,29 @@ extern "C" size_t vct_adjoint_workspace_size(int dim, int64_t n, int64_t nnz, in
                         (size_t)(n > 0 ? n : 1) * ns * sizeof(double), (size_t)(wide_list_len(n) + kWideList) * 4});
 }
 
-// The push form is the faster one where the columns' windows fit its
-// accumulators: d/dphi of 2,097,152 particles in 3-D 1.16 ms against 2.25 ms in
-// the transposed form, cubic spline (819,200) 0.44 against 0.61 ms.  Where they
-// do not, it passes over each window several times with the records read from
-// memory: 2-D columns of 512 layers (1,048,576 particles) 0.81 against 0.39 ms,
-// 3-D columns of 60 layers (1,536,000) 2.38 against 1.67 ms.  So a list with a
-// transposed-entry map takes the push form up to a mean window of 85% of the
-// accumulators, which leaves the wider ones room.
-static bool push_fits(int dim, int64_t n, int64_t ncols) {
-    return n * (dim == 3 ? 9 : 3) <= ncols * (kPAcc * 85 / 100);
+// The form of a list with the transposed-entry map.  The push form reads the
+// chunk windows once, in long chains per column; the transposed form writes and
+// reads every entry (16 bytes).  d/dphi in us, transposed / push, one
+// MI355X, by rows and particles:
+//     3-D, rows of        24          31          56           76          102
+//     9,216             28 / 40     28 / 45     31 / 47      33 / 49      39 / 63
+//     50,000            44 / 66     45 / 70     50 / 67      55 / 77      67 / 69
+//     300,000          112 / 201   119 / 182   207 / 196    249 / 200    332 / 240
+//     2,097,152        849 / 1223  927 / 1053  1357 / 1122  1625 / 1146  2131 / 1292
+//     2-D, rows of         9          25
+//     40,000            32 / 47     37 / 61
+//     240,000           70 / 111    82 / 101
+// so the push form takes 3-D lists of rows from 50 and 6,000,000 entries.  Columns
+// beyond kPushWindow are summed in passes, the records read from memory: 2-D
+// columns of 512 layers (1,048,576 particles) 320 / 740, 3-D columns of 60
+// layers (600,000) 640 / 950; a list with more than a quarter of its particles
+// in such columns keeps the transposed form.  Up to kOwnMaxDeg particles, where
+// both take two launches, the push form stays and saves the room for the
+// entries; it is a few us behind there (2,496 particles in 2-D 33 against 28,
+// 10,080 in 3-D 54 against 37).
+static bool push_preferred(const vct_nlist* nl) {
+    if (nl->wide_particles > 1 && (int64_t)(nl->wide_particles - 1) * 4 > nl->n) return false;
+    return nl->n <= kOwnMaxDeg || (nl->dim == 3 && nl->nnz >= 6000000 && nl->nnz >= 50 * nl->n);
 }
 
 // The body of both adjoint entry points; push_only ignores a transposed-entry
@@ -1416,7 +1448,8 @@ static int adjoint_run(const vct_nlist* nl, const double* pos_sorted, const doub
     a.nrows = n_out_rows(dim, out_mask);
     a.wbuf = wbuf; a.rowsum = rowsum; a.partial = partial; a.wide = wide; a.dphi = dphi;
     a.two_only = col_t != nullptr;
-    if (nl->chunk_win && push_fits(dim, n, ncols)) a.col_t = nullptr;
+    if (nl->chunk_win && push_preferred(nl)) a.col_t = nullptr;
+    a.wide_cols = nl->wide_particles != 1;
     const int64_t cap = ncols + n / kChunk + 1;
     // (the allocation-free entry point makes no stream)
     const bool overlap = !push_only && n >= kOverlapMin;
@@ -1510,6 +1543,7 @@ extern "C" int vct_apply_ops_adjoint_r2(const vct_nlist* nl, const double* pos_s
     a.r_yz = dim == 3 ? rh + 5 : -1;
     a.nrows = n_out_rows(dim, out_mask);
     a.partial = partial; a.wide = wide; a.phi = phi; a.dzhat = dzhat;
+    a.wide_cols = nl->wide_particles != 1;
     const int64_t cap = ncols + n / kChunk + 1;
     if (dim == 2)
         st = (kernel == VCT_KERNEL_WENDLAND_C2)

@@ -307,11 +307,12 @@ __global__ void k_scatter(int64_t n, int ncomp, const int32_t* __restrict__ perm
 // ------------------------------------------------------------------ chunk table
 
 // What a search hands to the host: the entries found, whether some window is
-// beyond 16-bit offsets, whether an entry had no transpose, and how many
-// windows are wider than the staged hit words describe.
+// beyond 16-bit offsets, whether an entry had no transpose, how many windows
+// are wider than the staged hit words describe, and the particles of columns
+// wider than kPushWindow.
 struct SearchHead {
     int64_t nnz;
-    int32_t overflow, miss, wide, pad;
+    int32_t overflow, miss, wide, in_wide;
 };
 
 // Chunks of one column: ceil(count / kChunk) pieces of consecutive particles.
@@ -342,11 +343,12 @@ __device__ int64_t z_of(const Grid& g, const int64_t* __restrict__ cs, int64_t c
 // 2-D set has few columns of many chunks (1,048,576 particles: 683 columns of
 // 25 chunks, each chunk two bisections over the column's cells: 86 us with one
 // thread per column, 9 us now; 3-D columns of 5 chunks fill a third of the lanes
-// and take what they took, 10 us).
+// and take what they took, 10 us).  The same lanes add up the columns around,
+// for the particles of wide columns.
 constexpr int kFillLanes = 16;
 template <int D>
 __global__ void k_chunk_fill(Grid g, int64_t n, const int64_t* __restrict__ cs, const int64_t* __restrict__ off,
-                             int32_t* __restrict__ cstart, int4* __restrict__ cinfo) {
+                             int32_t* __restrict__ cstart, int4* __restrict__ cinfo, SearchHead* __restrict__ head) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t c = t / kFillLanes;
     const int lane = (int)(t % kFillLanes);
@@ -357,6 +359,17 @@ __global__ void k_chunk_fill(Grid g, int64_t n, const int64_t* __restrict__ cs, 
     }
     const int64_t nz = grid_nz<D>(g);
     const int64_t a = cs[col_key<D>(g, c, 0)], e = cs[col_key<D>(g, c, nz - 1) + 1];
+    static_assert(kFillLanes >= kMaxRanges, "a lane per column around");
+    {
+        const int64_t ny = D == 3 ? g.nc[1] : 1;
+        const int64_t x = c / ny + (D == 3 ? lane / 3 : lane) - 1, y = c % ny + (D == 3 ? lane % 3 - 1 : 0);
+        const bool in = lane < (D == 3 ? 9 : 3) && x >= 0 && x < g.nc[0] && y >= 0 && y < ny;
+        const int64_t q = x * ny + y;
+        int win = in ? (int)(cs[col_key<D>(g, q, nz - 1) + 1] - cs[col_key<D>(g, q, 0)]) : 0;
+#pragma unroll
+        for (int m = kFillLanes / 2; m >= 1; m >>= 1) win += __shfl_xor(win, m, kWave);
+        if (lane == 0 && win > kPushWindow && e > a) atomicAdd(&head->in_wide, (int)(e - a));
+    }
     int64_t b = off[c] + lane;
     for (int64_t p = a + (int64_t)lane * kChunk; p < e; p += (int64_t)kFillLanes * kChunk, b += kFillLanes) {
         const int64_t q = (p + kChunk < e ? p + kChunk : e) - 1;
@@ -1154,7 +1167,8 @@ static int build_chunks(const vct_nlist* nl, const Grid& g, int32_t* tmp, int64_
     int st = exclusive_scan(tmp, ncols, nl->chunk_off, tiles, s);
     if (st) return st;
     VCT_LAUNCH("k_chunk_fill", (k_chunk_fill<D>), dim3((unsigned)(((ncols + 1) * kFillLanes + 255) / 256)), dim3(256),
-               0, s, g, nl->n, nl->cell_start, nl->chunk_off, nl->chunk_start, reinterpret_cast<int4*>(nl->chunk_info));
+               0, s, g, nl->n, nl->cell_start, nl->chunk_off, nl->chunk_start, reinterpret_cast<int4*>(nl->chunk_info),
+               head);
     VCT_LAUNCH_CHECK();
     return VCT_OK;
 }
@@ -1269,6 +1283,7 @@ extern "C" int vct_neighbors(vct_nlist* nl, const double* pos_sorted, int64_t co
     if ((st = read_head(ws, h, s))) return st;
     *nnz_out = h.nnz;
     nl->nnz = h.nnz;
+    if (!reuse_row_ptr) nl->wide_particles = 1 + h.in_wide;
     if (!want_cols) return VCT_OK;
     if (col_cap < h.nnz) return VCT_E_CAPACITY;
     if (nl->col_t && (!nl->col || h.nnz > INT32_MAX)) return VCT_E_ARG;
@@ -1299,6 +1314,7 @@ extern "C" int vct_neighbors_search(vct_nlist* nl, const double* pos_sorted, int
     if ((st = read_head(ws, h, s))) return st;
     *nnz_out = h.nnz;
     nl->nnz = h.nnz;
+    nl->wide_particles = 1 + h.in_wide;
     *staged = h.overflow ? kStagedOverflow : h.wide ? kStagedFill : kStagedWords;
     return VCT_OK;
 }

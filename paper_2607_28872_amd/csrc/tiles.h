@@ -30,6 +30,12 @@ inline int64_t mean_row(const vct_nlist* nl) {
     return nl->nnz > 0 && nl->n > 0 ? nl->nnz / nl->n : INT32_MAX;
 }
 
+// Window particles of a cell column up to which the adjoint's push form holds
+// the column's records and two-word sums (and R2's records, fields and sums) in
+// LDS.  The search counts the particles of wider columns into
+// nl->wide_particles, as 1 + their number (0: a list without the count).
+constexpr int kPushWindow = 3200;
+
 // Chunk table: chunk b covers sorted particles [start[b], start[b+1]) of
 // column info[b].x, z cells [info[b].y, info[b].z].
 struct ChunkTable {

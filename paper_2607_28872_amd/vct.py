@@ -50,7 +50,7 @@ class vct_map(C.Structure):
 
 
 class vct_nlist(C.Structure):
-    _fields_ = [("dim", C.c_int32), ("reserved", C.c_int32), ("n", C.c_int64), ("ncell", C.c_int64),
+    _fields_ = [("dim", C.c_int32), ("wide_particles", C.c_int32), ("n", C.c_int64), ("ncell", C.c_int64),
                 ("chunk_cap", C.c_int64), ("lo", C.c_double * 3), ("hi", C.c_double * 3), ("R", C.c_double),
                 ("cell_start", C.c_void_p), ("chunk_off", C.c_void_p), ("chunk_start", C.c_void_p),
                 ("chunk_info", C.c_void_p), ("row_ptr", C.c_void_p), ("col", C.c_void_p), ("col16", C.c_void_p),
@@ -600,8 +600,8 @@ class Geometry:
     def adjoint(self, u_sorted, proj=None, want_dtheta=True):
         """dphi (sorted) and dtheta for the cotangent u of the Laplacian; `proj`
         is the FP64 apply output (1, n, n_out) of the field, needed for dtheta.
-        The push form runs unless the cell columns' windows are too wide for it
-        and keep_col left the transposed-entry map."""
+        With keep_col the faster of the push and the transposed form runs, else
+        the push form."""
         import torch
         nt = self.cmap.nterms
         dphi = torch.empty(max(self.n, 1), dtype=torch.float64, device=self.device)

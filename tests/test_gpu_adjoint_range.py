@@ -1,7 +1,7 @@
 """d/dphi of cotangents that range over many orders of magnitude inside a cell
 column: every particle's sum is as accurate as FP64 sums of its own terms,
 however large the others' are, in every form: transposed, push with records in
-LDS, push in passes.  (Columns of over 3,264 window particles keep one word per
+LDS, push in passes.  (Columns of over 3,200 window particles keep one word per
 sum in a list without the transposed-entry map: there the bar is relative to the
 largest.)  The bar is per particle, against sums of weights formed
 here in FP64 from the same state: 64 u of its own sum of |terms|, the terms of
@@ -50,6 +50,8 @@ SETS = {
     "3d": lambda: I.small("sigma3d"),
     "3d-cubic": lambda: I.make_sigma3d(20, 18, 11, 0.05, kernel=CUBIC),
     "3d-tall": lambda: I.make_sigma3d(14, 13, 120, 0.05),   # column windows of 9 x 1,365 particles
+    "3d-tall-small": lambda: I.make_sigma3d(9, 9, 120, 0.05),
+    "2d-tall-small": lambda: I.make_2d(12, 800, 1.0, 0.10),
     "2d": lambda: I.small("bfe2d"),
     "2d-tall": lambda: I.make_2d(40, 700, 1.0, 0.10),       # 3 x 2,154
     "2d-between": lambda: I.make_2d(40, 380, 1.0, 0.10),    # 3 x 1,170: records and one word in LDS, not two
@@ -114,20 +116,23 @@ def test_each_particle_by_its_own_terms(name):
     w = SETS[name]()
     g = vct.Geometry(w.pos, w.vol, w.lo, w.hi, w.R, w.kernel, device=DEV, keep_col=True)
     assert g.moments(w.mapspec, MASK) == vct.VCT_OK
-    wide = columns(g) > 3264
-    assert wide.any() == (name in ("3d-tower", "3d-tall", "2d-tall", "2d-between")), name
+    wide = columns(g) > 3200
+    assert wide.any() == (name == "3d-tower" or "tall" in name or name == "2d-between"), name
     perm = g.perm[: g.n].long().cpu().numpy()
-    win, col_t = g.nl.chunk_win, g.nl.col_t
+    win, col_t, count = g.nl.chunk_win, g.nl.col_t, g.nl.wide_particles
     for kind in ("normal", "depth6", "depth12", "depth30", "gauss", "random", "spikes"):
         uh = cotangent(kind, w, np.random.default_rng(3))[perm]
         u = torch.as_tensor(uh, device=DEV)
         ref, mag = sums(g, w, uh)
-        for form in ("auto", "transposed", "push"):
-            one_word = form == "push" and (columns(g) > 3264).any()
+        for form in ("auto", "transposed", "push", "passes"):   # (passes: wide columns in a list with the map)
+            one_word = form == "push" and (columns(g) > 3200).any()
             if one_word and kind != "normal":
                 continue
             g.nl.chunk_win = None if form == "transposed" else win
             g.nl.col_t = None if form == "push" else col_t
+            if form == "passes" and not (name.endswith("tall-small")):
+                continue
+            g.nl.wide_particles = 0 if form == "passes" else count   # (0: a small set then takes the push form)
             got = g.adjoint(u, want_dtheta=False)[0].cpu().numpy()
             err = np.abs(got - ref)
             if one_word:
@@ -136,4 +141,3 @@ def test_each_particle_by_its_own_terms(name):
             bad = err > 64 * 2.0 ** -53 * mag + 2.0 ** -1000
             assert not bad.any(), (kind, form, int(bad.sum()), float((err / np.maximum(mag, 1e-290)).max()))
             assert np.array_equal(got, g.adjoint(u, want_dtheta=False)[0].cpu().numpy()), (kind, form)
-        g.nl.chunk_win, g.nl.col_t = win, col_t
