@@ -474,7 +474,8 @@ size_t vct_adjoint_workspace_size(int dim, int64_t n, int64_t nnz, int nterms);
  * dtheta [map->nterms] are device outputs; either may be NULL.  A term that
  * is not finite makes the outputs it reaches NaN.  The workspace holds
  * nnz + (1 + 3^(d-1)) n doubles and the reduction partials
- * (vct_adjoint_workspace_size, with nnz = nl->nnz).  When both dphi and
+ * (vct_adjoint_workspace_size, with nnz = nl->nnz; nnz = 0 is enough where the
+ * push form runs).  When both dphi and
  * dtheta of at least 3,000,000 particles are wanted, dtheta is computed on a
  * second stream of the calling host thread (created on its first such call on
  * the device, default priority, kept until the process ends), forked from

@@ -1413,10 +1413,11 @@ static int adjoint_run(const vct_nlist* nl, const double* pos_sorted, const doub
         return VCT_OK;
     }
     if (!pos_sorted || !vol_sorted || !nl->col16 || !state64 || !u) return VCT_E_ARG;
-    const int32_t* col_t = push_only ? nullptr : nl->col_t;
-    if (dphi && !col_t && !nl->chunk_win) return VCT_E_ARG;   // the push form reads the stored windows
+    const bool mapped = !push_only && nl->col_t;
+    const bool push = !mapped || (nl->chunk_win && push_preferred(nl));
+    if (dphi && push && !nl->chunk_win) return VCT_E_ARG;   // the push form reads the stored windows
     if (dtheta && !proj) return VCT_E_ARG;
-    const int64_t nnz = (dphi && col_t) ? nl->nnz : 0;   // the buffer is indexed by entries
+    const int64_t nnz = (dphi && !push) ? nl->nnz : 0;   // the buffer is indexed by entries
     if (nnz < 0) return VCT_E_ARG;
     if (!ws || ws_bytes < vct_adjoint_workspace_size(dim, n, nnz, mp.nterms)) return VCT_E_WORKSPACE;
     Carver cv(ws, ws_bytes);
@@ -1429,7 +1430,7 @@ static int adjoint_run(const vct_nlist* nl, const double* pos_sorted, const doub
     const int64_t ncols = dim == 3 ? g.nc[0] * g.nc[1] : g.nc[0];
     AdjArgs a;
     a.n = n; a.invR = 1.0 / nl->R; a.g = g; a.pos = pos_sorted; a.vol = vol_sorted; a.state = state64; a.u = u;
-    a.proj = proj; a.row_ptr = nl->row_ptr; a.col16 = nl->col16; a.col_t = col_t; a.cs = nl->cell_start;
+    a.proj = proj; a.row_ptr = nl->row_ptr; a.col16 = nl->col16; a.col_t = push ? nullptr : nl->col_t; a.cs = nl->cell_start;
     a.cstart = nl->chunk_start; a.cinfo = reinterpret_cast<const int4*>(nl->chunk_info);
     a.cwin = nl->chunk_win;
     a.nchunks = nl->chunk_off + ncols;
@@ -1447,8 +1448,7 @@ static int adjoint_run(const vct_nlist* nl, const double* pos_sorted, const doub
     }
     a.nrows = n_out_rows(dim, out_mask);
     a.wbuf = wbuf; a.rowsum = rowsum; a.partial = partial; a.wide = wide; a.dphi = dphi;
-    a.two_only = col_t != nullptr;
-    if (nl->chunk_win && push_preferred(nl)) a.col_t = nullptr;
+    a.two_only = mapped;
     a.wide_cols = nl->wide_particles != 1;
     const int64_t cap = ncols + n / kChunk + 1;
     // (the allocation-free entry point makes no stream)

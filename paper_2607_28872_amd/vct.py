@@ -606,7 +606,8 @@ class Geometry:
         nt = self.cmap.nterms
         dphi = torch.empty(max(self.n, 1), dtype=torch.float64, device=self.device)
         dth = torch.empty(max(nt, 1), dtype=torch.float64, device=self.device) if want_dtheta else None
-        ws = _bytes(lib().vct_adjoint_workspace_size(self.dim, self.n, self.nnz, nt), self.device)
+        ws = _bytes(lib().vct_adjoint_workspace_size(self.dim, self.n, self.nnz if self.nl.col_t else 0, nt),
+                    self.device)   # (no room for the entries without the map)
         vct_apply_ops_adjoint(self.nl, self.pos, self.vol, self.kernel, self.state64, self.mask, self.cmap, proj,
                               u_sorted, dphi, dth, ws)
         return dphi[: self.n], (dth[:nt] if dth is not None else None)

@@ -61,3 +61,26 @@ def test_choice(name):
     assert ("k_adjoint_weights" in names) == transposed and ("k_adjoint_push" in names) != transposed
     assert g.nl.wide_particles == 1 + particles_in_wide(g)
     assert ("k_adjoint_push (wide)" in names) == (not transposed and g.nl.wide_particles > 1)
+
+
+@pytest.mark.parametrize("name", ["3d-small", "3d-long-rows", "2d-plain", "2d-tall"])
+def test_workspace_of_the_form(name):
+    """The push form needs no room for the entries, the transposed form does."""
+    make, transposed = SETS[name]
+    w = make()
+    g = vct.Geometry(w.pos, w.vol, w.lo, w.hi, w.R, w.kernel, device=DEV, keep_col=True)
+    g.moments(w.mapspec, MASK)
+    u = torch.ones(g.n, dtype=torch.float64, device=DEV)
+    want = g.adjoint(u, want_dtheta=False)[0]
+    sizes = [vct.lib().vct_adjoint_workspace_size(g.dim, g.n, k, g.cmap.nterms) for k in (0, g.nnz)]
+    for size, enough in ((sizes[0] - 1, False), (sizes[0], not transposed), (sizes[1] - 1, not transposed),
+                         (sizes[1], True)):
+        ws = torch.empty(size, dtype=torch.uint8, device=DEV)
+        dphi = torch.empty(g.n, dtype=torch.float64, device=DEV)
+        args = (g.nl, g.pos, g.vol, g.kernel, g.state64, MASK, g.cmap, None, u, dphi, None, ws)
+        if enough:
+            vct.vct_apply_ops_adjoint(*args)
+            assert torch.equal(dphi, want)
+        else:
+            with pytest.raises(vct.VctError):
+                vct.vct_apply_ops_adjoint(*args)
