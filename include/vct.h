@@ -294,7 +294,7 @@ typedef struct {
 int64_t vct_chunk_capacity(int dim, int64_t n, int64_t ncell);
 
 /* Workspace of vct_neighbors: counts, scan tiles, flags and a staging area of
- * 136 16-bit entries per particle (272 n bytes), and a list of chunks. */
+ * 136 16-bit entries per particle (272 n bytes). */
 size_t vct_neighbors_workspace_size(int64_t n, int64_t ncell);
 
 /* Neighbour lists S_i = { j != i : d2(i,j) < R*R } (Eq. SPH_neighbor_set) of

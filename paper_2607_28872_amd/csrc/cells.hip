@@ -307,8 +307,8 @@ __global__ void k_scatter(int64_t n, int ncomp, const int32_t* __restrict__ perm
 // ------------------------------------------------------------------ chunk table
 
 // What a search hands to the host: the entries found, whether some window is
-// beyond 16-bit offsets, whether an entry had no transpose, how many windows
-// are wider than the staged hit words describe, and the particles of columns
+// beyond 16-bit offsets, whether an entry had no transpose, whether a window is
+// wider than the staged hit words describe, and the particles of columns
 // wider than kPushWindow.
 struct SearchHead {
     int64_t nnz;
@@ -431,15 +431,19 @@ constexpr int kBmWords = kStage / 2;           // hit words per particle slot: w
 // counts and the chunk's hit words, [word][particle] with the chunk's np
 // particles per word, at word p0 * kBmWords of `col16` (the staging buffer),
 // for k_nb_expand to turn into rows; a window wider than kBmWords * 32
-// candidates does not fit there: its chunk goes to the list `wide`, whose
-// counts k_nb_wide adds.  head->overflow flags windows beyond 65535.
+// candidates does not fit there: its chunk is counted only, and head->wide
+// tells the host to run the fill pass.  head->overflow flags windows beyond 65535.
 template <int D, int MODE>
-__device__ __forceinline__ void nb_chunk(uint32_t b, int64_t n, const double* __restrict__ pos, const Grid& g, double R2,
-                                         double sc, const int64_t* __restrict__ cs, const int32_t* __restrict__ cstart,
-                                         const int4* __restrict__ cinfo, int32_t* __restrict__ counts,
-                                         const int64_t* __restrict__ row_ptr, int32_t* __restrict__ col,
-                                         uint16_t* __restrict__ col16, SearchHead* __restrict__ head,
-                                         int32_t* __restrict__ wide, int32_t* __restrict__ win_tab) {
+__global__ __launch_bounds__(kNbThreads, 6) void k_nb_chunk(int64_t n, const double* __restrict__ pos, Grid g,
+                                                            double R2, double sc, const int64_t* __restrict__ cs,
+                                                            const int32_t* __restrict__ cstart,
+                                                            const int4* __restrict__ cinfo,
+                                                            const int64_t* __restrict__ nchunks,
+                                                            int32_t* __restrict__ counts,
+                                                            const int64_t* __restrict__ row_ptr,
+                                                            int32_t* __restrict__ col, uint16_t* __restrict__ col16,
+                                                            SearchHead* __restrict__ head,
+                                                            int32_t* __restrict__ win_tab) {
     constexpr bool FILL = MODE == 1, STAGE = MODE == 2;
     static_assert(kChunk == kWave && kChunk == 16 * kNbWaves, "16 particles to a wave");
     static_assert(kNbSeg % kNbBlock == 0, "segments hold whole blocks");
@@ -448,6 +452,8 @@ __device__ __forceinline__ void nb_chunk(uint32_t b, int64_t n, const double* __
     __shared__ int32_t wcnt[kNbWaves][kChunk];
     __shared__ float wmax[kNbWaves];
     __shared__ WindowT<D> w;
+    uint32_t b;
+    if (!chunk_of_block(nchunks, b)) return;   // uniform over the work-group
     const int64_t p0 = cstart[b], p1 = cstart[b + 1];
     const int np = (int)(p1 - p0);
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), pl = threadIdx.x % kWave;
@@ -486,10 +492,8 @@ __device__ __forceinline__ void nb_chunk(uint32_t b, int64_t n, const double* __
     }
     // the chunk's hit words (MODE 2), np per word; only when they fit its
     // share of the staging buffer (np * kBmWords words)
-    if (STAGE && W > kBmWords * 32) {   // uniform
-        if (threadIdx.x == 0) wide[atomicAdd(&head->wide, 1)] = (int32_t)b;
-        return;
-    }
+    const bool words = STAGE && W <= kBmWords * 32;   // uniform
+    if (STAGE && !words && threadIdx.x == 0) atomicOr(&head->wide, 1);
     uint32_t* bmg = STAGE ? reinterpret_cast<uint32_t*>(col16) + p0 * kBmWords : nullptr;
     int rowpos = 0;                     // entries of the row found so far (MODE 1)
     int mycnt = 0;                      // hits of this lane's words (MODES 0, 2)
@@ -622,7 +626,7 @@ __device__ __forceinline__ void nb_chunk(uint32_t b, int64_t n, const double* __
             if constexpr (FILL) {
                 bm[blk * 4 + quad][cpl] = bits;
             } else {
-                if (STAGE && valid && tb < W)
+                if (words && valid && tb < W)
                     bmg[dcheck((tb / 32) * np + cpl, np * kBmWords, kChkCapacity)] = bits;
                 mycnt += __popc(bits);
             }
@@ -672,41 +676,6 @@ __device__ __forceinline__ void nb_chunk(uint32_t b, int64_t n, const double* __
             for (int v = 0; v < kNbWaves; ++v) c += wcnt[v][pl];
             counts[p0 + pl] = c;
         }
-    }
-}
-
-// One chunk per work-group.
-template <int D, int MODE>
-__global__ __launch_bounds__(kNbThreads, 6) void k_nb_chunk(int64_t n, const double* __restrict__ pos, Grid g,
-                                                            double R2, double sc, const int64_t* __restrict__ cs,
-                                                            const int32_t* __restrict__ cstart,
-                                                            const int4* __restrict__ cinfo,
-                                                            const int64_t* __restrict__ nchunks,
-                                                            int32_t* __restrict__ counts,
-                                                            const int64_t* __restrict__ row_ptr,
-                                                            int32_t* __restrict__ col, uint16_t* __restrict__ col16,
-                                                            SearchHead* __restrict__ head, int32_t* __restrict__ wide,
-                                                            int32_t* __restrict__ win_tab) {
-    uint32_t b;
-    if (!chunk_of_block(nchunks, b)) return;   // uniform over the work-group
-    nb_chunk<D, MODE>(b, n, pos, g, R2, sc, cs, cstart, cinfo, counts, row_ptr, col, col16, head, wide, win_tab);
-}
-
-// The counts of the listed wide chunks, taken in turn by a fixed grid (none at
-// the supports in use: the launch then ends at once).
-constexpr int kWideBlocks = 512;
-template <int D>
-__global__ __launch_bounds__(kNbThreads) void k_nb_wide(int64_t n, const double* __restrict__ pos, Grid g, double R2,
-                                                        double sc, const int64_t* __restrict__ cs,
-                                                        const int32_t* __restrict__ cstart,
-                                                        const int4* __restrict__ cinfo, int32_t* __restrict__ counts,
-                                                        SearchHead* __restrict__ head,
-                                                        const int32_t* __restrict__ wide) {
-    const int cnt = head->wide;
-    for (int k = blockIdx.x; k < cnt; k += gridDim.x) {
-        nb_chunk<D, 0>((uint32_t)wide[k], n, pos, g, R2, sc, cs, cstart, cinfo, counts, nullptr, nullptr, nullptr, head,
-                       nullptr, nullptr);
-        __syncthreads();   // the chunk's LDS is consumed
     }
 }
 
@@ -954,7 +923,7 @@ extern "C" int64_t vct_chunk_capacity(int dim, int64_t n, int64_t ncell) {
 // Workspace without the staging buffer (enough for the two-pass search).
 static size_t nb_ws_base(int64_t n, int64_t ncell) {
     const int64_t m = n > ncell ? n : ncell;
-    return aligned_sum({(size_t)m * 4, scan_ws_bytes(m), sizeof(SearchHead), (size_t)(n / kChunk + ncell + 1) * 4});
+    return aligned_sum({(size_t)m * 4, scan_ws_bytes(m), sizeof(SearchHead)});
 }
 
 extern "C" size_t vct_neighbors_workspace_size(int64_t n, int64_t ncell) {
@@ -1142,7 +1111,6 @@ struct NbWork {
     int32_t* counts;
     int64_t* tiles;
     SearchHead* head;
-    int32_t* wide;         // chunks whose windows are wider than the hit words
     uint16_t* staged;      // hit words
     uint16_t* range_pos;   // per row: where each column's part begins
     NbWork(const vct_nlist* nl, void* p, size_t bytes) {
@@ -1151,7 +1119,6 @@ struct NbWork {
         counts = cv.take<int32_t>((size_t)m);
         tiles = cv.take<int64_t>(scan_ws_bytes(m) / 8);
         head = cv.take<SearchHead>(1);
-        wide = cv.take<int32_t>((size_t)(n / kChunk + nl->ncell + 1));
         staged = cv.take<uint16_t>((size_t)(n > 0 ? n : 1) * kStage);
         range_pos = cv.take<uint16_t>((size_t)(n > 0 ? n : 1) * (kMaxRanges - 1));
     }
@@ -1183,14 +1150,8 @@ static int launch_nb(const vct_nlist* nl, const double* pos, const Grid& g, cons
     VCT_LAUNCH(name, (k_nb_chunk<D, MODE>), dim3((unsigned)cap), dim3(kNbThreads), 0, s, nl->n, pos, g,
                R2, 1.0 / sqrt(R2), nl->cell_start, nl->chunk_start, cinfo, nl->chunk_off + ncols,
                MODE == 1 ? nullptr : ws.counts, nl->row_ptr, MODE == 1 ? nl->col : nullptr,
-               MODE == 1 ? nl->col16 : ws.staged, ws.head, ws.wide, nl->chunk_win);
+               MODE == 1 ? nl->col16 : ws.staged, ws.head, nl->chunk_win);
     VCT_LAUNCH_CHECK();
-    if (MODE == 2) {
-        VCT_LAUNCH("k_nb_chunk (count)", (k_nb_wide<D>), dim3((unsigned)(cap < kWideBlocks ? cap : kWideBlocks)),
-                   dim3(kNbThreads), 0, s, nl->n, pos, g, R2, 1.0 / sqrt(R2), nl->cell_start, nl->chunk_start, cinfo,
-                   ws.counts, ws.head, ws.wide);
-        VCT_LAUNCH_CHECK();
-    }
     return VCT_OK;
 }
 
