@@ -314,13 +314,24 @@ struct SearchHead {
     int64_t nnz;
     int32_t overflow, miss, wide, in_wide;
 };
+// After the head, kSymSlots sums of the transposed-entry map (see k_col_transpose),
+// cleared with the head: together zero if the rows are symmetric.
+constexpr int kSymSlots = 256;
+struct SearchState {
+    SearchHead head;
+    unsigned long long sym[kSymSlots];
+};
+__device__ __forceinline__ void clear_state(SearchState* st, int64_t nnz, int64_t t) {
+    if (t == 0) st->head = SearchHead{nnz, 0, 0, 0, 0};
+    if (t < kSymSlots) st->sym[t] = 0ull;
+}
 
 // Chunks of one column: ceil(count / kChunk) pieces of consecutive particles.
 template <int D>
 __global__ void k_chunk_count(Grid g, const int64_t* __restrict__ cs, int32_t* __restrict__ nch,
-                              SearchHead* __restrict__ head) {
+                              SearchState* __restrict__ st) {
     const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (c == 0) *head = SearchHead{0, 0, 0, 0, 0};   // for the search that follows
+    clear_state(st, 0, c);   // for the search that follows
     if (c >= grid_ncols<D>(g)) return;
     const int64_t nz = grid_nz<D>(g);
     const int64_t cnt = cs[col_key<D>(g, c, nz - 1) + 1] - cs[col_key<D>(g, c, 0)];
@@ -923,7 +934,7 @@ extern "C" int64_t vct_chunk_capacity(int dim, int64_t n, int64_t ncell) {
 // Workspace without the staging buffer (enough for the two-pass search).
 static size_t nb_ws_base(int64_t n, int64_t ncell) {
     const int64_t m = n > ncell ? n : ncell;
-    return aligned_sum({(size_t)m * 4, scan_ws_bytes(m), sizeof(SearchHead)});
+    return aligned_sum({(size_t)m * 4, scan_ws_bytes(m), sizeof(SearchState)});
 }
 
 extern "C" size_t vct_neighbors_workspace_size(int64_t n, int64_t ncell) {
@@ -950,9 +961,25 @@ namespace vct {
 // Bound by the scattered reads of those confirmations and by the map's stores:
 // with a binary search per candidate, nine reads instead of one or two, 0.80
 // ms, and one search per entry, each lane searching 16 at a time, 2.66 ms, for
-// 1,049,800 particles in 3-D (104M entries); now 0.48 ms.  2-D, 1,048,576
+// 1,049,800 particles in 3-D (104M entries); now 0.52 ms (0.48 without the check below).  2-D, 1,048,576
 // particles: 0.43 -> 0.12 ms.  Windows beyond kTWin candidates are taken in
 // parts.
+// Those reads confirm the first entry of every run; that each of the others has
+// its transpose too is confirmed over the whole set: the sum of
+// a(i) b(j) - b(i) a(j) over the entries (i, j), a and b two hash values of 32
+// bits (multipliers from the golden ratio and the roots of 2 and 3), in 64-bit integers is zero if every entry has its transpose, and with
+// an entry that has none it is zero by a chance of about 2^-32.  (Reading every
+// entry of the runs as well takes 0.35 ms more.)
+struct SymPair {
+    uint64_t a, b;
+};
+__device__ __forceinline__ SymPair sym_pair(int32_t j) {
+    uint32_t x = (uint32_t)j * 0x9e3779b9u;
+    x ^= x >> 15;
+    x *= 0x6a09e667u;
+    const uint32_t y = (x ^ x >> 12) * 0xbb67ae85u;
+    return {x, y ^ y >> 15};
+}
 constexpr int kTThreads = 512;
 constexpr int kTWin = 1536;   // candidates per part (18 KB of LDS)
 template <int D, bool OFFS>
@@ -965,7 +992,7 @@ __global__ __launch_bounds__(kTThreads) void k_col_transpose(Grid g, const int64
                                                              const int32_t* __restrict__ col,
                                                              const uint16_t* __restrict__ col16,
                                                              const uint16_t* __restrict__ range_pos,
-                                                             int32_t* __restrict__ col_t, int32_t* __restrict__ miss) {
+                                                             int32_t* __restrict__ col_t, SearchState* __restrict__ st) {
     constexpr int kLanes = kTThreads / kChunk;   // lanes per row
     // row entries per lane held in registers: the rows of R = 3 d0 (2-D: with
     // 14 slots, mostly empty, 0.142 instead of 0.121 ms at 1,048,576 particles)
@@ -1030,12 +1057,25 @@ __global__ __launch_bounds__(kTThreads) void k_col_transpose(Grid g, const int64
         tt[s] = e < re ? offset_of(e) : -1;
     }
     const int64_t tail = rb + lane + (int64_t)kLanes * kTSlots;
+    bool bad = false;   // an entry that is not in the window, or a run that is not in its place
+#pragma unroll
+    for (int s = 0; s < kTSlots; ++s) bad = bad || (rb + lane + (int64_t)kLanes * s < re && (unsigned)tt[s] >= (unsigned)W);
+    for (int64_t e = tail; e < re; e += kLanes) bad = bad || (unsigned)offset_of(e) >= (unsigned)W;
+    uint64_t sa = 0, sb = 0;   // sums of a(j) and b(j) over the lane's entries
     for (int s0 = 0; s0 < W; s0 += kTWin) {
         const int sW = W - s0 < kTWin ? W - s0 : kTWin;
-        for (int t = threadIdx.x; t < sW; t += kTThreads) mask[0][t] = mask[1][t] = 0u;
+        for (int t = threadIdx.x; t < sW; t += kTThreads) {
+            mask[0][t] = mask[1][t] = 0u;
+            base[t] = (int32_t)window_global<D>(w, s0 + t);   // the candidate j, until its run is found
+        }
         __syncthreads();
         auto mark = [&](int t) {
-            if ((unsigned)t < (unsigned)sW) atomicOr(&mask[pl >> 5][t], 1u << (pl & 31));
+            if ((unsigned)t < (unsigned)sW) {
+                atomicOr(&mask[pl >> 5][t], 1u << (pl & 31));
+                const SymPair h = sym_pair(base[t]);
+                sa += h.a;
+                sb += h.b;
+            }
         };
 #pragma unroll
         for (int s = 0; s < kTSlots; ++s) mark(tt[s] - s0);
@@ -1048,7 +1088,7 @@ __global__ __launch_bounds__(kTThreads) void k_col_transpose(Grid g, const int64
 #pragma unroll
             for (int q = 1; q < kMaxRanges; ++q)
                 if (q < w.nr && s0 + t >= w.off[q]) r = q;
-            const int64_t j = w.gstart[r] + (s0 + t - w.off[r]);
+            const int64_t j = base[t];
             int64_t lo = row_ptr[j], hi = row_ptr[j + 1];
             if (range_pos) {   // the part of row j in the chunk's column
                 const int own = s_own[r];
@@ -1075,7 +1115,7 @@ __global__ __launch_bounds__(kTThreads) void k_col_transpose(Grid g, const int64
                 }
             }
             const bool ok = at + cnt <= hi;
-            if (!ok) atomicOr(miss, 1);
+            bad = bad || !ok;
             base[t] = ok ? (int32_t)at : -1;
         }
         __syncthreads();
@@ -1091,6 +1131,17 @@ __global__ __launch_bounds__(kTThreads) void k_col_transpose(Grid g, const int64
         for (int s = 0; s < kTSlots; ++s) store(rb + lane + (int64_t)kLanes * s, tt[s] - s0);
         for (int64_t e = tail; e < re; e += kLanes) store(e, offset_of(e) - s0);
         __syncthreads();   // the part's masks are consumed
+    }
+    if (bad) atomicOr(&st->head.miss, 1);
+    const SymPair hi = sym_pair((int32_t)(p0 + pl));
+    unsigned long long sum = hi.a * sb - hi.b * sa;
+    for (int m = 1; m < kWave; m <<= 1) sum += __shfl_xor(sum, m, kWave);
+    unsigned long long* part = reinterpret_cast<unsigned long long*>(mask);
+    if (threadIdx.x % kWave == 0) part[threadIdx.x / kWave] = sum;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int v = 1; v < kTThreads / kWave; ++v) sum += part[v];
+        atomicAdd(&st->sym[b % kSymSlots], sum);
     }
 }
 
@@ -1110,6 +1161,7 @@ int nlist_check(const vct_nlist* nl, Grid& g) {
 struct NbWork {
     int32_t* counts;
     int64_t* tiles;
+    SearchState* state;
     SearchHead* head;
     uint16_t* staged;      // hit words
     uint16_t* range_pos;   // per row: where each column's part begins
@@ -1118,24 +1170,25 @@ struct NbWork {
         Carver cv(p, bytes);
         counts = cv.take<int32_t>((size_t)m);
         tiles = cv.take<int64_t>(scan_ws_bytes(m) / 8);
-        head = cv.take<SearchHead>(1);
+        state = cv.take<SearchState>(1);
+        head = &state->head;
         staged = cv.take<uint16_t>((size_t)(n > 0 ? n : 1) * kStage);
         range_pos = cv.take<uint16_t>((size_t)(n > 0 ? n : 1) * (kMaxRanges - 1));
     }
 };
 
 template <int D>
-static int build_chunks(const vct_nlist* nl, const Grid& g, int32_t* tmp, int64_t* tiles, SearchHead* head,
-                        hipStream_t s) {
+static int build_chunks(const vct_nlist* nl, const Grid& g, const NbWork& ws, hipStream_t s) {
+    int32_t* tmp = ws.counts;
     const int64_t ncols = D == 3 ? g.nc[0] * g.nc[1] : g.nc[0];
     VCT_LAUNCH("k_chunk_count", (k_chunk_count<D>), dim3((unsigned)((ncols + 255) / 256)), dim3(256), 0, s, g,
-               nl->cell_start, tmp, head);
+               nl->cell_start, tmp, ws.state);
     VCT_LAUNCH_CHECK();
-    int st = exclusive_scan(tmp, ncols, nl->chunk_off, tiles, s);
+    int st = exclusive_scan(tmp, ncols, nl->chunk_off, ws.tiles, s);
     if (st) return st;
     VCT_LAUNCH("k_chunk_fill", (k_chunk_fill<D>), dim3((unsigned)(((ncols + 1) * kFillLanes + 255) / 256)), dim3(256),
                0, s, g, nl->n, nl->cell_start, nl->chunk_off, nl->chunk_start, reinterpret_cast<int4*>(nl->chunk_info),
-               head);
+               ws.head);
     VCT_LAUNCH_CHECK();
     return VCT_OK;
 }
@@ -1178,7 +1231,7 @@ static int nb_check(const vct_nlist* nl, const double* pos, const void* ws, size
 template <int D>
 static int nb_search(const vct_nlist* nl, const double* pos, const Grid& g, const NbWork& ws, bool stage,
                      hipStream_t s) {
-    int st = build_chunks<D>(nl, g, ws.counts, ws.tiles, ws.head, s);
+    int st = build_chunks<D>(nl, g, ws, s);
     if (st) return st;
     if (nl->n > 0) {
         st = stage ? launch_nb<D, 2>(nl, pos, g, ws, s) : launch_nb<D, 0>(nl, pos, g, ws, s);
@@ -1202,11 +1255,11 @@ static int nb_rows(const vct_nlist* nl, const double* pos, const Grid& g, const 
     if (nl->col16)
         VCT_LAUNCH("k_col_transpose", (k_col_transpose<D, true>), grid, dim3(kTThreads), 0, s, g, nl->cell_start,
                    nl->chunk_start, cinfo, nl->chunk_off + ncols, nl->chunk_win, nl->row_ptr, nl->col, nl->col16,
-                   range_pos, nl->col_t, &ws.head->miss);
+                   range_pos, nl->col_t, ws.state);
     else
         VCT_LAUNCH("k_col_transpose", (k_col_transpose<D, false>), grid, dim3(kTThreads), 0, s, g, nl->cell_start,
                    nl->chunk_start, cinfo, nl->chunk_off + ncols, nl->chunk_win, nl->row_ptr, nl->col, nl->col16,
-                   range_pos, nl->col_t, &ws.head->miss);
+                   range_pos, nl->col_t, ws.state);
     VCT_LAUNCH_CHECK();
     return VCT_OK;
 }
@@ -1217,7 +1270,19 @@ static int read_head(const NbWork& ws, SearchHead& h, hipStream_t s) {
     return VCT_OK;
 }
 
-__global__ void k_head_given(SearchHead* head, const int64_t* nnz) { *head = SearchHead{*nnz, 0, 0, 0, 0}; }
+__global__ void k_head_given(SearchState* st, const int64_t* nnz) { clear_state(st, *nnz, threadIdx.x); }
+
+// The end of a call that wrote the transposed-entry map: whether every entry
+// has its transpose, and the head.
+static int read_transposed(const NbWork& ws, SearchHead& h, hipStream_t s) {
+    SearchState st;
+    VCT_HIP_CHECK(hipMemcpyAsync(&st, ws.state, sizeof(st), hipMemcpyDeviceToHost, s));
+    VCT_HIP_CHECK(hipStreamSynchronize(s));
+    h = st.head;
+    unsigned long long sum = 0;
+    for (unsigned long long v : st.sym) sum += v;
+    return h.overflow ? VCT_E_WINDOW : h.miss || sum ? VCT_E_HIP : VCT_OK;
+}
 
 extern "C" int vct_neighbors(vct_nlist* nl, const double* pos_sorted, int64_t col_cap, int64_t* nnz_out,
                              int reuse_row_ptr, void* ws_p, size_t ws_bytes, void* stream) {
@@ -1233,7 +1298,7 @@ extern "C" int vct_neighbors(vct_nlist* nl, const double* pos_sorted, int64_t co
     const NbWork ws(nl, ws_p, ws_bytes);
     const bool want_cols = nl->col || nl->col16;
     if (reuse_row_ptr) {
-        VCT_LAUNCH("k_head_given", k_head_given, dim3(1), dim3(1), 0, s, ws.head, nl->row_ptr + nl->n);
+        VCT_LAUNCH("k_head_given", k_head_given, dim3(1), dim3(kSymSlots), 0, s, ws.state, nl->row_ptr + nl->n);
         VCT_LAUNCH_CHECK();
     } else {
         st = nl->dim == 2 ? nb_search<2>(nl, pos_sorted, g, ws, want_cols, s)
@@ -1252,9 +1317,9 @@ extern "C" int vct_neighbors(vct_nlist* nl, const double* pos_sorted, int64_t co
     const bool words = !reuse_row_ptr && h.wide == 0;
     st = nl->dim == 2 ? nb_rows<2>(nl, pos_sorted, g, ws, words, s) : nb_rows<3>(nl, pos_sorted, g, ws, words, s);
     if (st) return st;
+    if (nl->col_t) return read_transposed(ws, h, s);
     if ((st = read_head(ws, h, s))) return st;
-    if (h.overflow) return VCT_E_WINDOW;
-    return h.miss ? VCT_E_HIP : VCT_OK;
+    return h.overflow ? VCT_E_WINDOW : VCT_OK;
 }
 
 // what vct_neighbors_search left in the workspace
@@ -1295,7 +1360,6 @@ extern "C" int vct_neighbors_rows(const vct_nlist* nl, const double* pos_sorted,
     const bool words = staged == kStagedWords;
     st = nl->dim == 2 ? nb_rows<2>(nl, pos_sorted, g, ws, words, s) : nb_rows<3>(nl, pos_sorted, g, ws, words, s);
     if (st || !nl->col_t) return st;
-    SearchHead h;   // the transposed-entry map reports entries without a transpose
-    if ((st = read_head(ws, h, s))) return st;
-    return h.miss ? VCT_E_HIP : VCT_OK;
+    SearchHead h;
+    return read_transposed(ws, h, s);
 }
