@@ -279,6 +279,14 @@ __device__ __forceinline__ void turn_over() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// sqrt(x), x >= 0, from the hardware's estimate y of 1/sqrt(x): g = x y
+// corrected by (x - g^2) y / 2, whose factors stay in range for every x (y^2
+// does not below 2^-1022, the square of a distance of 1e-154).
+__device__ __forceinline__ double pair_distance(double x) {
+    const double y = __builtin_amdgcn_rsq(x), g = x * y;
+    return x > 0.0 ? fma(fma(-g, g, x), 0.5 * y, g) : 0.0;
+}
+
 // The part of a row's exchanges that no value enters.  Entries 2 lane and
 // 2 lane + 1 of up to 128 are the lane's: their weights c (0 past the row's
 // end) and LDS places jl (-1 there), and the slopes of the scan over the lanes'
@@ -460,7 +468,7 @@ __device__ __forceinline__ void jbar_cell_shared(const JbarArgs& A, int p0, int 
                 r2 += d * d;
             }
             m.jl[s] = fjl[s];
-            const double c = cvr * (A.re - vsqrt(r2));
+            const double c = cvr * (A.re - pair_distance(r2));
             m.c[s] = m.jl[s] >= 0 ? c : 0.0;
         }
         row_slopes(m);
