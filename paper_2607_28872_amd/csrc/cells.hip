@@ -1200,6 +1200,8 @@ static int launch_nb(const vct_nlist* nl, const double* pos, const Grid& g, cons
     const char* name = MODE == 0 ? "k_nb_chunk (count)" : MODE == 1 ? "k_nb_chunk (fill)" : "k_nb_chunk (stage)";
     const int4* cinfo = reinterpret_cast<const int4*>(nl->chunk_info);
     const double R2 = nl->R * nl->R;
+    // (the staging search is the counting one too: timed under both names)
+    const LaunchTimer counted(MODE == 2 ? "k_nb_chunk (count)" : nullptr, s);
     VCT_LAUNCH(name, (k_nb_chunk<D, MODE>), dim3((unsigned)cap), dim3(kNbThreads), 0, s, nl->n, pos, g,
                R2, 1.0 / sqrt(R2), nl->cell_start, nl->chunk_start, cinfo, nl->chunk_off + ncols,
                MODE == 1 ? nullptr : ws.counts, nl->row_ptr, MODE == 1 ? nl->col : nullptr,

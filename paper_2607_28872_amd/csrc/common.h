@@ -94,7 +94,7 @@ struct LaunchTimer {
     int rec = -1;
     hipStream_t s;
     LaunchTimer(const char* name, hipStream_t st) : s(st) {
-        if (timing_on()) rec = timing_begin(name, st);
+        if (name && timing_on()) rec = timing_begin(name, st);
     }
     ~LaunchTimer() {
         if (rec >= 0) timing_end(rec, s);
