@@ -284,7 +284,10 @@ typedef struct {
     uint16_t* col16;        /* [nnz] or NULL; 16-byte aligned */
     int32_t* col_t;         /* [nnz] or NULL: for entry e = (i, j) of row i, the position of
                                the entry (j, i) in row j (needs col); read by the adjoint */
-    int64_t nnz;            /* written by vct_neighbors (the total of row_ptr) */
+    int64_t nnz;            /* written by vct_neighbors (the total of row_ptr); the mean row
+                               nnz / n selects the launch shape of the calls that sweep rows
+                               (0: the one for long rows): their FP64 sums then differ in the
+                               last digits, VCT_MIXED and VCT_MIXED_S64 results do not */
     int32_t* chunk_win;     /* [chunk_cap][32] or NULL: every chunk's window (its column
                                ranges), written by vct_neighbors and read by the other
                                calls instead of recomputing it from cell_start */
@@ -571,7 +574,9 @@ size_t vct_ppe_workspace_size(int dim, int64_t n, uint32_t out_mask);
  * (dirichlet may be NULL), by BiCGSTAB with the Jacobi preconditioner on the
  * right (diagonal: the coefficient of p_i in row i).  The operator is the FP64
  * Laplacian of vct_apply_ops on the fixed state; its coefficients are formed
- * once and kept in the workspace where they fit, or in every product.  `p`
+ * once and kept in the workspace where they fit (the product is then the sum of
+ * W_ij (p_j - p_i) in one pass), or in every product (by the two passes of
+ * vct_apply_ops): the same operator, rounded differently.  `p`
  * holds the initial guess on entry and the solution on return.  Stops when
  * ||r|| <= tol ||rhs|| (the recurrence residual) or after max_iter
  * iterations.  The scalars of the method stay on the device; every inner

@@ -6,16 +6,17 @@
 // (P_a,i, P_s,i the first- and second-order parts of particle i's Laplacian
 // row of the state), the field cotangent is
 //   dphi_k = sum_{i in S_k} u_i W_ik  -  sum_{j in S_k} u_k W_kj .
-// Both forms below evaluate each weight once, with particle i's own state in
-// registers, and sum without floating-point atomics, so every run gives the
+// Both forms below evaluate each weight once (but for a few sums of the push
+// form), with particle i's own state in registers, and sum without floating-point atomics, so every run gives the
 // same bits:
 //   transposed form (needs the transposed-entry map col_t): every particle i
 //     writes u_i W_ij at the transposed position of its entries and its row
 //     sum to a second buffer; every particle k then sums its row of the first
 //     buffer in row order and subtracts its row sum;
-//   push form (no map): every particle adds u_i W_ij to the accumulator of j
-//     in LDS as an exact integer (below), per cell column, and the columns'
-//     totals are summed per particle in a fixed order.  The bathymetry
+//   push form (without the map, or where it is the faster one: push_preferred):
+//     every particle adds u_i W_ij to the accumulator of j in LDS as exact
+//     integers (below), per cell column, and the columns' totals are summed per
+//     particle in a fixed order.  The bathymetry
 //     adjoint with physical positions fixed (reading R2, below) sums its
 //     position terms the same way.
 //
@@ -734,9 +735,10 @@ __device__ __forceinline__ void push_column(const AdjArgs& A, double* __restrict
     const double Mb = vmax * 1.0625 * bmax;   // the factor covers |r~| rounded above 1
     // terms reaching one accumulator: at most one per neighbour of its particle
     const double nterm = (double)deg;
-    // R2: two bits fewer, the scale its results have always been rounded at
-    // (dtheta is a sum over all particles that cancels to as little as 1e-5 of
-    // its terms, so another scale shows in it at parts in 1e9)
+    // R2: two bits fewer than there is room for.  dtheta is a sum over all
+    // particles that cancels to as little as 1e-5 of its terms, so a change of
+    // scale moves it by parts in 1e9; its error against 64 bits, 8e-13 (3e-13
+    // with the two bits), does not need them, and its results stay what they were.
     const int top = OP::kR2 ? 60 : 62;
     const int bl = ilogb(fmax(nterm, 1.0)) + 1;   // bitlen(d_max)
     const int k = (Mb > 0.0 && Mb <= 1.7976931348623157e308) ? top - ilogb(Mb) - bl : 0;

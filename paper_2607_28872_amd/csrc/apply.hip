@@ -265,8 +265,9 @@ __device__ __forceinline__ void apply_chunk_global(const ApplyArgs<S>& A, const 
             T vj, r[D], q2, vc, iq4;
             double dx[D];
             fetch(A.col16[e], q, vj);
-            // (the short classes weigh as with the window in LDS: where a
-            // chunk's records are read from does not show in its results)
+            // (the short classes weigh as with the window in LDS: where a chunk's
+            // records are read from does not show in the mixed form's results; the
+            // FP64 form's first pass is in FP32 there and in FP64 here)
             if constexpr (C == kLongRows) pair_geom<D, KERNEL, T>(q, vj, xi, invR, dx, r, q2, vc);
             else pair_geom<D, KERNEL, T, Scaled<T>::value>(q, vj, xi, invR, dx, r, q2, vc, &iq4);
             const T wgt = vc * T(q.w - phi_i);

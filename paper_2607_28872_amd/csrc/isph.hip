@@ -75,7 +75,8 @@ struct ZeroRec {
 // them the compiler keeps the mapping's uniform products in registers across
 // the sweeps and spills them, 2 ms.)  1,065,547 particles in 3-D, one field: 0.75 -> 0.46
 // ms, 1,048,576 in 2-D 0.32 -> 0.096 ms; bound by latency (staging, then one
-// wave's mapping) with two work-groups on a CU.
+// wave's mapping) with two work-groups on a CU: vector instructions are issued in
+// 56% of the cycles (46% in k_grad_sum), waves wait 48% (53%) of theirs.
 template <int D, int KERNEL, int C>
 __global__ __launch_bounds__((kChunk * RowShape<C>::lanes), RowShape<C>::waves) void k_ops0(ZeroArgs A, MapParams mp) {
     using Dm = Dims<D>;

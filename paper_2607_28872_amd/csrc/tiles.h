@@ -19,11 +19,12 @@ namespace vct {
 constexpr int kChunk = 64;        // particles per chunk
 constexpr int kMaxRanges = 9;     // 3 x 3 columns in 3-D, 3 in 2-D
 
-// Mean row length up to which a set takes the kernels' short-row shapes: 28 and
-// 64 register slots per row (2-D, 3-D), a little above the mean rows of the
-// supports in use that fit them (2-D: 26 at R = 3 d0, 20 at 2.4 d0; 3-D: 57 at
-// 2.4 d0); the next supports up (3-D: 103 at 3 d0) would run most of each row
-// outside the slots.
+// Mean row length up to which a set takes the kernels' short-row shapes, whose
+// register slots hold 32 entries of a row in 2-D (the FP64 apply 28) and 64 in
+// 3-D: above the mean rows of the supports in use that fit them (2-D: 26 at
+// R = 3 d0, 20 at 2.4 d0; 3-D: 57 at 2.4 d0).  The next supports up (3-D: 103 at
+// 3 d0) would run most of each row outside the slots; at mean rows of 29 and 30
+// the FP64 apply's last entries take the loop after them.
 template <int D> constexpr int64_t short_row() { return D == 2 ? 30 : 62; }
 // The mean row length the neighbour search left in the list (nnz unset: long).
 inline int64_t mean_row(const vct_nlist* nl) {
