@@ -463,9 +463,9 @@ size_t vct_adjoint_workspace_size(int dim, int64_t n, int64_t nnz, int nterms);
  *     slot order; a particle for which the second rounding may exceed 2^-53 of
  *     its total in a column takes its sum in FP64 from its neighbours' states
  *     instead.  So each entry of dphi is as accurate as an FP64 sum of its own
- *     terms.  (Without nl->col_t, columns of more than 3200 window particles
- *     sum the first integer alone: their entries are accurate to about
- *     2^-62 x longest row x M.)  The row sum u_i sum_j W_ij is subtracted.
+ *     terms.  (Lists of more than 10,240 particles without nl->col_t sum the first
+ *     integer alone: their entries are accurate to about 2^-62 x longest row x
+ *     M.)  The row sum u_i sum_j W_ij is subtracted.
  * dtheta: per particle from D^ phi_i, reduced in a fixed order.
  * `state64` must come from vct_moments (or vct_moments_resolve) with out_mask
  * containing VCT_OUT_LAP and either VCT_OUT_PZ or both VCT_OUT_PGRAD and

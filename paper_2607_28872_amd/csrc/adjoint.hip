@@ -66,7 +66,7 @@ struct AdjArgs {
     int r_gz, r_zz, r_xz, r_yz;   // rows of dz^, z^z^, x^z^, y^z^ (-1 in 2-D) in proj
     double* partial;   // [3^(d-1)][n] per-source-column totals of the push form
     int32_t* wide;     // [kWideList + n / 256 + 2]: see kWideCount, kWideMaxDeg, kWideList
-    bool two_only;     // push form: every column in two-word sums
+    bool two;          // push form: two-word sums
     bool wide_cols;    // there may be columns of more than kPushWindow window particles
     bool own_maxdeg;   // push form: every column finds the longest row of the (small) set itself
     double* wbuf;      // [nnz]: u_i W_ij at the transposed position
@@ -514,8 +514,9 @@ __global__ __launch_bounds__(kAThreads, 2) void k_r2_prep(AdjArgs A, double* __r
 // neighbours' states (few particles of an ordinary field, whose only entries
 // in a column lie at the very edge of the support).  Every particle's sum is
 // then as accurate as FP64 sums of the same terms, whatever the others' are.
-// (R2 keeps one word; so do columns of more than kPTwo window particles of a
-// list without the transposed-entry map.)  The gradient step of 2,097,152
+// R2 keeps one word, and so do lists of more than kOwnMaxDeg particles without
+// the transposed-entry map, which have no other form: their sums are accurate to
+// one FP64 rounding of the column's largest.  The gradient step of 2,097,152
 // particles in 3-D takes 5.97 ms with the second word, 5.81 ms without.
 //
 // Bound: with r~ = r/R and q = |r~| < 1 inside the support, P_a . r~ <= |P_a| q,
@@ -594,12 +595,12 @@ __device__ __forceinline__ void push_column(const AdjArgs& A, double* __restrict
     constexpr int kThreads = OP::kThreads;
     constexpr int kW = kThreads / kWave;
     constexpr int kAcc = OP::kAcc;
-    // the accumulators (8 bytes; two words: kTwoCap more of them), then FAST the
-    // records (32 bytes; R2: and the field's values)
+    // the accumulators (8 bytes; two words: as many more), then FAST the records
+    // (32 bytes; R2: and the field's values)
     constexpr bool kTwo = TWO;
     constexpr int kTwoCap = FAST ? kPTwo : kAcc;
-    constexpr int kBytes1 = kAcc * (FAST ? (OP::kR2 ? 48 : 40) : 8), kBytes2 = kTwo ? kTwoCap * (FAST ? 48 : 16) : 0;
-    __shared__ __align__(32) unsigned char s_mem[kBytes1 > kBytes2 ? kBytes1 : kBytes2];
+    constexpr int kBytes = kTwo ? kTwoCap * (FAST ? 48 : 16) : kAcc * (FAST ? (OP::kR2 ? 48 : 40) : 8);
+    __shared__ __align__(32) unsigned char s_mem[kBytes];
     unsigned long long* const s_acc = reinterpret_cast<unsigned long long*>(s_mem);
     unsigned long long* const s_low = s_acc + kTwoCap;
     __shared__ uint32_t s_nan[kAcc / 32];
@@ -634,12 +635,11 @@ __device__ __forceinline__ void push_column(const AdjArgs& A, double* __restrict
     }
     __syncthreads();
     const int Wc = s_cw.off[s_cw.nr];
-    if (FAST && Wc > (kTwo && A.two_only ? kTwoCap : kAcc)) {   // uniform: left to the wide pass
+    if (FAST && Wc > (kTwo ? kTwoCap : kAcc)) {   // uniform: left to the wide pass
         if (tid == 0) wide[kWideList + atomicAdd(&wide[kWideCount], 1)] = (int32_t)c;
         return;
     }
-    const bool two = kTwo && (!FAST || Wc <= kTwoCap);   // uniform
-    double4* const s_pos = reinterpret_cast<double4*>(s_acc + (two ? 2 * kTwoCap : kAcc));
+    double4* const s_pos = reinterpret_cast<double4*>(s_acc + (kTwo ? 2 * kTwoCap : kAcc));
     double* const s_phi = reinterpret_cast<double*>(s_pos + kAcc);   // R2 alone
     int rown = 0;   // the column's own range
     for (int r = 0; r < kMaxRanges; ++r)
@@ -864,7 +864,7 @@ __device__ __forceinline__ void push_column(const AdjArgs& A, double* __restrict
                             double xr;
                             if (quantize(x, X, xr)) {
                                 atomicAdd(&s_acc[tc], X);
-                                if (two) {   // uniform
+                                if constexpr (kTwo) {
                                     // the rest (exact, at most 1/2) to an integer of at most 50 bits:
                                     // the low bits of its sum with 1.5 2^52
                                     const double y = (x - xr) * low_scale, z = y + 0x1.8p52;
@@ -891,7 +891,7 @@ __device__ __forceinline__ void push_column(const AdjArgs& A, double* __restrict
         const int tn = Wc - t0 < kAcc ? Wc - t0 : kAcc;
         for (int t = tid; t < tn; t += kThreads) s_acc[t] = 0ull;
         for (int t = tid; t < (tn + 31) / 32; t += kThreads) s_nan[t] = 0u;
-        if (two) {
+        if constexpr (kTwo) {
             for (int t = tid; t < tn; t += kThreads) s_low[t] = 0ull;
             for (int t = tid; t < (tn + 31) / 32; t += kThreads) s_lost[t] = 0u;
         }
@@ -935,7 +935,7 @@ __device__ __forceinline__ void push_column(const AdjArgs& A, double* __restrict
                 return fma((double)(int)(unsigned int)(X >> 32), 0x1p32, (double)(unsigned int)X);
             };
             double v = ldexp(value(s_acc[t]), -k);
-            if (two) {
+            if constexpr (kTwo) {
                 v += ldexp(value(s_low[t]), -k - k2);
                 // at most 2^bl terms rounded by half a unit: below 2^-53 of the total, or the mark
                 if (((s_lost[t >> 5] >> (t & 31)) & 1u) && !(fabs(v) >= ldexp(1.0, 52 + bl - k - k2)))
@@ -948,12 +948,12 @@ __device__ __forceinline__ void push_column(const AdjArgs& A, double* __restrict
     }
 }
 
-template <int D, int KERNEL, class OP>
+template <int D, int KERNEL, class OP, bool TWO>
 __global__ __launch_bounds__(OP::kThreads, 1) void k_adjoint_push(AdjArgs A, double* __restrict__ partial,
                                                                int32_t* __restrict__ wide) {
     const int64_t c = xcd_tile(blockIdx.x, gridDim.x);
     if (c >= grid_ncols<D>(A.g)) return;   // uniform over the work-group
-    push_column<D, KERNEL, OP, true, !OP::kR2>(A, partial, c, wide);
+    push_column<D, KERNEL, OP, true, TWO>(A, partial, c, wide);
 }
 
 // the listed wide columns, taken in turn by a fixed grid
@@ -1245,6 +1245,23 @@ static int launch_dtheta(const AdjArgs& a, const MapParams& mp, double* dtheta, 
     return VCT_OK;
 }
 
+// the push form of d/dphi after the longest row is known
+template <int D, int KERNEL, bool TWO>
+static int launch_push(const AdjArgs& a, int64_t ncols, hipStream_t s) {
+    VCT_LAUNCH("k_adjoint_push", (k_adjoint_push<D, KERNEL, PushLap, TWO>), dim3((unsigned)ncols),
+               dim3(PushLap::kThreads), 0, s, a, a.partial, a.wide);
+    VCT_LAUNCH_CHECK();
+    if (a.wide_cols) {
+        VCT_LAUNCH("k_adjoint_push (wide)", (k_adjoint_push_wide<D, KERNEL, PushLap, TWO>), dim3(256),
+                   dim3(PushLap::kThreads), 0, s, a, a.partial, a.wide);
+        VCT_LAUNCH_CHECK();
+    }
+    VCT_LAUNCH("k_adjoint_combine", (k_adjoint_combine<D, KERNEL, TWO>), dim3((unsigned)((a.n + 255) / 256)), dim3(256),
+               0, s, a, a.dphi);
+    VCT_LAUNCH_CHECK();
+    return VCT_OK;
+}
+
 // overlap: run d/dtheta on the calling thread's second stream, forked from
 // and joined back into s (not for the allocation-free entry point, whose
 // first call must not create streams)
@@ -1277,19 +1294,8 @@ static int launch_adjoint(AdjArgs a, int64_t cap, const MapParams& mp, double* d
                        a.row_ptr, a.wide);
             VCT_LAUNCH_CHECK();
         }
-        VCT_LAUNCH("k_adjoint_push", (k_adjoint_push<D, KERNEL, PushLap>), dim3((unsigned)ncols), dim3(PushLap::kThreads),
-                   0, s, a, a.partial, a.wide);
-        VCT_LAUNCH_CHECK();
-        if (a.wide_cols && a.two_only)
-            VCT_LAUNCH("k_adjoint_push (wide)", (k_adjoint_push_wide<D, KERNEL, PushLap, true>), dim3(256),
-                       dim3(PushLap::kThreads), 0, s, a, a.partial, a.wide);
-        else if (a.wide_cols)
-            VCT_LAUNCH("k_adjoint_push (wide)", (k_adjoint_push_wide<D, KERNEL, PushLap, false>), dim3(256),
-                       dim3(PushLap::kThreads), 0, s, a, a.partial, a.wide);
-        VCT_LAUNCH_CHECK();
-        VCT_LAUNCH("k_adjoint_combine", (k_adjoint_combine<D, KERNEL, true>), dim3((unsigned)((n + 255) / 256)),
-                   dim3(256), 0, s, a, a.dphi);
-        VCT_LAUNCH_CHECK();
+        const int st = a.two ? launch_push<D, KERNEL, true>(a, ncols, s) : launch_push<D, KERNEL, false>(a, ncols, s);
+        if (st) return st;
     }
     if (side) {
         VCT_HIP_CHECK(hipStreamWaitEvent(s, side->join, 0));
@@ -1313,7 +1319,7 @@ static int launch_r2(AdjArgs a, int64_t cap, const MapParams& mp, double* gz, do
     a.r2h = r2h;
     a.r2b = r2b;
     a.rowsum = r2b;   // each column reads its particles' bounds before it writes their row sums
-    VCT_LAUNCH("k_adjoint_push (R2)", (k_adjoint_push<D, KERNEL, PushR2>), dim3((unsigned)ncols), dim3(PushR2::kThreads), 0,
+    VCT_LAUNCH("k_adjoint_push (R2)", (k_adjoint_push<D, KERNEL, PushR2, false>), dim3((unsigned)ncols), dim3(PushR2::kThreads), 0,
                s, a, a.partial, a.wide);
     VCT_LAUNCH_CHECK();
     if (a.wide_cols)
@@ -1450,7 +1456,7 @@ static int adjoint_run(const vct_nlist* nl, const double* pos_sorted, const doub
     }
     a.nrows = n_out_rows(dim, out_mask);
     a.wbuf = wbuf; a.rowsum = rowsum; a.partial = partial; a.wide = wide; a.dphi = dphi;
-    a.two_only = mapped;
+    a.two = mapped || n <= kOwnMaxDeg;
     a.wide_cols = nl->wide_particles != 1;
     const int64_t cap = ncols + n / kChunk + 1;
     // (the allocation-free entry point makes no stream)

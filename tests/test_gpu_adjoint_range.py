@@ -1,8 +1,8 @@
 """d/dphi of cotangents that range over many orders of magnitude inside a cell
 column: every particle's sum is as accurate as FP64 sums of its own terms,
 however large the others' are, in every form: transposed, push with records in
-LDS, push in passes.  (Columns of over 3,200 window particles keep one word per
-sum in a list without the transposed-entry map: there the bar is relative to the
+LDS, push in passes.  (Lists of more than 10,240 particles without the
+transposed-entry map keep one word per sum: there the bar is relative to the
 largest.)  The bar is per particle, against sums of weights formed
 here in FP64 from the same state: 64 u of its own sum of |terms|, the terms of
 a weight taken by magnitude and the kernel shape with its slope (a rounding of
@@ -55,6 +55,7 @@ SETS = {
     "2d": lambda: I.small("bfe2d"),
     "2d-tall": lambda: I.make_2d(40, 700, 1.0, 0.10),       # 3 x 2,154
     "2d-between": lambda: I.make_2d(40, 380, 1.0, 0.10),    # 3 x 1,170: records and one word in LDS, not two
+    "2d-between-small": lambda: I.make_2d(24, 380, 1.0, 0.10),
 }
 
 
@@ -117,7 +118,7 @@ def test_each_particle_by_its_own_terms(name):
     g = vct.Geometry(w.pos, w.vol, w.lo, w.hi, w.R, w.kernel, device=DEV, keep_col=True)
     assert g.moments(w.mapspec, MASK) == vct.VCT_OK
     wide = columns(g) > 3200
-    assert wide.any() == (name == "3d-tower" or "tall" in name or name == "2d-between"), name
+    assert wide.any() == (name == "3d-tower" or "tall" in name or "between" in name), name
     perm = g.perm[: g.n].long().cpu().numpy()
     win, col_t, count = g.nl.chunk_win, g.nl.col_t, g.nl.wide_particles
     for kind in ("normal", "depth6", "depth12", "depth30", "gauss", "random", "spikes"):
@@ -125,12 +126,12 @@ def test_each_particle_by_its_own_terms(name):
         u = torch.as_tensor(uh, device=DEV)
         ref, mag = sums(g, w, uh)
         for form in ("auto", "transposed", "push", "passes"):   # (passes: wide columns in a list with the map)
-            one_word = form == "push" and (columns(g) > 3200).any()
+            one_word = form == "push" and g.n > 10240
             if one_word and kind != "normal":
                 continue
             g.nl.chunk_win = None if form == "transposed" else win
             g.nl.col_t = None if form == "push" else col_t
-            if form == "passes" and not (name.endswith("tall-small")):
+            if form == "passes" and not name.endswith("-small"):
                 continue
             g.nl.wide_particles = 0 if form == "passes" else count   # (0: a small set then takes the push form)
             got = g.adjoint(u, want_dtheta=False)[0].cpu().numpy()
