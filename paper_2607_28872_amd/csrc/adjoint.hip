@@ -636,7 +636,15 @@ __device__ __forceinline__ void push_column(const AdjArgs& A, double* __restrict
     __syncthreads();
     const int Wc = s_cw.off[s_cw.nr];
     if (FAST && Wc > (kTwo ? kTwoCap : kAcc)) {   // uniform: left to the wide pass
-        if (tid == 0) wide[kWideList + atomicAdd(&wide[kWideCount], 1)] = (int32_t)c;
+        if (A.wide_cols) {
+            if (tid == 0) wide[kWideList + atomicAdd(&wide[kWideCount], 1)] = (int32_t)c;
+        } else {   // a list that claims to have none: no pass follows, and no count was cleared
+            for (int t = tid; t < Wc; t += kThreads) {
+                int r = 0;
+                for (int kk = 1; kk < s_cw.nr; ++kk) r = t >= s_cw.off[kk] ? kk : r;
+                partial[(int64_t)s_slot[r] * n + s_cw.gstart[r] + (t - s_cw.off[r])] = __builtin_nan("");
+            }
+        }
         return;
     }
     double4* const s_pos = reinterpret_cast<double4*>(s_acc + (kTwo ? 2 * kTwoCap : kAcc));

@@ -84,3 +84,14 @@ def test_workspace_of_the_form(name):
         else:
             with pytest.raises(vct.VctError):
                 vct.vct_apply_ops_adjoint(*args)
+
+
+@pytest.mark.parametrize("keep_col", [True, False])
+def test_wrong_count_of_wide_columns_shows(keep_col):
+    """A list that claims to have no wide column, and has: NaN there, not a sum left out."""
+    w = I.make_2d(12, 800, 1.0, 0.10)
+    g = vct.Geometry(w.pos, w.vol, w.lo, w.hi, w.R, w.kernel, device=DEV, keep_col=keep_col)
+    g.moments(w.mapspec, MASK)
+    assert (columns(g) > 3200).all() and g.nl.wide_particles == 1 + g.n
+    g.nl.wide_particles = 1
+    assert torch.isnan(g.adjoint(torch.ones(g.n, dtype=torch.float64, device=DEV), want_dtheta=False)[0]).all()
