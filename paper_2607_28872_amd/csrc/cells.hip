@@ -967,9 +967,10 @@ namespace vct {
 // Those reads confirm the first entry of every run; that each of the others has
 // its transpose too is confirmed over the whole set: the sum of
 // a(i) b(j) - b(i) a(j) over the entries (i, j), a and b two hash values of 32
-// bits (multipliers from the golden ratio and the roots of 2 and 3), in 64-bit integers is zero if every entry has its transpose, and with
-// an entry that has none it is zero by a chance of about 2^-32.  (Reading every
-// entry of the runs as well takes 0.35 ms more.)
+// bits (multipliers from the golden ratio and the roots of 2 and 3), in 64-bit
+// integers is zero if every entry has its transpose, and with an entry that has
+// none it is zero by a chance of about 2^-32.  (Reading every entry of the runs
+// as well takes 0.35 ms more.)
 struct SymPair {
     uint64_t a, b;
 };
@@ -1059,7 +1060,8 @@ __global__ __launch_bounds__(kTThreads) void k_col_transpose(Grid g, const int64
     const int64_t tail = rb + lane + (int64_t)kLanes * kTSlots;
     bool bad = false;   // an entry that is not in the window, or a run that is not in its place
 #pragma unroll
-    for (int s = 0; s < kTSlots; ++s) bad = bad || (rb + lane + (int64_t)kLanes * s < re && (unsigned)tt[s] >= (unsigned)W);
+    for (int s = 0; s < kTSlots; ++s)
+        bad = bad || (rb + lane + (int64_t)kLanes * s < re && (unsigned)tt[s] >= (unsigned)W);
     for (int64_t e = tail; e < re; e += kLanes) bad = bad || (unsigned)offset_of(e) >= (unsigned)W;
     uint64_t sa = 0, sb = 0;   // sums of a(j) and b(j) over the lane's entries
     for (int s0 = 0; s0 < W; s0 += kTWin) {
